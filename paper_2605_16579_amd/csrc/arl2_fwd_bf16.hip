@@ -1,9 +1,9 @@
 // Read-only denoising pass on bf16 MFMA (gfx950):
 //   out = softmax(q k^T * sm_scale) v + g * L2Norm(q) S            paper Eq. (2), (3), (5), (6)
 //
-// One workgroup (8 wavefronts, two per SIMD, 256 registers each) owns 256 query rows of one
-// (stream, head); each wavefront owns 32 of them.  Everything is computed transposed so that
-// no operand is re-laid out between the two GEMMs:
+// One workgroup (8 wavefronts, two per SIMD, 256 registers each) owns 256 query rows of one (stream, head), each
+// wavefront 32 of them, or half a tile, 128 rows, with two wavefronts on the same rows and half of every key tile
+// each.  Everything is computed transposed so that no operand is re-laid out between the two GEMMs:
 //
 //   S^T[kv][q]  = K[kv][:] . Q[q][:]      A = K tile rows from LDS,  B = Q fragments in registers
 //   O^T[d][q]  += V^T[d][kv] . P^T[kv][q] A = V^T fragments from LDS, B = exp'd S^T accumulators
@@ -15,29 +15,28 @@
 // V^T fragments come from the row-major V tile in LDS through the transposing LDS read
 // (ds_read_b64_tr_b16), four keys per read.
 //
-// Per key tile every wavefront runs S = K Q^T (16 MFMAs), the online softmax of its 32 logits
-// per lane (VALU), then O += V^T P^T (16 MFMAs).  On this hardware a wavefront does not overlap
-// its own VALU work with its own MFMAs; the overlap comes from the second wavefront on the
-// same SIMD, which the MFMA arbitration keeps about one phase behind the first.  Inside an MFMA
-// chain every step issues one MFMA and the LDS read of the operand fragment needed seven MFMAs
-// later, across chain boundaries, so the matrix pipe never waits for LDS latency.
-//
-// K/V tiles travel HBM/L2 -> registers (buffer loads, zero beyond the last key) -> a 3-stage
-// LDS ring with one workgroup barrier per tile.  The softmax is optimistic: probabilities are
-// taken relative to the running maximum as it stands, and only when a lane's share of the row
-// sum shows that a logit exceeded it by more than ~2^7 (or on the first tile) is the true tile
-// maximum computed, the running maximum raised, the accumulators rescaled and the tile redone.
-// This removes the per-tile maximum reduction and the accumulator rescale from the steady
-// state without changing the normalised result.  (Row sums use plain fp32 adds: the bf16
-// dot-product instruction measured far slower next to MFMAs.)
+// The unit of the schedule is a slot, the softmax of one 32-key block beside the first GEMM of the next block and the
+// second GEMM of the previous one (see `slot`).  K/V tiles travel HBM/L2 -> registers (buffer loads, zero beyond the
+// last key) -> an LDS ring with one workgroup barrier per tile.  The softmax is optimistic: the running maximum
+// starts as the first block's, probabilities are taken relative to it as it stands, and only when a lane's share of
+// the row sum shows that a logit exceeded it by more than ~2^7 is the block maximum computed, the running maximum
+// raised, the accumulators rescaled and the block redone.  This removes the per-block maximum reduction and the
+// accumulator rescale from the steady state without changing the normalised result.  (Row sums use plain fp32 adds:
+// the bf16 dot product measured far slower next to MFMAs, and so did 4 x 4 x 4 MFMAs against a matrix of ones.)
 //
 // Epilogue (fused linear readout): O_inter^T[e][q] = S^T[e][d] . Q^T[d][q] with the fp32
-// state split into bf16 hi + lo parts, staged row-major through the (now free) LDS and read
+// state split into bf16 hi + lo parts, staged row-major through LDS and read
 // transposed like V, the raw bf16 q fragments as B operand, and the L2 norm of q applied as an
 // fp32 per-column scale.  The linear branch may read a query of its own (Eq. (3): RoPE(phi_q(Q))):
 // either given as an array, or computed here from the pre-map rows and the head's D x D matrix, in
 // which case the rotated, rounded accumulators of that small GEMM are used as the B fragments
 // directly.  The gate is one value per (token, head) (Eq. (6)), per token, or per output feature.
+//
+// What bounds it: the matrix cores and, on real data, the power they draw (a launch that fills the chip holds the
+// clock at 1.73 GHz).  Measured for one pass with state and gate, 12 heads x 128:
+//   4680 tokens (228 tiles of 256 rows)   128 us; 1560 tokens (156 half tiles) 26 us, 43 us with 84 whole tiles;
+//   2 x 3 heads, 328 tokens: 11 us, 17 us before (query rows loaded fragment by fragment, the tiles of the prologue one
+//   after the other, the first block's exponentials computed twice, whole tiles).
 #include "arl2_device.h"
 
 #include <type_traits>
@@ -45,14 +44,15 @@
 namespace arl2 {
 namespace {
 
-constexpr int BM = 256;   // query rows per workgroup
 constexpr int BN = 64;    // keys per tile
 constexpr int NT = 512;   // threads per workgroup
 constexpr int NSTAGE = 4; // LDS ring depth (a power of two)
 constexpr int kStoreStep0 = 4;   // the tile copy's LDS writes go into steps 4, 6, ... of an interval's second slot
 
-template <int D>
+template <int D, int KG>
 struct FwdCfg {
+    static constexpr int BM = 256 / KG;          // query rows per workgroup
+    static constexpr int RG = 8 / KG;            // wavefronts that share their rows' keys with KG - 1 others each
     static constexpr int KS = D / 16;            // k-steps of the QK^T contraction
     static constexpr int DB = D / 32;            // 32-row blocks of O^T
     static constexpr int CPR = D / 8;            // 16-byte chunks per row
@@ -61,7 +61,8 @@ struct FwdCfg {
     static constexpr int K_BYTES = BN * KROW;
     static constexpr int V_BYTES = BN * VROW;
     static constexpr int STAGE = K_BYTES + V_BYTES;   // one K/V tile
-    static constexpr int KV_BYTES = NSTAGE * STAGE;
+    static constexpr int KV_BYTES = (KG == 1 ? NSTAGE : 2) * STAGE;
+    static constexpr int DBW = DB / KG;          // 32-feature blocks of the output that a wavefront finishes
     static constexpr int SS_BYTES = D * VROW;    // one bf16 part of the state staged [d][e]
     static constexpr int ST_BYTES = 2 * SS_BYTES;
     static constexpr int SCH = (D * CPR + NT - 1) / NT;   // 8-float state pieces per thread
@@ -70,12 +71,18 @@ struct FwdCfg {
     static constexpr int WH_BYTES = (D / 2) * KROW;
     static constexpr int TST = D / 2 + 2;        // floats per staged table row (conflict-free 8-byte reads)
     static constexpr int TAB_BYTES = 2 * 32 * TST * 4;
-    static constexpr int FM_BYTES = WH_BYTES + (NT / 64) * TAB_BYTES;
+    static constexpr int FM_BYTES = WH_BYTES + RG * TAB_BYTES;
     static constexpr int WCH = ((D / 2) * CPR + NT - 1) / NT;     // 16-byte chunks of the Wq half per thread
     static constexpr int TCH = 32 * (D / 8) / 64;                 // 16-byte chunks of one table tile per lane
     static constexpr int SMEM0 = (KV_BYTES > ST_BYTES ? (KV_BYTES > OUT_BYTES ? KV_BYTES : OUT_BYTES)
                                                       : (ST_BYTES > OUT_BYTES ? ST_BYTES : OUT_BYTES));
-    static constexpr int SMEM = SMEM0 > FM_BYTES ? SMEM0 : FM_BYTES;
+    static constexpr int SMEM1 = SMEM0 > FM_BYTES ? SMEM0 : FM_BYTES;
+    // with two key groups the ring is half as large and the state has room of its own behind it
+    static constexpr int S_OFF = KG == 1 ? 0 : KV_BYTES;
+    static constexpr int ML_OFF = KG == 1 ? SMEM1 : (KV_BYTES + ST_BYTES > SMEM1 ? KV_BYTES + ST_BYTES : SMEM1);
+    static constexpr int SMEM = ML_OFF + (KG == 1 ? 0 : 8 * 2 * 32 * 4);
+    static_assert(SMEM <= 160 * 1024, "more LDS than a CU has");
+    static_assert(KG == 1 || 8 * DBW * 16 * 64 * 4 <= KV_BYTES, "the partial outputs pass through the ring");
     static constexpr int KCH = BN * CPR / NT;    // 16-byte chunks per thread per tile (K and V each)
     static constexpr int ROWS_PER_PASS = NT / CPR;
     static constexpr int S_LEN = KS;             // MFMAs of the S^T chain of one 32-key block
@@ -101,83 +108,102 @@ struct FwdCfg {
 constexpr float kRowSumLimit = 4096.0f;
 
 
-template <int D>
-__global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles, float scale_log2, int ragged_last)
+// Query tile qt (of 256 / KG rows) of (stream, head) bh, by one workgroup.
+template <int D, int KG, bool FUSED_MAP>
+__device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int bh, int qt, unsigned char *smem)
 {
-    using C = FwdCfg<D>;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[C::SMEM];
+    using C = FwdCfg<D, KG>;
+    constexpr int BM = C::BM;
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, c = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, c = lane & 31, hh = lane >> 5;
+    const int rg = wave % C::RG, kg = wave / C::RG;       // row group and key group of this wavefront
 
-    int qt, bh;
-    if (ragged_last) {
-        // Several rounds of workgroups, and the last query tile of every head is ragged (its workgroup has
-        // idle wavefronts and finishes early): every XCD takes B H / 8 heads, their full tiles first, head
-        // by head, and their ragged tiles at the end of its dispatch order, where a short job shortens the
-        // last, partly filled round (workgroup ids go round the 8 XCDs in dispatch order).
-        const int x = blockIdx.x % kNumXcd, loc = blockIdx.x / kNumXcd;
-        const int heads_x = a.B * a.H / kNumXcd, n_full = n_qtiles - 1;
-        if (loc < heads_x * n_full) {
-            bh = x * heads_x + loc / n_full;
-            qt = loc % n_full;
-        } else {
-            bh = x * heads_x + (loc - heads_x * n_full);
-            qt = n_full;
-        }
-    } else {
-        const int work = xcd_contiguous_id(blockIdx.x, gridDim.x);
-        qt = work % n_qtiles;
-        bh = work / n_qtiles;
-    }
     const int h = bh % a.H, b = bh / a.H;
     const int H = a.H, Lq = a.Lq, Lkv = a.Lkv;
 
-    const bf16_t *qg = (const bf16_t *)a.q;
-    const bf16_t *kg = (const bf16_t *)a.k + ((size_t)b * Lkv * H + h) * D;
-    const bf16_t *vg = (const bf16_t *)a.v + ((size_t)b * Lkv * H + h) * D;
+    const bf16_t *kgl = (const bf16_t *)a.k + ((size_t)b * Lkv * H + h) * D;
+    const bf16_t *vgl = (const bf16_t *)a.v + ((size_t)b * Lkv * H + h) * D;
     const uint32_t tok_bytes = (uint32_t)H * D * 2;                       // one token, all heads
     const uint32_t kv_range = (uint32_t)(Lkv - 1) * tok_bytes + 2 * D;    // bytes of this head's K (or V) slice
-    const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(kg, kv_range);
-    const __amdgpu_buffer_rsrc_t v_rsrc = make_rsrc(vg, kv_range);
+    const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(kgl, kv_range);
+    const __amdgpu_buffer_rsrc_t v_rsrc = make_rsrc(vgl, kv_range);
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane (c, hh) holds Q[row][16 t + 8 hh + 0..7]
-    const int q0 = qt * BM + wave * 32;
+    const int q0 = qt * BM + rg * 32;
     const int qrow = q0 + c;
     bf16x8 qf[C::KS];
-    float qss = 0.f;
-    {
-        const bf16_t *qp = qg + ((size_t)(b * (size_t)Lq + (qrow < Lq ? qrow : 0)) * H + h) * D + 8 * hh;
+    float qss = 0.f;                  // |row|^2 over the full head dimension
+    // The rows travel whole (16-byte chunks, D / 8 lanes per row) through LDS rows of KROW bytes to the fragments:
+    // fragment loads straight from memory touch 32 cache lines per instruction.  The key groups of a row group move
+    // a share of its rows each.  Rows past the last query read as zero.
+    constexpr int QCH = 32 * C::CPR / 64 / KG;             // chunks per lane
+    const int q_rows = Lq - qt * BM < BM ? Lq - qt * BM : BM;
+    const __amdgpu_buffer_rsrc_t q_rsrc = make_rsrc((const bf16_t *)a.q + ((size_t)(b * (size_t)Lq + qt * BM) * H + h) * D,
+                                                    (uint32_t)(q_rows - 1) * tok_bytes + 2 * D);
+    auto fetch_rows = [&](u32x4 *x) {
 #pragma unroll
-        for (int t = 0; t < C::KS; ++t) {
-            bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (qrow < Lq) x = *(const bf16x8 *)(qp + 16 * t);
-            qf[t] = x;
+        for (int i = 0; i < QCH; ++i) {
+            const int id = lane + 64 * (kg * QCH + i);
+            x[i] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, (uint32_t)(32 * rg + id / C::CPR) * tok_bytes + 16 * (id % C::CPR), 0, 0);
+        }
+    };
+    auto put_rows = [&](unsigned char *dst, const u32x4 *x) {
+#pragma unroll
+        for (int i = 0; i < QCH; ++i) {
+            const int id = lane + 64 * (kg * QCH + i);
+            *(u32x4 *)(dst + (id / C::CPR) * C::KROW + 16 * (id % C::CPR)) = x[i];
+        }
+    };
+    auto get_rows = [&](const unsigned char *src) {
+#pragma unroll
+        for (int t = 0; t < C::KS; ++t) qf[t] = *(const bf16x8 *)(src + c * C::KROW + 32 * t + 16 * hh);
+    };
+    // the same fragments straight from memory (the other query arrays of the epilogue)
+    const size_t row_off = ((size_t)(b * (size_t)Lq + (qrow < Lq ? qrow : 0)) * H + h) * D;   // rows past the last query read row 0, unused
+    auto load_rows = [&](const bf16_t *src, bf16x8 *x) {
+#pragma unroll
+        for (int t = 0; t < C::KS; ++t) x[t] = *(const bf16x8 *)(src + row_off + 8 * hh + 16 * t);
+    };
+    auto square_rows = [&]() {
+        qss = 0.f;
+#pragma unroll
+        for (int t = 0; t < C::KS; ++t)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float f = (float)x[j];
+                const float f = (float)qf[t][j];
                 qss = fmaf(f, f, qss);
             }
-        }
-        qss = xhalf_sum(qss);   // |q_row|^2 over the full head dimension
-    }
+        qss = xhalf_sum(qss);
+    };
 
     // ---- global -> registers -> LDS copies: 16-byte chunks, chunk id = tid + NT*i -> (row, col)
     u32x4 kst[C::KCH], vst[C::KCH];
-    uint32_t g_off = (uint32_t)(tid / C::CPR) * tok_bytes + 16 * (tid % C::CPR);   // chunk 0 of tile 0
+    const uint32_t g_off0 = (uint32_t)(tid / C::CPR) * tok_bytes + 16 * (tid % C::CPR);   // chunk 0 of tile 0
     const int lds_k_off = (tid / C::CPR) * C::KROW + 16 * (tid % C::CPR);
     const int lds_v_off = (tid / C::CPR) * C::VROW + 16 * (tid % C::CPR);
+    uint32_t g_off = g_off0;          // chunk 0 of the next tile to load
 
-    auto load_tile = [&]() {       // loads the tile at g_off and advances g_off by one tile
+    auto load_k = [&](int tile, u32x4 *x) {
 #pragma unroll
-        for (int i = 0; i < C::KCH; ++i) {
-            const uint32_t off = g_off + (uint32_t)i * C::ROWS_PER_PASS * tok_bytes;
-            kst[i] = __builtin_amdgcn_raw_buffer_load_b128(k_rsrc, off, 0, 0);
-            vst[i] = __builtin_amdgcn_raw_buffer_load_b128(v_rsrc, off, 0, 0);
-        }
-        g_off += BN * tok_bytes;
+        for (int i = 0; i < C::KCH; ++i)
+            x[i] = __builtin_amdgcn_raw_buffer_load_b128(k_rsrc, g_off0 + (uint32_t)(tile * BN + i * C::ROWS_PER_PASS) * tok_bytes, 0, 0);
     };
-    // the same copy in pieces: part h of the loads (chunk h of K and of V), piece p of the stores
+    auto load_v = [&](int tile, u32x4 *x) {
+#pragma unroll
+        for (int i = 0; i < C::KCH; ++i)
+            x[i] = __builtin_amdgcn_raw_buffer_load_b128(v_rsrc, g_off0 + (uint32_t)(tile * BN + i * C::ROWS_PER_PASS) * tok_bytes, 0, 0);
+    };
+    auto store_k = [&](int stage, const u32x4 *x) {
+#pragma unroll
+        for (int i = 0; i < C::KCH; ++i) *(u32x4 *)(smem + stage * C::STAGE + lds_k_off + i * C::ROWS_PER_PASS * C::KROW) = x[i];
+    };
+    auto store_v = [&](int stage, const u32x4 *x) {
+#pragma unroll
+        for (int i = 0; i < C::KCH; ++i)
+            *(u32x4 *)(smem + stage * C::STAGE + C::K_BYTES + lds_v_off + i * C::ROWS_PER_PASS * C::VROW) = x[i];
+    };
+    // the same copy in pieces.  One key group: the loads of a tile (chunk h of K and of V), its stores (piece p).
     auto load_tile_part = [&](auto h_) {
         constexpr int h = decltype(h_)::value;
         const uint32_t off = g_off + (uint32_t)h * C::ROWS_PER_PASS * tok_bytes;
@@ -191,14 +217,15 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
         if constexpr ((p & 1) == 0) *(u32x4 *)(smK + lds_k_off + (p >> 1) * C::ROWS_PER_PASS * C::KROW) = kst[p >> 1];
         else *(u32x4 *)(smK + C::K_BYTES + lds_v_off + (p >> 1) * C::ROWS_PER_PASS * C::VROW) = vst[p >> 1];
     };
-    auto store_tile = [&](int stage) {
-        unsigned char *smK = smem + stage * C::STAGE;
-        unsigned char *smV = smK + C::K_BYTES;
-#pragma unroll
-        for (int i = 0; i < C::KCH; ++i) {
-            *(u32x4 *)(smK + lds_k_off + i * C::ROWS_PER_PASS * C::KROW) = kst[i];
-            *(u32x4 *)(smV + lds_v_off + i * C::ROWS_PER_PASS * C::VROW) = vst[i];
-        }
+    // Several key groups, interval j: piece p of K(j + 2) or V(j) from its register into LDS, then the same piece
+    // of K(j + 3) or V(j + 1) is requested (g_off: V(j + 1)).
+    auto copy_part = [&](int stage, auto p_) {
+        constexpr int p = decltype(p_)::value, h = p >> 1;
+        store_tile_part(stage, p_);
+        const uint32_t off = g_off + (uint32_t)h * C::ROWS_PER_PASS * tok_bytes;
+        if constexpr ((p & 1) == 0) kst[h] = __builtin_amdgcn_raw_buffer_load_b128(k_rsrc, off + 2 * BN * tok_bytes, 0, 0);
+        else vst[h] = __builtin_amdgcn_raw_buffer_load_b128(v_rsrc, off, 0, 0);
+        if constexpr (p == 2 * C::KCH - 1) g_off += BN * tok_bytes;
     };
 
     // lane roles inside a 32-key block
@@ -212,14 +239,24 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
     bf16x8 fr[C::RING];          // A-operand fragments in flight from LDS
     float m_run = -INFINITY;     // running max of scaled logits (log2 domain)
     float l_run = 0.f;           // this lane's share of the running sum
+    auto clear_output = [&]() {
 #pragma unroll
-    for (int db = 0; db < C::DB; ++db)
+        for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
+            for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
+    };
 
-    // Byte offsets in the ring of the K rows / V rows of 32-key block `blk` (tile blk / 2, half blk % 2).
-    auto k_block = [&](int blk) -> int { return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * 32 * C::KROW; };
-    auto v_block = [&](int blk) -> int { return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * 32 * C::VROW; };
+    // Byte offsets in the ring of the K rows / V rows of this wavefront's 32-key block `blk`: half blk % 2 of tile
+    // blk / 2, or with two key groups half kg of tile blk.
+    auto k_block = [&](int blk) -> int {
+        if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * 32 * C::KROW;
+        else return (blk & 1) * C::STAGE + kg * 32 * C::KROW;
+    };
+    auto v_block = [&](int blk) -> int {
+        if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * 32 * C::VROW;
+        else return (blk & 1) * C::STAGE + C::K_BYTES + kg * 32 * C::VROW;
+    };
+    auto first_key = [&](int blk) -> int { return KG == 1 ? 32 * blk : BN * blk + 32 * kg; };
     // A-operand fragments: k-step n of S^T = K Q^T (a K row piece), and MFMA n of O^T += V^T P^T
     // (16-key step n / DB, row block n % DB: a transposed V piece).
     auto k_frag = [&](const unsigned char *kp, auto n_) -> bf16x8 {
@@ -238,14 +275,14 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
         constexpr int PAR = decltype(par_)::value;
         const float mneg = -m_run;
         float psum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
+        static_for<0, 8>([&](auto r_) {
+            constexpr int r = 2 * decltype(r_)::value;
             const float p0 = __builtin_amdgcn_exp2f(fmaf(s_acc[PAR][r], scale_log2, mneg));
             const float p1 = __builtin_amdgcn_exp2f(fmaf(s_acc[PAR][r + 1], scale_log2, mneg));
             psum += p0 + p1;
             pf[2 * PAR + (r >> 3)][r & 7] = to_bf16(p0);
             pf[2 * PAR + (r >> 3)][(r & 7) + 1] = to_bf16(p1);
-        }
+        });
         return psum;
     };
 
@@ -259,7 +296,10 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
     // logit v+1, sum and conversion of logit v) so that no instruction waits for the one before it.
     // copy_: 0 nothing; 1 this slot also requests the next K/V tile from global memory (early steps);
     // 2 it also writes that tile, by now in registers, into ring stage `cstage`, one 16-byte piece per thread
-    // every other step, so that the copy runs under the MFMAs instead of in a burst before the barrier.
+    // every other step, so that the copy runs under the MFMAs instead of in a burst before the barrier; 3 (several key
+    // groups) the whole copy of an interval and its barrier, as soon as the slot has requested its last fragment: the
+    // fragments requested after that are the next slot's, from the tiles that the barrier publishes; 4 the same for the last
+    // tile, whose V is all that is left to store.
     auto slot = [&](auto par_, auto has_s_, auto has_pv_, auto next_s_, auto masked_, int j, auto copy_, int cstage) {
         constexpr int PAR = decltype(par_)::value;
         constexpr int COPY = decltype(copy_)::value;
@@ -279,7 +319,7 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
             if constexpr (v < 16) {
                 if constexpr (MASKED) {              // keys past the end of the sequence (last tile only)
                     const int kvl = 8 * (v >> 2) + 4 * hh + (v & 3);
-                    if (32 * j + kvl >= Lkv) s_acc[PAR][v] = -INFINITY;
+                    if (first_key(j) + kvl >= Lkv) s_acc[PAR][v] = -INFINITY;
                 }
                 x[v] = fmaf(s_acc[PAR][v], scale_log2, mneg);
             }
@@ -334,6 +374,16 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
             if constexpr (COPY == 1 && (n & 1) == 1 && n / 2 < C::KCH) load_tile_part(std::integral_constant<int, n / 2>{});
             if constexpr (COPY == 2 && n >= kStoreStep0 && n < kStoreStep0 + 4 * C::KCH && ((n - kStoreStep0) & 1) == 0)
                 store_tile_part(cstage, std::integral_constant<int, (n - kStoreStep0) / 2>{});
+            if constexpr (COPY >= 3) {
+                static_for<0, 2 * C::KCH>([&](auto p_) {
+                    constexpr int p = decltype(p_)::value;
+                    if constexpr (p * (NS - C::PF) / (2 * C::KCH) == n) {
+                        if constexpr (COPY == 3) copy_part(PAR, p_);
+                        else if constexpr (p & 1) store_tile_part(PAR, p_);
+                    }
+                });
+                if constexpr (n == NS - C::PF - 1) lds_barrier();
+            }
             if constexpr (n == 0) {
                 op_scale(std::integral_constant<int, 0>{});
                 op_scale(std::integral_constant<int, 1>{});
@@ -350,25 +400,24 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
         float psum = ps0 + ps1;
         // Rarely (always on the first block) a logit exceeded the running maximum by more than the
         // threshold: take the true block maximum, raise the running maximum, rescale, redo the block.
-        if (__any(!(psum < kRowSumLimit))) {      // wave-uniform; also true for inf and NaN
+        if (__builtin_expect(__any(!(psum < kRowSumLimit)), 0)) {      // wave-uniform; also true for inf and NaN
+            // (compile-time loops: the compiler unrolls nothing on a path it is told to be rare)
             float mx = s_acc[PAR][0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s_acc[PAR][r]);
+            static_for<1, 16>([&](auto r_) { mx = fmaxf(mx, s_acc[PAR][decltype(r_)::value]); });
             mx = xhalf_max(mx) * scale_log2;
             const float m_new = fmaxf(m_run, mx);
             const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
             m_run = m_new;
             l_run *= alpha;
-#pragma unroll
-            for (int db = 0; db < C::DB; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o_acc[db][r] *= alpha;
+            if constexpr (HAS_PV)
+                static_for<0, C::DB>([&](auto db_) {
+                    static_for<0, 16>([&](auto r_) { o_acc[decltype(db_)::value][decltype(r_)::value] *= alpha; });
+                });
             psum = exp_block(par_);
         }
         l_run += psum;
     };
 
-    const int ntiles = (Lkv + BN - 1) / BN;
     const std::false_type no{};
     const std::true_type yes{};
     const std::integral_constant<int, 0> par0{};
@@ -376,120 +425,282 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
     const std::integral_constant<int, 0> copy0{};
     const std::integral_constant<int, 1> copy1{};
     const std::integral_constant<int, 2> copy2{};
+    const std::integral_constant<int, 3> copy3{};
+    const std::integral_constant<int, 4> copy4{};
 
-    // ---- prologue: tiles 0 and 1 into the ring
-    load_tile();
-    store_tile(0);
-    load_tile();
-    store_tile(1);
-    __syncthreads();
-
-    // Barrier interval i covers the slots of key blocks 2i and 2i+1: they read K of tiles i and i+1 and V of
-    // tiles i-1 and i.  Tile i+2 is fetched into registers at its start and written at its end to the ring
-    // stage of tile i-2 (four stages); the barrier that closes the interval publishes it.
-    auto close_interval = [&](int i) {
-        store_tile((i + 2) & (NSTAGE - 1));
-        __syncthreads();
+    // S(0), plain: nothing to overlap it with
+    auto first_product = [&]() {
+        const unsigned char *kp = smem + k_block(0) + k_frag_off;
+        const unsigned char *np = smem + k_block(1) + k_frag_off;
+        static_for<0, C::PF>([&](auto m_) { fr[decltype(m_)::value] = k_frag(kp, m_); });
+        static_for<0, C::S_LEN>([&](auto n_) {
+            constexpr int n = decltype(n_)::value;
+            constexpr int m = n + C::PF;
+            if constexpr (m < C::S_LEN) fr[m % C::RING] = k_frag(kp, std::integral_constant<int, m>{});
+            else fr[m % C::RING] = k_frag(np, std::integral_constant<int, m - C::S_LEN>{});
+            if constexpr (n == 0) {
+                const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[n], zero, 0, 0, 0);
+            } else {
+                s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[n], s_acc[0], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
     };
-
-    if (q0 < Lq) {
-        // S(0), plain: nothing to overlap it with
-        {
-            const unsigned char *kp = smem + k_block(0) + k_frag_off;
-            const unsigned char *np = smem + k_block(1) + k_frag_off;
-            static_for<0, C::PF>([&](auto m_) { fr[decltype(m_)::value] = k_frag(kp, m_); });
-            static_for<0, C::S_LEN>([&](auto n_) {
-                constexpr int n = decltype(n_)::value;
-                constexpr int m = n + C::PF;
-                if constexpr (m < C::S_LEN) fr[m % C::RING] = k_frag(kp, std::integral_constant<int, m>{});
-                else fr[m % C::RING] = k_frag(np, std::integral_constant<int, m - C::S_LEN>{});
-                if constexpr (n == 0) {
-                    const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                    s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[n], zero, 0, 0, 0);
-                } else {
-                    s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[n], s_acc[0], 0, 0, 0);
+    // The running maximum starts as the true maximum of the first block (which always holds a key: with two key groups
+    // Lkv > 32), so that its slot need not find out by computing every exponential twice.
+    auto first_maximum = [&]() {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int key = first_key(0) + 8 * (r >> 2) + 4 * hh + (r & 3);
+            mx = fmaxf(mx, key < Lkv ? s_acc[0][r] : -INFINITY);
+        }
+        m_run = xhalf_max(mx) * scale_log2;
+    };
+    // second GEMM of the last key block `blk` of parity P (its first fragments are in flight)
+    auto last_product = [&](auto p_, int blk) {
+        constexpr int P = decltype(p_)::value;
+        const unsigned char *vp = smem + v_block(blk) + v_frag_off;
+        static_for<0, C::PV_LEN>([&](auto n_) {
+            constexpr int n = decltype(n_)::value;
+            constexpr int m = n + C::PF;
+            if constexpr (m < C::PV_LEN) fr[m % C::RING] = v_frag(vp, std::integral_constant<int, m>{});
+            o_acc[n % C::DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], pf[2 * P + n / C::DB], o_acc[n % C::DB], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    const float *Sg = a.S != nullptr ? a.S + ((size_t)b * H + h) * D * D : nullptr;
+    unsigned char *smHi = smem + C::S_OFF, *smLo = smHi + C::SS_BYTES;
+    f32x4 sr[C::SCH][2];
+    auto load_state = [&]() {         // 8-float pieces: row id / CPR, column piece id % CPR
+#pragma unroll
+        for (int i = 0; i < C::SCH; ++i) {
+            const int id = tid + NT * i;
+            if (id < D * C::CPR) {
+                const float *sp = Sg + (size_t)(id / C::CPR) * D + 8 * (id % C::CPR);
+                sr[i][0] = *(const f32x4 *)(sp);
+                sr[i][1] = *(const f32x4 *)(sp + 4);
+            }
+        }
+    };
+    auto store_state = [&]() {        // split into bf16 hi + lo, row-major [d][e]
+#pragma unroll
+        for (int i = 0; i < C::SCH; ++i) {
+            const int id = tid + NT * i;
+            if (id < D * C::CPR) {
+                union { u32x4 u; bf16x8 v; } hi, lo;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float x = sr[i][j >> 2][j & 3];
+                    const bf16_t hb = to_bf16(x);
+                    hi.v[j] = hb;
+                    lo.v[j] = to_bf16(x - (float)hb);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            });
+                const int off = (id / C::CPR) * C::VROW + 16 * (id % C::CPR);
+                *(u32x4 *)(smHi + off) = hi.u;
+                *(u32x4 *)(smLo + off) = lo.u;
+            }
         }
-        load_tile();
-        if (ntiles == 1) {
-            slot(par0, yes, no, no, yes, 0, copy0, 0);
-            slot(par1, no, yes, no, yes, 1, copy0, 0);
-        } else {
-            slot(par0, yes, no, yes, no, 0, copy0, 0);
-            slot(par1, yes, yes, yes, no, 1, copy0, 0);
-        }
-        close_interval(0);
-#pragma unroll 1
-        for (int i = 1; i < ntiles - 1; ++i) {
-            slot(par0, yes, yes, yes, no, 2 * i, copy1, 0);
-            slot(par1, yes, yes, yes, no, 2 * i + 1, copy2, (i + 2) & (NSTAGE - 1));
-            // the writes are complete once at most the LDS reads issued after the last of them are still
-            // outstanding (LDS operations complete in order); those reads stay in flight across the barrier
-            lds_barrier_keep<C::LDS_AFTER_COPY>();
-        }
-        if (ntiles > 1) {
-            const int i = ntiles - 1;
-            slot(par0, yes, yes, no, yes, 2 * i, copy0, 0);
-            slot(par1, no, yes, no, yes, 2 * i + 1, copy0, 0);
-        }
-        // second GEMM of the last key block (its first fragments are in flight)
+    };
+    constexpr bool EARLY_STATE = KG > 1 && !FUSED_MAP;   // the state goes to LDS before the key loop
+
+    if constexpr (KG == 1) {
+        const int ntiles = (Lkv + BN - 1) / BN;
+        // ---- prologue: tiles 0 and 1 into the ring, all their loads and those of the query rows in flight together
         {
-            const unsigned char *vp = smem + v_block(2 * ntiles - 1) + v_frag_off;
-            static_for<0, C::PV_LEN>([&](auto n_) {
-                constexpr int n = decltype(n_)::value;
-                constexpr int m = n + C::PF;
-                if constexpr (m < C::PV_LEN) fr[m % C::RING] = v_frag(vp, std::integral_constant<int, m>{});
-                o_acc[n % C::DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], pf[2 + n / C::DB], o_acc[n % C::DB], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            });
+            u32x4 k1[C::KCH], v1[C::KCH], x[QCH];
+            load_k(0, kst);
+            fetch_rows(x);
+            load_v(0, vst);
+            load_k(1, k1);
+            load_v(1, v1);
+            store_k(0, kst);
+            unsigned char *mine = smem + 2 * C::STAGE + wave * 32 * C::KROW;     // in stages that tile 2 and on will use
+            static_assert(KG > 1 || 8 * 32 * C::KROW <= 2 * C::STAGE, "the query rows pass through two ring stages");
+            put_rows(mine, x);
+            store_v(0, vst);
+            store_k(1, k1);
+            store_v(1, v1);
+            get_rows(mine);
+            square_rows();
+        }
+        __syncthreads();
+        clear_output();
+
+        // Barrier interval i covers the slots of key blocks 2i and 2i+1: they read K of tiles i and i+1 and V of
+        // tiles i-1 and i.  Tile i+2 is fetched into registers at its start and written at its end to the ring
+        // stage of tile i-2 (four stages); the barrier that closes the interval publishes it.
+        auto close_interval = [&](int i) {
+            store_k((i + 2) & (NSTAGE - 1), kst);
+            store_v((i + 2) & (NSTAGE - 1), vst);
+            __syncthreads();
+        };
+        auto load_tile = [&](int tile) {
+            load_k(tile, kst);
+            load_v(tile, vst);
+        };
+        g_off += 3 * BN * tok_bytes;
+        if (q0 < Lq) {
+            first_product();
+            load_tile(2);
+            first_maximum();
+            if (ntiles == 1) {
+                slot(par0, yes, no, no, yes, 0, copy0, 0);
+                slot(par1, no, yes, no, yes, 1, copy0, 0);
+            } else {
+                slot(par0, yes, no, yes, no, 0, copy0, 0);
+                slot(par1, yes, yes, yes, no, 1, copy0, 0);
+            }
+            close_interval(0);
+#pragma unroll 1
+            for (int i = 1; i < ntiles - 1; ++i) {
+                slot(par0, yes, yes, yes, no, 2 * i, copy1, 0);
+                slot(par1, yes, yes, yes, no, 2 * i + 1, copy2, (i + 2) & (NSTAGE - 1));
+                // the writes are complete once at most the LDS reads issued after the last of them are still
+                // outstanding (LDS operations complete in order); those reads stay in flight across the barrier
+                lds_barrier_keep<C::LDS_AFTER_COPY>();
+            }
+            if (ntiles > 1) {
+                const int i = ntiles - 1;
+                slot(par0, yes, yes, no, yes, 2 * i, copy0, 0);
+                slot(par1, no, yes, no, yes, 2 * i + 1, copy0, 0);
+            }
+            last_product(par1, 2 * ntiles - 1);
+        } else {
+            // A wavefront whose 32 rows all lie past the last query (the ragged last workgroup of a head) only
+            // helps to move the tiles: the same loads, stores and barriers, no arithmetic.  Its rows are never
+            // stored.
+            load_tile(2);
+            close_interval(0);
+#pragma unroll 1
+            for (int i = 1; i < ntiles - 1; ++i) {
+                load_tile(i + 2);
+                close_interval(i);
+            }
+            l_run = 1.0f;
         }
     } else {
-        // A wavefront whose 32 rows all lie past the last query (the ragged last workgroup of a head) only
-        // helps to move the tiles: the same loads, stores and barriers, no arithmetic.  Its rows are never
-        // stored.
-        load_tile();
-        close_interval(0);
-#pragma unroll 1
-        for (int i = 1; i < ntiles - 1; ++i) {
-            load_tile();
-            close_interval(i);
+        // ---- several key groups: a wavefront works on one 32-key block of every tile, one slot per tile.  Slot j reads
+        // K(j + 1) and V(j - 1); K(j + 2) and V(j) are written during it, so two ring stages are enough.
+        const int nt0 = (Lkv + BN - 1) / BN, nt = nt0 > 1 ? nt0 : 2;     // a second, empty tile where there is only one
+        {
+            u32x4 k0[C::KCH], k1[C::KCH], x[QCH];
+            load_k(0, k0);
+            fetch_rows(x);
+            load_k(1, k1);
+            load_k(2, kst);
+            load_v(0, vst);
+            g_off += BN * tok_bytes;
+            store_k(0, k0);
+            put_rows(smem + C::S_OFF + rg * 32 * C::KROW, x);
+            static_assert(KG == 1 || C::RG * 32 * C::KROW <= C::ST_BYTES, "the query rows pass through the state's room");
+            store_k(1, k1);
         }
-        l_run = 1.0f;
+        lds_barrier();
+        if (EARLY_STATE && Sg != nullptr) load_state();      // arrives under the first products
+        if (q0 < Lq) {
+            get_rows(smem + C::S_OFF + rg * 32 * C::KROW);
+            square_rows();
+            first_product();
+            lds_barrier();            // every wavefront has read K(0), whose stage slot 0 overwrites, and its query rows
+            first_maximum();
+            slot(par0, yes, no, yes, yes, 0, copy3, 0);
+            if (EARLY_STATE && Sg != nullptr) store_state();
+            clear_output();
+            int j = 1;
+#pragma unroll 1
+            for (; j + 1 < nt - 1; j += 2) {
+                slot(par1, yes, yes, yes, no, j, copy3, 0);
+                slot(par0, yes, yes, yes, no, j + 1, copy3, 0);
+            }
+            if (j < nt - 1) {
+                slot(par1, yes, yes, yes, no, j, copy3, 0);
+                ++j;
+            }
+            // the last slot has no first product: its fragments start with V(nt - 2)
+            const unsigned char *vp = smem + v_block(j - 1) + v_frag_off;
+            static_for<0, C::PF>([&](auto m_) { fr[decltype(m_)::value] = v_frag(vp, m_); });
+            if (j & 1) {
+                slot(par1, no, yes, no, yes, j, copy4, 0);
+                last_product(par1, j);
+            } else {
+                slot(par0, no, yes, no, yes, j, copy4, 0);
+                last_product(par0, j);
+            }
+        } else {                      // rows past the last query: moves the tiles and the state only
+            lds_barrier();
+            if (EARLY_STATE && Sg != nullptr) store_state();
+            clear_output();
+#pragma unroll 1
+            for (int j = 0; j < nt; ++j) {
+                static_for<0, 2 * C::KCH>([&](auto p_) { copy_part(j & 1, p_); });
+                lds_barrier();
+            }
+            l_run = 1.0f;
+            m_run = 0.f;
+        }
     }
 
     // ---- epilogue ------------------------------------------------------------------------
-    {
-        const float inv_l = 1.0f / xhalf_sum(l_run);
+    // The output blocks that this wavefront finishes: all of its rows' features, or with several key groups a share of
+    // them, after the groups' partial results (each relative to its own maximum) have been exchanged through LDS.
+    f32x16 out[C::DBW];
+    const int db0 = KG == 1 ? 0 : C::DBW * kg;
+    l_run = xhalf_sum(l_run);
+    if constexpr (KG == 1) {
+        const float inv_l = 1.0f / l_run;
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o_acc[db][r] *= inv_l;
+            for (int r = 0; r < 16; ++r) out[db][r] = o_acc[db][r] * inv_l;
+    } else {
+        static_assert(KG <= 2, "the exchange is written for two key groups");
+        float *ml = (float *)(smem + C::ML_OFF);                       // [wavefront][maximum, sum][row]
+        f32x4 *ox = (f32x4 *)smem;                                     // [wavefront][block][register quad][lane]
+        const int peer = wave ^ C::RG;
+        ml[(wave * 2 + hh) * 32 + c] = hh ? l_run : m_run;
+        __syncthreads();                                               // the ring is no longer read
+#pragma unroll
+        for (int i = 0; i < C::DBW; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {                              // the peer's blocks go to the peer
+                f32x4 x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = kg ? o_acc[i][4 * q + e] : o_acc[C::DBW + i][4 * q + e];
+                ox[((wave * C::DBW + i) * 4 + q) * 64 + lane] = x;
+            }
+        const float m_peer = ml[peer * 2 * 32 + c], l_peer = ml[(peer * 2 + 1) * 32 + c];
+        const float mm = fmaxf(m_run, m_peer);
+        const float f0 = __builtin_amdgcn_exp2f(m_run - mm), f1 = __builtin_amdgcn_exp2f(m_peer - mm);
+        const float inv_l = 1.0f / fmaf(l_run, f0, l_peer * f1);
+        const float f = f0 * inv_l, f_peer = f1 * inv_l;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < C::DBW; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 x = ox[((peer * C::DBW + i) * 4 + q) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    out[i][4 * q + e] = fmaf(kg ? o_acc[C::DBW + i][4 * q + e] : o_acc[i][4 * q + e], f, x[e] * f_peer);
+            }
     }
 
-    if (a.S != nullptr) {
+    if (Sg != nullptr) {
+        const size_t gtok = (size_t)b * Lq + (qrow < Lq ? qrow : 0);
+        const size_t gi = a.g_per_token ? gtok : gtok * H + h;
+        float g_row = 1.0f;                                   // requested here, used after the products
+        if (a.g != nullptr && !a.g_per_element)
+            g_row = a.g_is_bf16 ? (float)((const bf16_t *)a.g)[gi] : ((const float *)a.g)[gi];
         // O_inter^T[e][q] = sum_d S[d][e] * q[q][d]: the fp32 state is split into bf16 hi + lo parts
         // (fp32 accumulate), both staged row-major [d][e] in LDS and read as S^T fragments through the
         // transposing LDS read, exactly like V.
-        const float *Sg = a.S + ((size_t)b * H + h) * D * D;
         if (a.q_lin != nullptr) {
             // the linear branch has a query of its own (Eq. (3): its feature map differs from the
             // softmax branch's): take its fragments and its squared norm instead
-            const bf16_t *qp = (const bf16_t *)a.q_lin + ((size_t)(b * (size_t)Lq + (qrow < Lq ? qrow : 0)) * H + h) * D + 8 * hh;
-            qss = 0.f;
-#pragma unroll
-            for (int t = 0; t < C::KS; ++t) {
-                bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
-                if (qrow < Lq) x = *(const bf16x8 *)(qp + 16 * t);
-                qf[t] = x;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float f = (float)x[j];
-                    qss = fmaf(f, f, qss);
-                }
-            }
-            qss = xhalf_sum(qss);
+            load_rows((const bf16_t *)a.q_lin, qf);
+            square_rows();
         }
         // Fused feature map of the linear branch (Eq. (3)): q_lin^T[e][row] = sum_d Wq[e][d] xq[row][d], rotated
         // pair by pair, is never stored: the accumulator registers, rounded to bf16, are the B fragments of
@@ -497,18 +708,11 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
         // Wq[h] passes through LDS in two halves of D/2 output rows (whole rows in, fragments out) and every
         // wavefront stages the rotation table rows of its 32 tokens in a region of its own: read straight
         // from global memory, fragment by fragment, these operands cost ~13 us of cache-line requests.
-        const bool fused_map = a.xq != nullptr;
-        if (fused_map) {
-            const size_t row_off = ((size_t)(b * (size_t)Lq + (qrow < Lq ? qrow : 0)) * H + h) * D;
+        if constexpr (FUSED_MAP) {
             bf16x8 xf[C::KS];
-#pragma unroll
-            for (int t = 0; t < C::KS; ++t) {
-                bf16x8 x = {0, 0, 0, 0, 0, 0, 0, 0};
-                if (qrow < Lq) x = *(const bf16x8 *)((const bf16_t *)a.xq + row_off + 16 * t + 8 * hh);
-                xf[t] = x;
-            }
+            load_rows((const bf16_t *)a.xq, xf);
             unsigned char *smW = smem;                                           // D/2 rows of Wq[h], KROW bytes each
-            float *cosT = (float *)(smem + C::WH_BYTES + wave * C::TAB_BYTES);   // this wavefront's [32][TST] tables
+            float *cosT = (float *)(smem + C::WH_BYTES + rg * C::TAB_BYTES);   // [32][TST] tables of this wavefront's rows
             float *sinT = cosT + 32 * C::TST;
             const bool rope = a.cs != nullptr;
             qss = 0.f;
@@ -523,7 +727,7 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
                         *(u32x4 *)(smW + wr * C::KROW + 16 * wc) =
                             *(const u32x4 *)((const bf16_t *)a.Wq + ((size_t)h * D + half * (D / 2) + wr) * D + 8 * wc);
                 }
-                if (half == 0 && rope) {
+                if (half == 0 && rope && kg == 0) {
 #pragma unroll
                     for (int i = 0; i < C::TCH; ++i) {
                         const int id = lane + 64 * i;
@@ -573,63 +777,39 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
             }
             qss = xhalf_sum(qss);
         }
-        unsigned char *smHi = smem, *smLo = smem + C::SS_BYTES;
-        __syncthreads();                              // every wave is done with the K/V ring
-#pragma unroll
-        for (int i = 0; i < C::SCH; ++i) {
-            const int id = tid + NT * i;              // 8-float piece: row id / CPR, column piece id % CPR
-            if (id < D * C::CPR) {
-                const float *sp = Sg + (size_t)(id / C::CPR) * D + 8 * (id % C::CPR);
-                const f32x4 x0 = *(const f32x4 *)(sp);
-                const f32x4 x1 = *(const f32x4 *)(sp + 4);
-                union { u32x4 u; bf16x8 v; } hi, lo;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float x = j < 4 ? x0[j] : x1[j - 4];
-                    const bf16_t hb = to_bf16(x);
-                    hi.v[j] = hb;
-                    lo.v[j] = to_bf16(x - (float)hb);
-                }
-                const int off = (id / C::CPR) * C::VROW + 16 * (id % C::CPR);
-                *(u32x4 *)(smHi + off) = hi.u;
-                *(u32x4 *)(smLo + off) = lo.u;
-            }
+        if constexpr (!EARLY_STATE) {
+            __syncthreads();                              // every wave is done with the K/V ring
+            load_state();
+            store_state();
+            __syncthreads();
         }
-        __syncthreads();
-        f32x16 inter[C::DB];
+        f32x16 inter[C::DBW];
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db)
+        for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) inter[db][r] = 0.f;
         // k-slot j of half-wave hh must be d = 16t + 8hh + j to match q fragments loaded from memory, and
         // d = 16t + 8(j/4) + 4hh + j%4 to match fragments that were accumulator registers (fused feature map)
-        const int s_row = fused_map ? ((lane & 15) >> 2) + 4 * hh : 8 * hh + ((lane & 15) >> 2);
-        const int s_second = (fused_map ? 8 : 4) * C::VROW;
+        const int s_row = FUSED_MAP ? ((lane & 15) >> 2) + 4 * hh : 8 * hh + ((lane & 15) >> 2);
+        const int s_second = (FUSED_MAP ? 8 : 4) * C::VROW;
         const int s_frag_off = s_row * C::VROW + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
 #pragma unroll
         for (int t = 0; t < C::KS; ++t)
 #pragma unroll
-            for (int db = 0; db < C::DB; ++db) {
-                const unsigned char *p = smHi + s_frag_off + 16 * t * C::VROW + 64 * db;
-                const bf16x8 sh = __builtin_shufflevector(lds_read_tr(p), lds_read_tr(p + s_second), 0, 1, 2, 3, 4, 5, 6, 7);
-                const bf16x8 sl = __builtin_shufflevector(lds_read_tr(p + C::SS_BYTES), lds_read_tr(p + C::SS_BYTES + s_second),
-                                                          0, 1, 2, 3, 4, 5, 6, 7);
+            for (int db = 0; db < C::DBW; ++db) {
+                const unsigned char *p = smHi + s_frag_off + 16 * t * C::VROW + 64 * (db0 + db);
+                const bf16x8 sh = lds_read_tr_pair(p, s_second), sl = lds_read_tr_pair(p + C::SS_BYTES, s_second);
                 inter[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sh, qf[t], inter[db], 0, 0, 0);
                 inter[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sl, qf[t], inter[db], 0, 0, 0);
             }
-        // gate * L2 norm scale for this lane's query row
-        float gq = 1.0f / sqrtf(qss + a.l2_eps);
-        const size_t gtok = (size_t)b * Lq + (qrow < Lq ? qrow : 0);
-        const size_t gi = a.g_per_token ? gtok : gtok * H + h;
-        if (a.g != nullptr && !a.g_per_element && qrow < Lq)
-            gq *= a.g_is_bf16 ? (float)((const bf16_t *)a.g)[gi] : ((const float *)a.g)[gi];
+        const float gq = (1.0f / sqrtf(qss + a.l2_eps)) * g_row;       // gate * L2 norm scale for this lane's query row
         if (a.g != nullptr && a.g_per_element) {
             // one gate per output feature: registers 4 j .. 4 j + 3 of block db are features 32 db + 8 j + 4 hh + 0..3
 #pragma unroll
-            for (int db = 0; db < C::DB; ++db)
+            for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const size_t ge = gi * D + 32 * db + 8 * j + 4 * hh;
+                    const size_t ge = gi * D + 32 * (db0 + db) + 8 * j + 4 * hh;
                     float g4[4];
                     if (a.g_is_bf16) {
                         const bf16x4 x = *(const bf16x4 *)((const bf16_t *)a.g + ge);
@@ -642,58 +822,149 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, int n_qtiles
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        o_acc[db][4 * j + i] = fmaf(gq * g4[i], inter[db][4 * j + i], o_acc[db][4 * j + i]);
+                        out[db][4 * j + i] = fmaf(gq * g4[i], inter[db][4 * j + i], out[db][4 * j + i]);
                 }
         } else {
 #pragma unroll
-            for (int db = 0; db < C::DB; ++db)
+            for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o_acc[db][r] = fmaf(gq, inter[db][r], o_acc[db][r]);
+                for (int r = 0; r < 16; ++r) out[db][r] = fmaf(gq, inter[db][r], out[db][r]);
         }
     }
 
-    // transpose through LDS so that every output row is written as contiguous 16-byte pieces
-    __syncthreads();
-    unsigned char *region = smem + wave * 32 * C::KROW;
+    // Transpose through LDS so that rows are written as contiguous 16-byte pieces, each wavefront its own block of
+    // 32 rows x 32 DBW features.  With two key groups the block lies where the wavefront has just read its peer's
+    // partial result (nobody else touches that part); with one it may lie where others still read the state.
+    constexpr int OROW = 64 * C::DBW + 16, OCPR = 4 * C::DBW;          // LDS bytes and 16-byte chunks per row
+    static_assert(32 * OROW <= C::DBW * 16 * 64 * 4, "the block fits the peer's partial result");
+    unsigned char *region = smem + (KG == 1 ? wave * 32 * OROW : (wave ^ C::RG) * (C::DBW * 16 * 64 * 4));
+    if (KG == 1 || FUSED_MAP) __syncthreads();
 #pragma unroll
-    for (int db = 0; db < C::DB; ++db)
+    for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
         for (int j4 = 0; j4 < 4; ++j4) {
             bf16x4 w;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = to_bf16(o_acc[db][4 * j4 + i]);
-            const int e = 32 * db + 8 * j4 + 4 * hh;
-            *(bf16x4 *)(region + c * C::KROW + 2 * e) = w;
+            for (int i = 0; i < 4; ++i) w[i] = to_bf16(out[db][4 * j4 + i]);
+            *(bf16x4 *)(region + c * OROW + 2 * (32 * db + 8 * j4 + 4 * hh)) = w;
         }
-    __syncthreads();
     bf16_t *og = (bf16_t *)a.out;
 #pragma unroll
-    for (int i = 0; i < C::CPR / 2; ++i) {
+    for (int i = 0; i < 32 * OCPR / 64; ++i) {
         const int idx = lane + 64 * i;
-        const int row = idx / C::CPR, col = idx % C::CPR;
+        const int row = idx / OCPR, col = idx % OCPR;
         const int orow = q0 + row;
         if (orow < Lq) {
-            const u32x4 x = *(const u32x4 *)(region + row * C::KROW + 16 * col);
-            *(u32x4 *)(og + ((size_t)(b * (size_t)Lq + orow) * H + h) * D + 8 * col) = x;
+            const u32x4 x = *(const u32x4 *)(region + row * OROW + 16 * col);
+            *(u32x4 *)(og + ((size_t)(b * (size_t)Lq + orow) * H + h) * D + 32 * db0 + 8 * col) = x;
         }
     }
+}
+
+// How the workgroups of a launch divide the query tiles: whole 256-row tiles, half tiles of 128 rows with two key
+// groups, or whole tiles first and half ones at the end.
+enum FwdSplit { kWhole, kHalves, kHalvesLast };
+
+struct FwdGrid {
+    int n_qtiles;        // 256-row tiles per head (kHalves: 128-row tiles)
+    int n_tiles;         // all tiles
+    int n_whole;         // kHalvesLast: tiles that are served whole
+    int ragged_last;
+};
+
+template <int D, FwdSplit SPLIT, bool FUSED_MAP>
+__global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, FwdGrid g, float scale_log2)
+{
+    constexpr int SMEM1 = FwdCfg<D, 1>::SMEM, SMEM2 = FwdCfg<D, 2>::SMEM;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SPLIT == kWhole ? SMEM1 : SPLIT == kHalves ? SMEM2 : SMEM1 > SMEM2 ? SMEM1 : SMEM2];
+    int id = blockIdx.x, half = -1;
+    if (SPLIT == kHalvesLast && id >= g.n_whole) {
+        const int n_rest = g.n_tiles - g.n_whole;
+        half = (id - g.n_whole) / n_rest;
+        id = g.n_whole + (id - g.n_whole) % n_rest;
+    }
+    int qt, bh;
+    if (g.ragged_last) {
+        // Several rounds of workgroups, and the last query tile of every head is ragged (its workgroup has
+        // idle wavefronts and finishes early): every XCD takes B H / 8 heads, their full tiles first, head
+        // by head, and their ragged tiles at the end of its dispatch order, where a short job shortens the
+        // last, partly filled round (workgroup ids go round the 8 XCDs in dispatch order).
+        const int x = id % kNumXcd, loc = id / kNumXcd;
+        const int heads_x = a.B * a.H / kNumXcd, n_full = g.n_qtiles - 1;
+        if (loc < heads_x * n_full) {
+            bh = x * heads_x + loc / n_full;
+            qt = loc % n_full;
+        } else {
+            bh = x * heads_x + (loc - heads_x * n_full);
+            qt = n_full;
+        }
+    } else {
+        const int work = xcd_contiguous_id(id, g.n_tiles);
+        qt = work % g.n_qtiles;
+        bh = work / g.n_qtiles;
+    }
+    if constexpr (SPLIT == kWhole) {
+        fwd_tile<D, 1, FUSED_MAP>(a, scale_log2, bh, qt, smem);
+    } else if constexpr (SPLIT == kHalves) {
+        fwd_tile<D, 2, FUSED_MAP>(a, scale_log2, bh, qt, smem);
+    } else if (half < 0) {
+        fwd_tile<D, 1, FUSED_MAP>(a, scale_log2, bh, qt, smem);
+    } else if ((2 * qt + half) * 128 < a.Lq) {
+        fwd_tile<D, 2, FUSED_MAP>(a, scale_log2, bh, 2 * qt + half, smem);
+    }
+}
+
+template <int D, FwdSplit SPLIT>
+hipError_t launch_fwd(const FwdArgs &a, FwdGrid g, float scale_log2, hipStream_t stream)
+{
+    const int n_wg = SPLIT == kHalvesLast ? 2 * g.n_tiles - g.n_whole : g.n_tiles;
+    const dim3 grid((unsigned)n_wg), block(NT);
+    if (a.xq != nullptr) return launch_kernel(fwd_bf16_kernel<D, SPLIT, true>, grid, block, stream, a, g, scale_log2);
+    return launch_kernel(fwd_bf16_kernel<D, SPLIT, false>, grid, block, stream, a, g, scale_log2);
+}
+
+template <int D>
+hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
+{
+    const float scale_log2 = a.sm_scale * 1.4426950408889634f;
+    const long long heads = (long long)a.B * a.H;
+    const long long q256 = (a.Lq + 255) / 256, q128 = (a.Lq + 127) / 128;
+    if (heads * q128 > 0x3fffffffLL) return hipErrorInvalidValue;
+    FwdGrid g;
+    g.n_qtiles = (int)q256;
+    g.n_tiles = g.n_whole = (int)(heads * q256);
+    // more workgroups than CUs, a ragged last query tile per head, and whole heads per XCD
+    g.ragged_last = g.n_tiles > kNumCu && a.Lq % 256 != 0 && q256 > 1 && heads % kNumXcd == 0;
+    if (a.Lkv > 32) {                            // two key groups need a key each in the first tile
+        // Half tiles while they run as one round: 1024 tokens x 16 heads x 128 21.5 us against 28.6 us for whole tiles, x 32
+        // heads (256 half tiles) 26.6 against 29.9 us; just beyond, x 48 heads, 43.9 against 34.9 us.
+        if (heads * q128 <= kNumCu) {
+            g.n_qtiles = (int)q128;
+            g.n_tiles = (int)(heads * q128);
+            g.ragged_last = 0;
+            return launch_fwd<D, kHalves>(a, g, scale_log2, stream);
+        }
+        // The tail of a launch of several rounds: when at most half of the CUs would have a tile in it, these tiles are
+        // halved.  A half tile takes 0.57 of the time of a whole one, so that 2 x 1000 tokens x 136 heads (2.08
+        // rounds) take 94 us instead of 102 us, 2048 tokens x 66 heads x 64 wide (2.06 rounds) 97 instead of 110 us;
+        // nothing changes where more than half of the CUs have work in the last round.
+        const int rest = g.n_tiles % kNumCu;
+        if (g.n_tiles > kNumCu && rest > 0 && 2 * rest <= kNumCu) {
+            g.n_whole = g.n_tiles - rest;
+            return launch_fwd<D, kHalvesLast>(a, g, scale_log2, stream);
+        }
+    }
+    return launch_fwd<D, kWhole>(a, g, scale_log2, stream);
 }
 
 }  // namespace
 
 hipError_t launch_fwd_bf16(const FwdArgs &a, hipStream_t stream)
 {
-    const int n_qtiles = (a.Lq + BM - 1) / BM;
-    const long long nwg = (long long)n_qtiles * a.B * a.H;
-    if (nwg <= 0 || nwg > 0x7fffffffLL) return hipErrorInvalidValue;
     // the kernel addresses one stream's K (or V) with 32-bit byte offsets
     if ((long long)(a.Lkv + 4 * BN) * a.H * a.D * 2 > 0x7fffffffLL) return hipErrorInvalidValue;
-    const float scale_log2 = a.sm_scale * 1.4426950408889634f;
-    const dim3 grid((unsigned)nwg), block(NT);
-    // more workgroups than CUs, a ragged last query tile per head, and whole heads per XCD
-    const int ragged_last = nwg > kNumCu && a.Lq % BM != 0 && n_qtiles > 1 && ((long long)a.B * a.H) % kNumXcd == 0;
-    if (a.D == 128) return launch_kernel(fwd_bf16_kernel<128>, grid, block, stream, a, n_qtiles, scale_log2, ragged_last);
-    if (a.D == 64) return launch_kernel(fwd_bf16_kernel<64>, grid, block, stream, a, n_qtiles, scale_log2, ragged_last);
+    if (a.D == 128) return launch_fwd<128>(a, stream);
+    if (a.D == 64) return launch_fwd<64>(a, stream);
     return hipErrorInvalidValue;
 }
 

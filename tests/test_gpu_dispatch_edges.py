@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import workloads as W
-from helpers import TOL_F32, rel_err, rel_err_per_head, to_np
+from helpers import TOL_BF16_OUT, TOL_F32, rel_err, rel_err_per_head, to_np
 from test_gpu_parity import dev, gpu_commit, gpu_fwd, lib  # noqa: F401  (lib is the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -35,3 +35,39 @@ def test_fp32_tiles_and_key_groups(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
     gpu_commit(lib, k, v, gate, S_dev)
     e = rel_err_per_head(to_np(S_dev), oracle.commit(to_np(k), to_np(v), to_np(gate), S64))
     assert e <= TOL_F32, f"commit: {e:.3e}"
+
+
+# Readout: half tiles of 128 rows with two key groups while they fit one round (from 33 keys on: one, two, many key
+# tiles, a last tile with keys for one or both groups), whole tiles of 256 rows beyond, and whole tiles followed by half
+# tiles when the last round would be at most half full (272 and 544 tiles; a last half tile with and without rows).
+@pytest.mark.parametrize("B,H,Lq,Lkv,D", [
+    (1, 2, 40, 32, 128), (1, 2, 40, 33, 128), (2, 1, 128, 64, 64), (1, 3, 129, 65, 128), (1, 2, 256, 97, 64), (1, 2, 300, 128, 128),
+    (1, 2, 130, 161, 128), (2, 2, 385, 385, 64), (1, 2, 200, 200, 128), (8, 17, 150, 150, 64), (17, 16, 40, 40, 64), (17, 16, 200, 200, 64),
+    (17, 16, 300, 70, 64), (17, 16, 130, 40, 128), (3, 43, 290, 290, 128)])
+def test_readout_tile_splits(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"split_{B}_{H}_{Lq}_{Lkv}_{D}", B=B, H=H, L=Lq, D=D)
+    q, _, _, g = W.pass_inputs(w, 0, 0)
+    k, v = (W.normal(5, w, (B, Lkv, H, D), tag) for tag in (1, 2))
+    e = rel_err(to_np(gpu_fwd(lib, q, k, v, None, None)), oracle.fwd(to_np(q), to_np(k), to_np(v)))
+    assert e <= TOL_BF16_OUT, f"softmax: {e:.3e}"
+    # logits far above the first block's maximum: the running maximum has to be raised later on
+    k2 = k.clone()
+    k2[:, Lkv // 2:] *= 16
+    e = rel_err(to_np(gpu_fwd(lib, q, k2, v, None, None)), oracle.fwd(to_np(q), to_np(k2), to_np(v)))
+    assert e <= TOL_BF16_OUT, f"late maximum: {e:.3e}"
+    if Lq != Lkv:
+        return
+    S = W.normal(6, w, (B, H, D, D), 3, io_dtype="f32") * 0.2
+    S64 = to_np(S).astype(np.float64)
+    e = rel_err(to_np(gpu_fwd(lib, q, k, v, S, g)), oracle.fwd(to_np(q), to_np(k), to_np(v), S64, to_np(g)))
+    assert e <= TOL_BF16_OUT, f"readout: {e:.3e}"
+    # the fused query map against the two calls it stands for
+    Wq, _, _ = W.feature_weights(w)
+    cs, sn = W.rope_tables(w)
+    ql, out, ref = (torch.empty_like(q, device="cuda") for _ in range(3))
+    lib.arl2_feature_map(dev(q), dev(Wq), dev(cs), dev(sn), ql)
+    lib.arl2_hybrid_attn_fwd_ex(dev(q), dev(k), dev(v), ql, dev(S), dev(g), ref)
+    lib.arl2_hybrid_attn_fwd_fm(dev(q), dev(k), dev(v), dev(q), dev(Wq), dev(cs), dev(sn), dev(S), dev(g), out)
+    torch.cuda.synchronize()
+    # both round the mapped query to bf16 on fp32 sums in different orders: one ulp of an entry, then of the output
+    assert rel_err(to_np(out), to_np(ref)) <= 2.0 ** -7
