@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import workloads as W
-from helpers import TOL_BF16_OUT, TOL_F32, rel_err, rel_err_per_head, to_np
+from helpers import TOL_BF16_OUT, TOL_F32, TOL_STATE, rel_err, rel_err_per_head, to_np
 from test_gpu_parity import dev, gpu_commit, gpu_fwd, lib  # noqa: F401  (lib is the fixture)
 
 pytestmark = pytest.mark.gpu
@@ -71,3 +71,23 @@ def test_readout_tile_splits(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
     torch.cuda.synchronize()
     # both round the mapped query to bf16 on fp32 sums in different orders: one ulp of an entry, then of the output
     assert rel_err(to_np(out), to_np(ref)) <= 2.0 ** -7
+
+
+# Delta rule: tiles of 64 (D = 128) or 128 (D = 64) tokens shared by two or four token groups, one split per CU as far as
+# heads, tiles and the workspace allow (one tile, a ragged tile of one group, several rounds of the load ring, more heads
+# than CUs).
+@pytest.mark.parametrize("B,H,L,D", [
+    (1, 2, 1, 128), (1, 2, 33, 64), (2, 3, 64, 128), (1, 3, 65, 128), (1, 2, 128, 64), (1, 2, 129, 64), (2, 24, 321, 128),
+    (3, 86, 300, 64), (13, 20, 260, 128)])
+def test_delta_tiles_and_splits(lib, oracle, B, H, L, D):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"delta_{B}_{H}_{L}_{D}", B=B, H=H, L=L, D=D)
+    k, v, gate = W.clean_inputs(w, 0)
+    beta = W.uniform(2, w, (B, H), 0.2, 1.0, 0, 0, 97) / (1.0 + (L / D) ** 0.5) ** 2
+    S = W.normal(6, w, (B, H, D, D), 3, io_dtype="f32")
+    S_dev = dev(S).clone()
+    ws = lib.alloc_workspace(B, H, L, D, torch.bfloat16)
+    lib.arl2_state_commit_delta(dev(k), dev(v), dev(gate), dev(beta), S_dev, ws)
+    torch.cuda.synchronize()
+    ref = oracle.commit_delta(to_np(k), to_np(v), to_np(gate), to_np(beta), to_np(S).astype(np.float64))
+    e = rel_err_per_head(to_np(S_dev), ref)
+    assert e <= TOL_STATE, f"{e:.3e}"
