@@ -14,9 +14,9 @@
 //
 // Kernel 1 (one workgroup per block of tokens, all blocks in parallel) builds Z and leaves it, with K, V^T
 // and the per-token scalars, in the workspace in the operand-fragment order of kernel 2.  The Gram matrix
-// uses the raw bf16 keys (exact products) and is scaled in fp32; the triangular solve runs in fp32 in
-// blocks of 16 tokens, the diagonal systems on the vector ALU (one thread per feature), the off-diagonal
-// updates on MFMA with hi + lo splits.  K and V^T leave for the workspace as soon as the tiles are in LDS, Z
+// uses the raw bf16 keys (exact products) and is scaled in fp32; the triangular solve runs on the fp32 matrix
+// instructions in blocks of 16 tokens, whose diagonal systems are inverted beforehand on the vector ALU, the four
+// blocks at the same time.  K and V^T leave for the workspace as soon as the tiles are in LDS, Z
 // straight from the solver's registers.
 // Kernel 2 walks the blocks in order, one workgroup per 64 state columns (eight wavefronts at D = 128, four at
 // D = 64), with two dependent contractions per block (K S, then Z^T R).  With few heads the blocks of a head are cut into runs that are walked at
@@ -43,16 +43,16 @@ struct GdnCfg {
     static constexpr int CPR = D / 8;                   // 16-byte chunks per row
     static constexpr int ROW = 2 * D + 32;              // LDS bytes per row of a token-major tile (K, V)
     static constexpr int TILE = CT * ROW;               // one 64-token bf16 tile
-    static constexpr int ZROW = 2 * CT + 16;            // LDS bytes per row of a feature-major tile (Z^T)
     static constexpr int KCH = CT * CPR / NTA;          // chunks per thread per tile
     static constexpr int ROWS_PER_PASS = NTA / CPR;
     static constexpr int AST = 68;                      // floats per row of the 64 x 64 fp32 matrix
     static constexpr int NB = D / 32;                   // 32-wide blocks per side of a D x D matrix
     static constexpr int KS = D / 16;                   // k-steps of a D-long contraction
     static constexpr int REG = TILE > CT * AST * 4 ? TILE : CT * AST * 4;   // a region holds a tile or the fp32 matrix
-    static constexpr int SC_OFF = 4 * REG;              // per-token scalars behind the four regions
-    static constexpr int SMEM = SC_OFF + 8 * CT * 4 + 16;
-    static_assert(D * ZROW <= REG, "a feature-major tile must fit into one region");
+    static constexpr int SC_OFF = 2 * REG;              // per-token scalars behind the two regions
+    static constexpr int SMEM = SC_OFF + 6 * CT * 4;
+    static constexpr int WF = D / 4;                    // features per wavefront of the solve
+    static constexpr int NFB = WF / 16;                 // 16-feature blocks of them
     static_assert(KCH >= 1, "unsupported head dimension");
 };
 
@@ -90,12 +90,20 @@ __host__ __device__ constexpr size_t gdn_ops_bytes(int D) { return (size_t)CT * 
 
 // Kernel 1: the operands of one block's solve,
 //   S_out = gam S + Z^T (diag(beta) V + diag(-beta gamma- r) (K S)),    Z = (I + A)^-T diag(tail r) K.
+// Bound by latency (loads, the gate products, the inverses, the solve: a chain inside each workgroup), so what counts is
+// how many workgroups a CU holds: 39 KB of LDS (the fp32 matrix takes the place of V once V^T has left) and at most 128
+// registers, four per CU.  The solve itself needs no exchange: fp32 matrix instructions, whose 16 x 16 results are in the
+// register order of the next product's operand, so that a wavefront takes its own features through all four
+// token blocks.
+// Measured, 12 heads x 128, 4680 tokens (888 workgroups, 86 registers): 21.2 us; 31.1 us with the diagonal systems solved
+// by one thread per feature, hi + lo bf16 updates exchanged through LDS and two workgroups per CU (75 KB of LDS).  8 x 4
+// heads, 2000 tokens: 21.8 against 31.6 us.
 template <int D>
-__global__ __launch_bounds__(NTA, 2) void gdn_block_kernel(GdnArgs a, int nblk)
+__global__ __launch_bounds__(NTA, 4) void gdn_block_kernel(GdnArgs a, int nblk)
 {
     using C = GdnCfg<D>;
     __shared__ __attribute__((aligned(16))) unsigned char smem[C::SMEM];
-    unsigned char *R0 = smem, *R1 = smem + C::REG, *R2 = smem + 2 * C::REG, *R3 = smem + 3 * C::REG;
+    unsigned char *R0 = smem, *R1 = smem + C::REG;      // K tile; V tile, then the 64 x 64 fp32 matrix
     float *sc_r = (float *)(smem + C::SC_OFF);          // 1 / sqrt(|k_i|^2 + eps)
     float *sc_al = sc_r + CT, *sc_be = sc_al + CT;      // alpha_i, beta_i
     float *sc_tr = sc_be + CT;                          // (alpha_{i+1} .. alpha_64) r_i
@@ -103,7 +111,7 @@ __global__ __launch_bounds__(NTA, 2) void gdn_block_kernel(GdnArgs a, int nblk)
     float *sc_gam = sc_se + CT;
 
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, hh = lane >> 5, c32 = lane & 31;
+    const int wave = tid >> 6, lane = tid & 63, hh = lane >> 5, c32 = lane & 31, g = lane >> 4, c16 = lane & 15;
     const int blk = blockIdx.x % nblk;
     const int bh = blockIdx.x / nblk;
     const int h = bh % a.H, b = bh / a.H;
@@ -150,7 +158,7 @@ __global__ __launch_bounds__(NTA, 2) void gdn_block_kernel(GdnArgs a, int nblk)
             sc_be[tid] = be;
         }
     }
-    __syncthreads();
+    lds_barrier();
 
     // The record of this block in the workspace.  K and V^T depend on the tiles alone: they leave now, in
     // fragment order, and their stores drain while the solve runs.
@@ -183,161 +191,131 @@ __global__ __launch_bounds__(NTA, 2) void gdn_block_kernel(GdnArgs a, int nblk)
         sc_se[tid] = -(be * gp * r);
         if (tid == CT - 1) sc_gam[0] = gp * al;
     }
-    {
-        const int ib = wave >> 1, jb = wave & 1;         // rows i, columns j of the 64 x 64 Gram matrix
-        if (jb <= ib) {                                  // the strictly upper block is never used
-            f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    f32x16 gram = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    const int ib = wave >> 1, jb = wave & 1;             // rows i, columns j of the 64 x 64 Gram matrix
+    if (jb <= ib) {                                      // the strictly upper block is never used
 #pragma unroll
-            for (int t = 0; t < C::KS; ++t) {
-                const bf16x8 ka = *(const bf16x8 *)(R0 + (32 * ib + c32) * C::ROW + 32 * t + 16 * hh);
-                const bf16x8 kb = *(const bf16x8 *)(R0 + (32 * jb + c32) * C::ROW + 32 * t + 16 * hh);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, kb, acc, 0, 0, 0);
-            }
-            float *Gs = (float *)R2;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = 32 * ib + 8 * (r >> 2) + 4 * hh + (r & 3);
-                Gs[i * C::AST + 32 * jb + c32] = acc[r];
-            }
+        for (int t = 0; t < C::KS; ++t) {
+            const bf16x8 ka = *(const bf16x8 *)(R0 + (32 * ib + c32) * C::ROW + 32 * t + 16 * hh);
+            const bf16x8 kb = *(const bf16x8 *)(R0 + (32 * jb + c32) * C::ROW + 32 * t + 16 * hh);
+            gram = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, kb, gram, 0, 0, 0);
         }
     }
-    __syncthreads();
+    lds_barrier();                                       // V has been read; stores to the workspace stay in flight
+    float *At = (float *)R1;                             // indexed [column j][row i]
+    if (jb <= ib) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)                      // registers 4 q .. 4 q + 3: four consecutive rows
+            *(f32x4 *)(At + (32 * jb + c32) * C::AST + 32 * ib + 8 * q + 4 * hh) =
+                f32x4{gram[4 * q], gram[4 * q + 1], gram[4 * q + 2], gram[4 * q + 3]};
+    }
+    lds_barrier();
 
-    // ---- 3. A_ij = beta_i (alpha_{j+1} .. alpha_{i-1}) r_i r_j G_ij for i > j, in place;
+    // ---- 3. -A_ij = -beta_i (alpha_{j+1} .. alpha_{i-1}) r_i r_j G_ij for i > j, else 0, in place;
     //         thread = (column j, rows 16 wave .. 16 wave + 15)
     {
-        float *As = (float *)R2;
         const int j = lane, i0 = 16 * wave;
-        float g[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) g[e] = As[(i0 + e) * C::AST + j];
         // alpha_{j+1} .. alpha_{i0-1}: exclusive suffix product over the lanes of the gates before row i0
         float rho = lane_suffix_product(j < i0 ? sc_al[j] : 1.f, lane);
         const float rj = sc_r[j];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
+            f32x4 *p = (f32x4 *)(At + j * C::AST + i0 + 4 * q);
+            f32x4 x = *p;
             const f32x4 al4 = *(const f32x4 *)(sc_al + i0 + 4 * q);
             const f32x4 be4 = *(const f32x4 *)(sc_be + i0 + 4 * q);
             const f32x4 r4 = *(const f32x4 *)(sc_r + i0 + 4 * q);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int i = i0 + 4 * q + e;
-                if (i > j) {
-                    As[i * C::AST + j] = be4[e] * rho * r4[e] * rj * g[4 * q + e];
-                    rho *= al4[e];
-                }
+                const bool below = i0 + 4 * q + e > j;
+                x[e] = below ? -(be4[e] * rho * r4[e] * rj * x[e]) : 0.f;
+                rho *= below ? al4[e] : 1.f;
             }
+            *p = x;
         }
     }
-    __syncthreads();
+    lds_barrier();
 
-    // ---- 4. back substitution (I + A)^T Z = diag(tail r) K in blocks of 16 tokens, last block first.
-    // The 16 x 16 diagonal systems are solved on the vector ALU, thread = feature (row i of A updates
-    // rows j < i, all independent).  What a solved block contributes to the rows before it,
-    // U[j][f] = sum_{i in block} A_ij Z_i[f], is one MFMA k-step: A from the fp32 matrix in LDS and the
-    // block of Z passed through LDS, both split into bf16 hi + lo (three terms); U stays in accumulators
-    // (wavefront = 32 features, rows 0..63 as two 32-row blocks) and only the 16 rows the next block
-    // needs travel back through LDS.
-    float z[CT];
+    // ---- 4. the inverses of the four unit triangular 16 x 16 diagonal blocks, in place; wavefront = block,
+    // lane = column c16 of the inverse (the four lane groups alike, each stores a quarter), by forward substitution
     {
-        const float *As = (const float *)R2;
-        unsigned char *Zb = R3;                                   // [feature][16 tokens] bf16, hi then lo
-        float *Ux = (float *)(R3 + 2 * D * 32);                   // [16 rows][D + 4] fp32
-        constexpr int UST = D + 4;
-        if (tid < D) {
+        float *Ad = At + 16 * wave * (C::AST + 1);
+        float x[16];
 #pragma unroll
-            for (int i = 0; i < CT; ++i) z[i] = sc_tr[i] * (float)*(const bf16_t *)(R0 + i * C::ROW + 2 * tid);
-        }
-        f32x16 U[2];
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) U[rb][r] = 0.f;
-        static_for<0, 4>([&](auto bb_) {
-            constexpr int b4 = 3 - decltype(bb_)::value, i0 = 16 * b4;          // token block 3, 2, 1, 0
-            if (tid < D) {
-                // the block's 120 entries of A first, so that their LDS latency is paid once
-                f32x4 a4[15][4];
-                static_for<1, 16>([&](auto il_) {
-                    constexpr int il = decltype(il_)::value;
-                    static_for<0, (il + 3) / 4>([&](auto q_) {
-                        constexpr int q = decltype(q_)::value;
-                        a4[il - 1][q] = *(const f32x4 *)(As + (i0 + il) * C::AST + i0 + 4 * q);
-                    });
+        for (int i = 0; i < 16; ++i) x[i] = i == c16 ? 1.f : 0.f;
+        static_for<0, 15>([&](auto j_) {
+            constexpr int j = decltype(j_)::value;       // x[j] is final
+            static_for<(j + 1) / 4, 4>([&](auto q_) {
+                constexpr int q = decltype(q_)::value;
+                const f32x4 a4 = *(const f32x4 *)(Ad + j * C::AST + 4 * q);
+                static_for<0, 4>([&](auto e_) {
+                    constexpr int i = 4 * q + decltype(e_)::value;
+                    if constexpr (i > j) x[i] = fmaf(a4[i % 4], x[j], x[i]);
                 });
-                if constexpr (b4 < 3) {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) z[i0 + e] -= Ux[e * UST + tid];
-                }
-                static_for<0, 15>([&](auto ii_) {
-                    constexpr int il = 15 - decltype(ii_)::value;                  // z[i0 + il] is final
-                    static_for<0, il>([&](auto jl_) {
-                        constexpr int jl = decltype(jl_)::value;
-                        z[i0 + jl] = fmaf(-a4[il - 1][jl / 4][jl % 4], z[i0 + il], z[i0 + jl]);
-                    });
-                });
-                if constexpr (b4 > 0) {
-#pragma unroll
-                    for (int half = 0; half < 2; ++half) {
-                        bf16x8 h8, l8;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float x = z[i0 + 8 * half + e];
-                            h8[e] = to_bf16(x);
-                            l8[e] = to_bf16(x - (float)h8[e]);
-                        }
-                        *(bf16x8 *)(Zb + tid * 32 + 16 * half) = h8;
-                        *(bf16x8 *)(Zb + D * 32 + tid * 32 + 16 * half) = l8;
-                    }
-                }
-            }
-            if constexpr (b4 > 0) {
-                __syncthreads();
-                if (wave < C::NB) {
-                    const bf16x8 zh = *(const bf16x8 *)(Zb + (32 * wave + c32) * 32 + 16 * hh);
-                    const bf16x8 zl = *(const bf16x8 *)(Zb + D * 32 + (32 * wave + c32) * 32 + 16 * hh);
-                    constexpr int NRB = (i0 + 31) / 32;                                 // 32-row blocks that hold rows < i0
-                    static_for<0, NRB>([&](auto rb_) {
-                        constexpr int rb = decltype(rb_)::value;
-                        const int j = 32 * rb + c32;
-                        bf16x8 ah, al;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float x = j < i0 ? As[(i0 + 8 * hh + e) * C::AST + j] : 0.f;
-                            ah[e] = to_bf16(x);
-                            al[e] = to_bf16(x - (float)ah[e]);
-                        }
-                        U[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, zh, U[rb], 0, 0, 0);
-                        U[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, zl, U[rb], 0, 0, 0);
-                        U[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, zh, U[rb], 0, 0, 0);
-                    });
-                    // rows i0 - 16 .. i0 - 1 of U go to the feature threads
-                    constexpr int rb = (i0 - 16) / 32, r0 = ((i0 - 16) % 32) / 8 * 4;  // 32-row block, first register
-#pragma unroll
-                    for (int r = 0; r < 8; ++r)
-                        Ux[(8 * (r >> 2) + 4 * hh + (r & 3)) * UST + 32 * wave + c32] = U[rb][r0 + r];
-                }
-                __syncthreads();
-            }
+            });
+        });
+        // (a wavefront's LDS operations complete in order: its reads above are ahead of these writes)
+        static_for<0, 4>([&](auto q_) {
+            constexpr int q = decltype(q_)::value;
+            if (g == q) *(f32x4 *)(Ad + c16 * C::AST + 4 * q) = f32x4{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
         });
     }
-    // Z^T leaves straight from the registers of the feature threads, split into bf16 hi + lo:
-    // fragment (rb, t), lane (feature c32, hh) = Z^T[32 rb + c32][16 t + 8 hh + 0..7]; consecutive threads
-    // (features) write consecutive 16-byte pieces
-    if (tid < D) {
-        const int rb = tid >> 5, f32 = tid & 31;
+    lds_barrier();
+
+    // ---- 5. back substitution (I + A)^T Z = diag(tail r) K in blocks of 16 tokens, last block first:
+    //   Z_b = (I + A_bb)^-T Y_b,   Y_b' -= A_bb'^T Z_b for the blocks b' before b
+    // as 16 x 16 x 4 fp32 MFMAs, [token][feature].  A lane (feature c16, g) holds tokens 4 g + 0..3 of a block, which is
+    // the B operand of four k-steps (step s: token 4 g + s) with the A operand A[4 g + s][column c16], one 16-byte read.
+    f32x4 z[C::NFB][4];
 #pragma unroll
-        for (int q = 0; q < CT / 8; ++q) {               // q = 2 t + hh
-            bf16x8 h8, l8;
+    for (int b4 = 0; b4 < 4; ++b4) {
+        const f32x4 tr4 = *(const f32x4 *)(sc_tr + 16 * b4 + 4 * g);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float x = z[8 * q + e];
-                h8[e] = to_bf16(x);
-                l8[e] = to_bf16(x - (float)h8[e]);
+        for (int fb = 0; fb < C::NFB; ++fb) {
+            const bf16x4 k4 = lds_read_tr(R0 + (16 * b4 + 4 * g + (c16 >> 2)) * C::ROW + 2 * (C::WF * wave + 16 * fb) + 8 * (c16 & 3));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z[fb][b4][e] = tr4[e] * (float)k4[e];
+        }
+    }
+    static_for<0, 4>([&](auto bb_) {
+        constexpr int b4 = 3 - decltype(bb_)::value;
+        const f32x4 m4 = *(const f32x4 *)(At + (16 * b4 + c16) * C::AST + 16 * b4 + 4 * g);
+        f32x4 x[C::NFB];
+#pragma unroll
+        for (int fb = 0; fb < C::NFB; ++fb) x[fb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int fb = 0; fb < C::NFB; ++fb) x[fb] = __builtin_amdgcn_mfma_f32_16x16x4f32(m4[s], z[fb][b4][s], x[fb], 0, 0, 0);
+#pragma unroll
+        for (int fb = 0; fb < C::NFB; ++fb) z[fb][b4] = x[fb];
+        static_for<0, b4>([&](auto p_) {
+            constexpr int to = b4 - 1 - decltype(p_)::value;             // the block solved next first
+            const f32x4 a4 = *(const f32x4 *)(At + (16 * to + c16) * C::AST + 16 * b4 + 4 * g);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int fb = 0; fb < C::NFB; ++fb)
+                    z[fb][to] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[s], z[fb][b4][s], z[fb][to], 0, 0, 0);
+        });
+    });
+    // Z^T leaves straight from the accumulators, split into bf16 hi + lo: fragment (rb, t), lane (feature c32, hh) =
+    // Z^T[32 rb + c32][16 t + 8 hh + 0..7]; a lane holds the tokens of one half of such a piece
+#pragma unroll
+    for (int fb = 0; fb < C::NFB; ++fb) {
+        const int f = C::WF * wave + 16 * fb + c16;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            bf16x4 h4, l4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = z[fb][t][e];
+                h4[e] = to_bf16(x);
+                l4[e] = to_bf16(x - (float)h4[e]);
             }
-            const int p = (rb * 4 + (q >> 1)) * 64 + f32 + 32 * (q & 1);
-            Zhi[p] = h8;
-            Zlo[p] = l8;
+            const int p = ((f >> 5) * 4 + t) * 64 + (f & 31) + 32 * (g >> 1);
+            ((bf16x4 *)Zhi)[2 * p + (g & 1)] = h4;
+            ((bf16x4 *)Zlo)[2 * p + (g & 1)] = l4;
         }
     }
     if (tid < CT) {

@@ -91,3 +91,23 @@ def test_delta_tiles_and_splits(lib, oracle, B, H, L, D):  # noqa: F811
     ref = oracle.commit_delta(to_np(k), to_np(v), to_np(gate), to_np(beta), to_np(S).astype(np.float64))
     e = rel_err_per_head(to_np(S_dev), ref)
     assert e <= TOL_STATE, f"{e:.3e}"
+
+
+# Token-sequential delta rule where the triangular solve of a 64-token block matters most: keys of a block nearly alike,
+# learning rates up to one, gates of zero and one inside 16-token blocks, one token to several blocks and runs.
+@pytest.mark.parametrize("B,H,L,D", [(1, 2, 1, 128), (1, 3, 17, 64), (2, 2, 64, 128), (1, 2, 81, 64), (1, 5, 300, 128), (2, 3, 600, 64)])
+def test_gdn_blocks_of_similar_keys(lib, oracle, B, H, L, D):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"gdn_alike_{B}_{H}_{L}_{D}", B=B, H=H, L=L, D=D)
+    k, v, _ = W.clean_inputs(w, 0)
+    k = (0.1 * k.float() + k[:, :1].float()).to(torch.bfloat16)
+    alpha, beta = W.uniform(2, w, (B, L, H), 0.9, 1.0, 0, 0, 98), W.uniform(2, w, (B, L, H), 0.5, 1.0, 0, 0, 99)
+    alpha[:, 3::37], alpha[:, 5::41], beta[:, 7::29], beta[:, 9::31] = 0.0, 1.0, 0.0, 1.0
+    S = W.normal(6, w, (B, H, D, D), 3, io_dtype="f32")
+    S_dev = dev(S).clone()
+    ws = torch.empty(lib.arl2_gdn_workspace_bytes(B, H, L, D), dtype=torch.uint8, device="cuda")
+    lib.arl2_state_commit_gdn(dev(k), dev(v), dev(alpha), dev(beta), S_dev, ws)
+    torch.cuda.synchronize()
+    ref = oracle.commit_gdn(to_np(k), to_np(v), to_np(alpha), to_np(beta), to_np(S).astype(np.float64))
+    e = rel_err_per_head(to_np(S_dev), ref)
+    print(f"gdn similar keys {B}x{H}x{L}x{D}: {e:.2e}")
+    assert e <= TOL_STATE, f"{e:.3e}"
