@@ -163,6 +163,22 @@ __device__ __forceinline__ bf16x8 lds_read_tr_pair(const unsigned char *p, int s
     return __builtin_shufflevector(lds_read_tr(p), lds_read_tr(p + second_row_bytes), 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// 16 bytes per lane from `off` bytes into a buffer straight into LDS: lane l to byte address lds + 16 l (lds uniform).
+// Written out because the compiler, which of the built-in knows only that it writes LDS, waits for every such load in
+// flight before the next LDS read.  There is no output register; the caller waits on vmcnt before the bytes are read.
+// M0 carries the address and is handed back as it was.
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t lds)
+{
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "s"(lds), "v"(off), "s"(rsrc) : "memory");
+}
+// Byte address of an object in LDS.
+__device__ __forceinline__ uint32_t lds_address(const unsigned char *p)
+{
+    return (uint32_t)reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) unsigned char *)p);
+}
+
 // Sum / max of a value held by lane l and lane l^32 (the two half-waves).
 __device__ __forceinline__ float xhalf_sum(float x)
 {

@@ -113,29 +113,35 @@ __global__ __launch_bounds__(NT) void gate_proj_kernel(GateArgs a)
 // ---- dense projection: G[tok][n] = sigmoid( sum_j x[tok][j] Wg[n][j] ) for any number of outputs n ----
 // One workgroup owns TM tokens x TN outputs, each wavefront 64 tokens x TN / WN outputs (2 x NB MFMA
 // blocks).  The hidden dimension is walked in steps of 64 columns: the 128-byte row pieces of x and Wg
-// travel HBM/L2 -> registers -> LDS (padded rows: conflict-free 16-byte fragment reads), two LDS stages,
-// two steps of loads in flight in two register sets, one LDS-only barrier per step so that the loads
-// stay in flight across it.  With 2 x 2 blocks per wavefront every MFMA needs one 1 KB fragment from LDS
-// and the LDS pipe is as busy as the matrix pipe; 2 x 4 blocks need 0.75.  Two shapes:
-//   128 x 128, four wavefronts, two workgroups per CU    small problems: twice as many workgroups
-//   256 x 256, eight wavefronts of 64 x 128              large problems: half the LDS and L2 traffic per flop
+// travel straight from memory into one of ST LDS stages, up to ST - 1 steps ahead, one barrier per step.  (The
+// 16-byte chunks of a row are stored at chunk ^ (row / 2 % 8): a fragment read touches one chunk of 32 rows, which would
+// share banks otherwise, and a direct load leaves no room for padding.)  Three shapes:
+//   128 x 128, four wavefronts, four stages    while every workgroup has a CU to itself: nothing else hides its loads
+//   128 x 128, four wavefronts, two stages     two workgroups per CU, one multiplies while the other waits
+//   256 x 256, eight wavefronts of 64 x 128    large problems: half the LDS and L2 traffic per flop
+// Bound by the matrix cores inside a round (about two thirds busy with two workgroups per CU), outside it by the launch,
+// the first loads and the last stores, about 10 us.  Measured against loads through registers into padded LDS rows, fp32
+// gate, dm outputs of dm columns: 4680 tokens, dm 1536 39.9 -> 31.5 us; 1560 tokens 25.0 -> 19.7 us; 18720 tokens
+// 129 -> 106 us; 37440 tokens 235 -> 209 us; 999 tokens, dm 320 10.8 -> 9.2 us.  A 256 x 128 shape was nowhere better than
+// the best of these by more than 4 %.
 constexpr int GK = 64;                        // hidden columns per step
-constexpr int GROW = 2 * GK + 16;             // LDS bytes per staged row piece
+constexpr int GROW = 2 * GK;                  // LDS bytes per staged row piece
 
-template <int TM, int TN, int NTH>
-__global__ __launch_bounds__(NTH, 512 / NTH) void gate_dense_kernel(GateArgs a, int n_ntile)
+template <int TM, int TN, int NTH, int ST>
+__global__ __launch_bounds__(NTH, NTH / 256) void gate_dense_kernel(GateArgs a, int n_ntile)
 {
-    constexpr int WM = TM / 64, WN = NTH / 64 / WM;      // wavefronts along tokens, along outputs
+    constexpr int NW = NTH / 64;
+    constexpr int WM = TM / 64, WN = NW / WM;            // wavefronts along tokens, along outputs
     constexpr int NB = TN / WN / 32;                     // 32-output blocks per wavefront
-    constexpr int PR = NTH / 8;                          // rows covered by one round of 16-byte pieces
-    constexpr int XCHD = TM / PR, WCHD = TN / PR;        // pieces per thread and step: x, Wg
-    constexpr int OROW = TN + 4;                         // floats per row of the output tile staged in LDS
+    constexpr int XP = TM / 8 / NW, WP = TN / 8 / NW;    // loads of 8 rows per wavefront and step: x, Wg
     constexpr int STG = (TM + TN) * GROW;
-    static_assert(WM * WN * 64 == NTH && NB * 32 * WN == TN && XCHD * PR == TM && WCHD * PR == TN, "tile shape");
-    static_assert(32 * WM * OROW * 4 <= 2 * STG, "half of the output tile reuses the operand stages");
-    __shared__ __attribute__((aligned(16))) unsigned char sm[2 * STG];   // [stage][x rows, Wg rows]
+    constexpr int OROW = 64 + 4, OBYTES = 32 * OROW * 4; // 32 tokens x 64 outputs of a wavefront on their way out
+    static_assert(WM * WN == NW && NB * 32 * WN == TN && XP * 8 * NW == TM && WP * 8 * NW == TN && NB % 2 == 0, "tile shape");
+    static_assert(ST >= 2 && ST * STG <= 160 * 1024, "stages");
+    static_assert(NW * OBYTES <= ST * STG, "the wavefronts' output tiles reuse the stages");
+    __shared__ __attribute__((aligned(1024))) unsigned char sm[ST * STG];   // [stage][x rows, Wg rows]
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63, hh = lane >> 5, c = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, hh = lane >> 5, c = lane & 31;
     const int wm = wave % WM, wn = wave / WM;
     const int dm = a.dm, N = a.n_out;
     const long long ntok = (long long)a.B * a.L;
@@ -147,40 +153,29 @@ __global__ __launch_bounds__(NTH, 512 / NTH) void gate_dense_kernel(GateArgs a, 
     const uint32_t x_bytes = (uint32_t)(ntok * dm * 2), w_bytes = (uint32_t)((long long)N * dm * 2);
     const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(a.x, x_bytes);
     const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(a.Wg, w_bytes);
-    const int prow = tid >> 3, pcol = tid & 7;           // piece i of this thread: row prow + PR i, 16-byte column pcol
-    const int nk = (dm + GK - 1) / GK;
+    const int nk = dm / GK;                              // dm is a multiple of 64
 
-    // byte offsets of this thread's pieces at step 0; rows past the end point past the buffer (reads return zero)
-    uint32_t xoff[XCHD], woff[WCHD];
+    // Load i of this wavefront fills the rows 8 (NW i + wave) + 0..7, lane = (row lane / 8, chunk lane % 8).  Byte
+    // offsets at step 0; rows past the end point beyond the buffer at every step (and read as zero)
+    const uint32_t colb = 16 * ((lane & 7) ^ (4 * (wave & 1) + (lane >> 4)));
+    uint32_t xoff[XP], woff[WP];
 #pragma unroll
-    for (int i = 0; i < XCHD; ++i) {
-        const int row = prow + PR * i;
-        xoff[i] = tok0 + row < ntok ? (uint32_t)((tok0 + row) * dm * 2 + 16 * pcol) : x_bytes;
+    for (int i = 0; i < XP; ++i) {
+        const long long row = tok0 + 8 * (NW * i + wave) + (lane >> 3);
+        xoff[i] = row < ntok ? (uint32_t)(row * dm * 2) + colb : 0x80000000u;
     }
 #pragma unroll
-    for (int i = 0; i < WCHD; ++i) {
-        const int row = prow + PR * i;
-        woff[i] = n0 + row < N ? (uint32_t)((long long)(n0 + row) * dm * 2 + 16 * pcol) : w_bytes;
+    for (int i = 0; i < WP; ++i) {
+        const long long row = n0 + 8 * (NW * i + wave) + (lane >> 3);
+        woff[i] = row < N ? (uint32_t)(row * dm * 2) + colb : 0x80000000u;
     }
-    u32x4 xr[2][XCHD], wr[2][WCHD];
-    auto fetch = [&](int kc, auto j_) __attribute__((always_inline)) {   // step kc into register set j; rows and columns past the end read zeros
-        constexpr int j = decltype(j_)::value;
-        const uint32_t colb = 2 * GK * kc;
-        const bool okc = kc < nk && (int)colb + 16 * pcol < 2 * dm;
+    const uint32_t lds0 = lds_address(sm) + 1024 * wave;
+    auto fetch = [&](int kc, int st) __attribute__((always_inline)) {   // step kc into stage st; XP + WP loads also past the last step
+        const uint32_t kb = kc < nk ? 2 * GK * kc : 0x80000000u;
 #pragma unroll
-        for (int i = 0; i < XCHD; ++i)
-            xr[j][i] = __builtin_amdgcn_raw_buffer_load_b128(x_rsrc, okc && xoff[i] != x_bytes ? xoff[i] + colb : x_bytes, 0, 0);
+        for (int i = 0; i < XP; ++i) load_to_lds(x_rsrc, kc < nk ? xoff[i] + kb : kb, lds0 + st * STG + 1024 * NW * i);
 #pragma unroll
-        for (int i = 0; i < WCHD; ++i)
-            wr[j][i] = __builtin_amdgcn_raw_buffer_load_b128(w_rsrc, okc && woff[i] != w_bytes ? woff[i] + colb : w_bytes, 0, 0);
-    };
-    auto stage = [&](int st, auto j_) __attribute__((always_inline)) {
-        constexpr int j = decltype(j_)::value;
-        unsigned char *p = sm + st * STG + prow * GROW + 16 * pcol;
-#pragma unroll
-        for (int i = 0; i < XCHD; ++i) *(u32x4 *)(p + PR * i * GROW) = xr[j][i];
-#pragma unroll
-        for (int i = 0; i < WCHD; ++i) *(u32x4 *)(p + (TM + PR * i) * GROW) = wr[j][i];
+        for (int i = 0; i < WP; ++i) load_to_lds(w_rsrc, kc < nk ? woff[i] + kb : kb, lds0 + st * STG + TM * GROW + 1024 * NW * i);
     };
     f32x16 acc[2][NB];
 #pragma unroll
@@ -189,92 +184,98 @@ __global__ __launch_bounds__(NTH, 512 / NTH) void gate_dense_kernel(GateArgs a, 
         for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    auto contract = [&](int st) __attribute__((always_inline)) {
-        const unsigned char *xs = sm + st * STG + (64 * wm + c) * GROW + 16 * hh;
-        const unsigned char *ws = sm + st * STG + (TM + 32 * NB * wn + c) * GROW + 16 * hh;
+    // fragments of one 16-column k-step of a stage, in two sets: the next k-step is read while the current one is multiplied
+    bf16x8 xa[2][2], wb[2][NB];
+    const unsigned char *xs = sm + (64 * wm + c) * GROW, *ws = sm + (TM + 32 * NB * wn + c) * GROW;
+    const int swz = (c >> 1) & 7;                        // the same for all rows c + 32 i
+    auto read = [&](int st, auto t_) __attribute__((always_inline)) {
+        constexpr int t = decltype(t_)::value;
+        const int ch = st * STG + 16 * ((2 * t + hh) ^ swz);
 #pragma unroll
-        for (int t = 0; t < GK / 16; ++t) {
-            bf16x8 xa[2], wb[NB];
+        for (int i = 0; i < 2; ++i) xa[t & 1][i] = *(const bf16x8 *)(xs + 32 * i * GROW + ch);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) xa[i] = *(const bf16x8 *)(xs + 32 * i * GROW + 32 * t);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) wb[j] = *(const bf16x8 *)(ws + 32 * j * GROW + 32 * t);
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[i], wb[j], acc[i][j], 0, 0, 0);
-        }
+        for (int j = 0; j < NB; ++j) wb[t & 1][j] = *(const bf16x8 *)(ws + 32 * j * GROW + ch);
     };
-
-    const std::integral_constant<int, 0> J0{};
-    const std::integral_constant<int, 1> J1{};
-    // Step kc lives in register set kc % 2 and LDS stage kc % 2.  A step requests the loads of step kc + 2
-    // first (its register set was staged in the previous step), contracts stage kc % 2 and then stages step
-    // kc + 1, whose loads were requested a whole step earlier.
-    fetch(0, J0);
-    fetch(1, J1);
-    stage(0, J0);
-    lds_barrier();
-    for (int kc = 0; kc < nk; kc += 2) {
-        fetch(kc + 2, J0);
-        contract(0);
-        stage(1, J1);                 // step kc + 1 (zeros past the end); stage 1 was last read before the previous barrier
-        lds_barrier();
-        fetch(kc + 3, J1);
-        if (kc + 1 < nk) contract(1);
-        stage(0, J0);
-        lds_barrier();
-    }
-
-    // Epilogue through LDS (free after the last barrier), one 32-token block of every wavefront at a time:
-    // accumulator register r of block (i, j) is token 64 wm + 32 i + 8 (r / 4) + 4 hh + r % 4, output
-    // 32 (NB wn + j) + c; the 32 WM staged rows are then read back by rows, 16 bytes of fp32 per lane, so
-    // that a store instruction writes whole row pieces of up to 1 KB.
-    float *ot = reinterpret_cast<float *>(sm);
-    const bool vec = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(a.g) & 15) == 0;   // every row of g starts 16-byte (bf16: 8-byte) aligned
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        if (i) lds_barrier();                            // the first block has been read back
+    auto multiply = [&](auto t_) __attribute__((always_inline)) {
+        constexpr int t = decltype(t_)::value;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                ot[(32 * wm + 8 * (r >> 2) + 4 * hh + (r & 3)) * OROW + 32 * (NB * wn + j) + c] = acc[i][j][r];
-        lds_barrier();
-#pragma unroll 4
-        for (int id = tid; id < 32 * WM * (TN / 4); id += NTH) {
-            const int row = id / (TN / 4), col = 4 * (id % (TN / 4)), n = n0 + col;
-            const long long tok = tok0 + 64 * (row >> 5) + 32 * i + (row & 31);
-            if (tok >= ntok || n >= N) continue;
-            f32x4 s = *(const f32x4 *)(ot + row * OROW + col);
+            for (int i = 0; i < 2; ++i)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[t & 1][i], wb[t & 1][j], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int T = GK / 16;
+
+    // Step kc lives in stage kc % ST.  A step's barrier stands before its last k-step, whose fragments are in registers by
+    // then: past it every wavefront has read the stage, which takes the loads of step kc + ST, and the first fragments of
+    // step kc + 1 arrive under the last products.  The loads of the ST - 2 steps after that may still be in flight.
+    static_for<0, ST>([&](auto s_) { fetch(decltype(s_)::value, decltype(s_)::value); });
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((ST - 1) * (XP + WP)) : "memory");
+    read(0, std::integral_constant<int, 0>{});
+    for (int k0 = 0; k0 < nk; k0 += ST) {
+        static_for<0, ST>([&](auto s_) __attribute__((always_inline)) {
+            constexpr int st = decltype(s_)::value;
+            if (k0 + st >= nk) return;                   // uniform over the workgroup
+            static_for<0, T - 1>([&](auto t_) __attribute__((always_inline)) {
+                read(st, std::integral_constant<int, decltype(t_)::value + 1>{});
+                multiply(t_);
+            });
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((ST - 2) * (XP + WP)) : "memory");
+            fetch(k0 + st + ST, st);
+            read((st + 1) % ST, std::integral_constant<int, 0>{});
+            multiply(std::integral_constant<int, T - 1>{});
+        });
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // nothing in flight, every stage read
+
+    // Epilogue through LDS, a wavefront for itself, 32 tokens x 64 outputs at a time: accumulator register r of block (i, j)
+    // is token 64 wm + 32 i + 8 (r / 4) + 4 hh + r % 4, output 32 (NB wn + j) + c; the rows are read back 16 bytes of
+    // fp32 per lane, so that a store instruction writes four row pieces of 256 bytes.
+    float *ot = reinterpret_cast<float *>(sm + wave * OBYTES);
+    const bool vec = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(a.g) & 15) == 0;   // every row of g starts 16-byte (bf16: 8-byte) aligned
 #pragma unroll
-            for (int e = 0; e < 4; ++e) s[e] = 1.0f / (1.0f + __expf(-s[e]));
-            if (vec) {
-                if (a.g_is_bf16) {
-                    bf16x4 o;
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = to_bf16(s[e]);
-                    *(bf16x4 *)((bf16_t *)a.g + tok * N + n) = o;
+        for (int jp = 0; jp < NB; jp += 2) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) ot[(8 * (r >> 2) + 4 * hh + (r & 3)) * OROW + 32 * j + c] = acc[i][jp + j][r];
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {             // (a wavefront's LDS operations complete in order)
+                const int row = 4 * it + (lane >> 4), n = n0 + 32 * (NB * wn + jp) + 4 * (lane & 15);
+                const long long tok = tok0 + 64 * wm + 32 * i + row;
+                f32x4 s = *(const f32x4 *)(ot + row * OROW + 4 * (lane & 15));
+                if (tok >= ntok || n >= N) continue;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[e] = 1.0f / (1.0f + __expf(-s[e]));
+                if (vec) {
+                    if (a.g_is_bf16) {
+                        bf16x4 o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = to_bf16(s[e]);
+                        *(bf16x4 *)((bf16_t *)a.g + tok * N + n) = o;
+                    } else {
+                        *(f32x4 *)((float *)a.g + tok * N + n) = s;
+                    }
                 } else {
-                    *(f32x4 *)((float *)a.g + tok * N + n) = s;
-                }
-            } else {
-                for (int e = 0; e < 4 && n + e < N; ++e) {
-                    if (a.g_is_bf16) ((bf16_t *)a.g)[tok * N + n + e] = to_bf16(s[e]);
-                    else ((float *)a.g)[tok * N + n + e] = s[e];
+                    for (int e = 0; e < 4 && n + e < N; ++e) {
+                        if (a.g_is_bf16) ((bf16_t *)a.g)[tok * N + n + e] = to_bf16(s[e]);
+                        else ((float *)a.g)[tok * N + n + e] = s[e];
+                    }
                 }
             }
         }
-    }
 }
 
-template <int TM, int TN, int NTH>
+template <int TM, int TN, int NTH, int ST>
 hipError_t launch_gate_dense(const GateArgs &a, long long ntok, hipStream_t stream)
 {
     const long long n_ntile = (a.n_out + TN - 1) / TN, n_mtile = (ntok + TM - 1) / TM;
     if (n_mtile * n_ntile > 0x7fffffffLL) return hipErrorInvalidValue;
-    return launch_kernel(gate_dense_kernel<TM, TN, NTH>, dim3((unsigned)(n_mtile * n_ntile)), dim3(NTH), stream, a, (int)n_ntile);
+    return launch_kernel(gate_dense_kernel<TM, TN, NTH, ST>, dim3((unsigned)(n_mtile * n_ntile)), dim3(NTH), stream, a, (int)n_ntile);
 }
 
 }  // namespace
@@ -288,9 +289,16 @@ hipError_t launch_gate_proj_bf16(const GateArgs &a, hipStream_t stream)
     // x and Wg are addressed with 32-bit byte offsets
     if (ntok * a.dm * 2 > 0x7fffffffLL || (long long)a.n_out * a.dm * 2 > 0x7fffffffLL) return hipErrorInvalidValue;
     if (a.n_out > 32) {
-        // the large tiles once they fill the chip at least twice
-        const long long big = ((ntok + 255) / 256) * ((a.n_out + 255) / 256);
-        return big >= 2 * kNumCu ? launch_gate_dense<256, 256, 512>(a, ntok, stream) : launch_gate_dense<128, 128, 256>(a, ntok, stream);
+        if (a.dm % GK != 0) return hipErrorInvalidValue;
+        // One workgroup per CU: 128 x 128 with deep stages (256 tiles of dm 2048: 25.1 us, with two stages 28.8).  Beyond,
+        // the shape with the shorter sum of rounds, one of large tiles taking as long as about 1.5 of small ones
+        // (measured 1.47 to 1.6): 564 small or 144 large tiles of dm 1536 47.9 and 46.5 us, 1764 or 444 128 and 106 us,
+        // 444 or 114 31.5 and 47.7 us; 1512 or 384 of dm 3072, where the rule is indifferent, 171 and 169 us.
+        const long long small = ((ntok + 127) / 128) * ((a.n_out + 127) / 128), big = ((ntok + 255) / 256) * ((a.n_out + 255) / 256);
+        if (small <= kNumCu) return launch_gate_dense<128, 128, 256, 4>(a, ntok, stream);
+        const long long small_rounds = (small + 2 * kNumCu - 1) / (2 * kNumCu), big_rounds = (big + kNumCu - 1) / kNumCu;
+        return 3 * big_rounds <= 2 * small_rounds ? launch_gate_dense<256, 256, 512, 2>(a, ntok, stream)
+                                                  : launch_gate_dense<128, 128, 256, 2>(a, ntok, stream);
     }
     return launch_kernel(gate_proj_kernel, dim3((unsigned)nwg), dim3(NT), stream, a);
 }

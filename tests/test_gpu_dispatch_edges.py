@@ -111,3 +111,28 @@ def test_gdn_blocks_of_similar_keys(lib, oracle, B, H, L, D):  # noqa: F811
     e = rel_err_per_head(to_np(S_dev), ref)
     print(f"gdn similar keys {B}x{H}x{L}x{D}: {e:.2e}")
     assert e <= TOL_STATE, f"{e:.3e}"
+
+
+# Dense gate projection: 128 x 128 tiles with four stages (fewer hidden steps than stages, ragged tokens and outputs, rows
+# of g that do not start aligned), with two stages beyond one tile per CU, 256 x 256 tiles once they need fewer rounds
+# (odd step counts, outputs that end inside a tile).
+@pytest.mark.parametrize("B,L,H,D,mode,gdt", [
+    (1, 1, 1, 64, "element", "f32"), (2, 65, 33, 64, "head", "f32"), (1, 129, 39, 64, "head", "bf16"), (1, 200, 5, 64, "element", "bf16"),
+    (3, 127, 3, 128, "element", "f32"), (1, 33000, 1, 64, "element", "f32"), (3, 11001, 35, 64, "head", "bf16"),
+    (1, 33000, 2, 128, "element", "bf16"), (2, 16500, 3, 64, "element", "f32")])
+def test_gate_dense_tiles(lib, B, L, H, D, mode, gdt):  # noqa: F811
+    gen = torch.Generator().manual_seed(B * L + H)
+    n = H if mode == "head" else H * D
+    x = torch.randn((B, L, H * D), generator=gen).to(torch.bfloat16)
+    Wg = (torch.randn((n, H * D), generator=gen) / (H * D) ** 0.5).to(torch.bfloat16)
+    shape = (B, L, H) if mode == "head" else (B, L, H, D)
+    pad = 64                                              # guard values behind the gate: rows past the end are not stored
+    buf = torch.full((B * L * n + pad,), 7.0, dtype=torch.bfloat16 if gdt == "bf16" else torch.float32, device="cuda")
+    g = buf[:B * L * n].view(shape)
+    lib.arl2_gate_proj(dev(x), dev(Wg), g)
+    torch.cuda.synchronize()
+    ref = torch.sigmoid(x.reshape(B * L, -1).double() @ Wg.double().T).reshape(shape)
+    # sigmoid changes by at most a quarter of the fp32 sum's error; a bf16 gate adds half an ulp below one
+    err = (g.cpu().double() - ref).abs().max().item()
+    assert err <= (2.0 ** -9 + 2e-6 if gdt == "bf16" else 2e-6), f"{err:.3e}"
+    assert bool((buf[B * L * n:] == 7.0).all())
