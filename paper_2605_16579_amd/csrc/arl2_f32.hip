@@ -99,7 +99,8 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb)
     for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-    float m = -INFINITY, l = 0.f;             // running maximum of the scaled logits; this lane's share of the row sum
+    // running maximum of the scaled logits (finite also while every logit was -inf); this lane's share of the row sum
+    float m = -FLT_MAX, l = 0.f;
 
     if (wave < nblk) fetch_k(wave);
 #pragma unroll 1

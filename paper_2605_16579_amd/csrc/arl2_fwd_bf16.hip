@@ -456,7 +456,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             const int key = first_key(0) + 8 * (r >> 2) + 4 * hh + (r & 3);
             mx = fmaxf(mx, key < Lkv ? s_acc[0][r] : -INFINITY);
         }
-        m_run = xhalf_max(mx) * scale_log2;
+        m_run = fmaxf(xhalf_max(mx) * scale_log2, -FLT_MAX);     // finite also where every logit of the block is -inf
     };
     // second GEMM of the last key block `blk` of parity P (its first fragments are in flight)
     auto last_product = [&](auto p_, int blk) {

@@ -37,6 +37,24 @@ def test_fp32_tiles_and_key_groups(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
     assert e <= TOL_F32, f"commit: {e:.3e}"
 
 
+# Keys masked by logits of -inf: a wavefront whose first key blocks are all masked still merges what it has, or nothing.
+@pytest.mark.parametrize("dtype,B,H,Lq,Lkv,D,lo,hi", [
+    ("f32", 1, 2, 40, 300, 64, 0, 140), ("f32", 1, 2, 40, 200, 128, 32, 64), ("f32", 1, 1, 33, 300, 128, 10, 300),
+    ("bf16", 1, 2, 40, 128, 128, 32, 64), ("bf16", 1, 2, 130, 128, 64, 0, 64), ("bf16", 1, 2, 40, 64, 128, 32, 64),
+    ("bf16", 17, 16, 40, 100, 64, 0, 40)])
+def test_readout_keys_masked_by_infinite_logits(lib, oracle, dtype, B, H, Lq, Lkv, D, lo, hi):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["tiny" if dtype == "f32" else "ragged_small"], name=f"inf_{dtype}_{B}_{H}_{Lq}_{Lkv}_{D}",
+                            B=B, H=H, L=Lq, D=D, qkv_scale=1.0)
+    q, _, _, _ = W.pass_inputs(w, 0, 0)
+    k, v = (W.normal(5, w, (B, Lkv, H, D), tag) for tag in (1, 2))
+    q[..., 0] = 1.0
+    k[:, lo:hi, :, 0] = -float("inf")
+    seen = [j for j in range(Lkv) if not lo <= j < hi]
+    ref = oracle.fwd(to_np(q), to_np(k[:, seen].contiguous()), to_np(v[:, seen].contiguous()))
+    e = rel_err(to_np(gpu_fwd(lib, q, k, v, None, None)), ref)
+    assert e <= (TOL_F32 if dtype == "f32" else TOL_BF16_OUT), f"{e:.3e}"
+
+
 # Readout: half tiles of 128 rows with two key groups while they fit one round (from 33 keys on: one, two, many key
 # tiles, a last tile with keys for one or both groups), whole tiles of 256 rows beyond, and whole tiles followed by half
 # tiles when the last round would be at most half full (272 and 544 tiles; a last half tile with and without rows).
