@@ -299,7 +299,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     // every other step, so that the copy runs under the MFMAs instead of in a burst before the barrier; 3 (several key
     // groups) the whole copy of an interval and its barrier, as soon as the slot has requested its last fragment: the
     // fragments requested after that are the next slot's, from the tiles that the barrier publishes; 4 the same for the last
-    // tile, whose V is all that is left to store.
+    // tile, whose V is all that is left to store (into stage `cstage`).
     auto slot = [&](auto par_, auto has_s_, auto has_pv_, auto next_s_, auto masked_, int j, auto copy_, int cstage) {
         constexpr int PAR = decltype(par_)::value;
         constexpr int COPY = decltype(copy_)::value;
@@ -379,7 +379,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
                     constexpr int p = decltype(p_)::value;
                     if constexpr (p * (NS - C::PF) / (2 * C::KCH) == n) {
                         if constexpr (COPY == 3) copy_part(PAR, p_);
-                        else if constexpr (p & 1) store_tile_part(PAR, p_);
+                        else if constexpr (p & 1) store_tile_part(cstage, p_);
                     }
                 });
                 if constexpr (n == NS - C::PF - 1) lds_barrier();
@@ -504,6 +504,10 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         }
     };
     constexpr bool EARLY_STATE = KG > 1 && !FUSED_MAP;   // the state goes to LDS before the key loop
+    // D = 128 with the query rows kept to the end: 29 registers spilled with two endings (120 bytes of scratch per lane), none
+    // with one: 64 heads, 328 tokens 15.3 us with, 12.9 us without the spill.  The other forms have registers left, and with
+    // one ending they are 2 to 5 % slower (12 heads x 64, 200 tokens: 6.9 us against 7.2 us).
+    constexpr bool ONE_ENDING = D == 128 && !FUSED_MAP;
 
     if constexpr (KG == 1) {
         const int ntiles = (Lkv + BN - 1) / BN;
@@ -621,8 +625,18 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             // the last slot has no first product: its fragments start with V(nt - 2)
             const unsigned char *vp = smem + v_block(j - 1) + v_frag_off;
             static_for<0, C::PF>([&](auto m_) { fr[decltype(m_)::value] = v_frag(vp, m_); });
-            if (j & 1) {
-                slot(par1, no, yes, no, yes, j, copy4, 0);
+            // An ending for each parity, or one, to whose registers the even parity's logits and probabilities are moved: with
+            // two the largest form of this function does not fit the registers.
+            if constexpr (ONE_ENDING) {
+                if ((j & 1) == 0) {
+                    s_acc[1] = s_acc[0];
+                    pf[0] = pf[2];
+                    pf[1] = pf[3];
+                }
+                slot(par1, no, yes, no, yes, j, copy4, j & 1);
+                last_product(par1, j);
+            } else if (j & 1) {
+                slot(par1, no, yes, no, yes, j, copy4, 1);
                 last_product(par1, j);
             } else {
                 slot(par0, no, yes, no, yes, j, copy4, 0);
