@@ -515,19 +515,21 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         {
             u32x4 k1[C::KCH], v1[C::KCH], x[QCH];
             load_k(0, kst);
-            fetch_rows(x);
+            if (q0 < Lq) fetch_rows(x);
             load_v(0, vst);
             load_k(1, k1);
             load_v(1, v1);
             store_k(0, kst);
             unsigned char *mine = smem + 2 * C::STAGE + wave * 32 * C::KROW;     // in stages that tile 2 and on will use
             static_assert(KG > 1 || 8 * 32 * C::KROW <= 2 * C::STAGE, "the query rows pass through two ring stages");
-            put_rows(mine, x);
+            if (q0 < Lq) put_rows(mine, x);
             store_v(0, vst);
             store_k(1, k1);
             store_v(1, v1);
-            get_rows(mine);
-            square_rows();
+            if (q0 < Lq) {              // (wavefronts without rows keep off the LDS: 128 rows over 300 keys 8.7 -> 8.2 us)
+                get_rows(mine);
+                square_rows();
+            }
         }
         __syncthreads();
         clear_output();
@@ -937,6 +939,24 @@ hipError_t launch_fwd(const FwdArgs &a, FwdGrid g, float scale_log2, hipStream_t
     return launch_kernel(fwd_bf16_kernel<D, SPLIT, false>, grid, block, stream, a, g, scale_log2);
 }
 
+// Whether `tiles` query tiles of up to `rows` rows are faster in half tiles, as far as rows and keys decide it.  A half tile
+// has a longer start and end (two key groups and their exchange); what it shortens is the key loop.  Half against whole
+// tiles, in us, softmax alone (with a state, gate or fused map the lines are the same):
+//   more than 128 rows, so that halving makes more workgroups: from two key tiles on (128 heads x 128, 200 rows: 64 keys
+//     7.7 and 7.4, 65 keys 7.6 and 8.5; x 64: 5.7 and 5.3, 5.7 and 6.1);
+//   up to 128 rows, where two wavefronts share a loop and nothing else is gained: 24 heads x 128, 128 rows: 384 keys 9.6
+//     and 8.9, 640 keys 12.3 and 11.9, 1024 keys 16.5 and 16.5; 64 rows: 640 keys 11.7 and 11.8; 24 heads x 64, 64 rows: 384
+//     keys 7.0 and 6.7, 512 keys 7.8 and 7.8, 640 keys 8.7 and 8.9;
+//   the same on more than three quarters of the CUs at D = 128, where reading keys and values is the bound and whole tiles
+//     have more of them in flight: 256 heads, 128 rows: 1536 keys 37 and 35, 2048 keys 49 and 57.
+template <int D>
+bool halves_pay(int rows, int keys, long long tiles)
+{
+    if (rows > 128) return keys > BN;                    // (two key groups need a key each in the first tile)
+    if (D == 128 && 4 * tiles > 3 * kNumCu) return keys >= 32 * BN;
+    return keys >= (D == 128 ? 10 : 8) * BN;
+}
+
 template <int D>
 hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
 {
@@ -949,24 +969,23 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
     g.n_tiles = g.n_whole = (int)(heads * q256);
     // more workgroups than CUs, a ragged last query tile per head, and whole heads per XCD
     g.ragged_last = g.n_tiles > kNumCu && a.Lq % 256 != 0 && q256 > 1 && heads % kNumXcd == 0;
-    if (a.Lkv > 32) {                            // two key groups need a key each in the first tile
-        // Half tiles while they run as one round: 1024 tokens x 16 heads x 128 21.5 us against 28.6 us for whole tiles, x 32
-        // heads (256 half tiles) 26.6 against 29.9 us; just beyond, x 48 heads, 43.9 against 34.9 us.
-        if (heads * q128 <= kNumCu) {
-            g.n_qtiles = (int)q128;
-            g.n_tiles = (int)(heads * q128);
-            g.ragged_last = 0;
-            return launch_fwd<D, kHalves>(a, g, scale_log2, stream);
-        }
-        // The tail of a launch of several rounds: when at most half of the CUs would have a tile in it, these tiles are
-        // halved.  A half tile takes 0.57 of the time of a whole one, so that 2 x 1000 tokens x 136 heads (2.08
-        // rounds) take 94 us instead of 102 us, 2048 tokens x 66 heads x 64 wide (2.06 rounds) 97 instead of 110 us;
-        // nothing changes where more than half of the CUs have work in the last round.
-        const int rest = g.n_tiles % kNumCu;
-        if (g.n_tiles > kNumCu && rest > 0 && 2 * rest <= kNumCu) {
-            g.n_whole = g.n_tiles - rest;
-            return launch_fwd<D, kHalvesLast>(a, g, scale_log2, stream);
-        }
+    // Half tiles while they run as one round: 1024 tokens x 16 heads x 128 21.5 us against 28.6 us for whole tiles, x 32
+    // heads (256 half tiles) 26.6 against 29.9 us; just beyond, x 48 heads, 43.9 against 34.9 us.
+    if (heads * q128 <= kNumCu && halves_pay<D>(a.Lq, a.Lkv, heads)) {
+        g.n_qtiles = (int)q128;
+        g.n_tiles = (int)(heads * q128);
+        g.ragged_last = 0;
+        return launch_fwd<D, kHalves>(a, g, scale_log2, stream);
+    }
+    // The tail of a launch of several rounds: when at most half of the CUs would have a tile in it, these tiles are
+    // halved.  A half tile takes 0.57 of the time of a whole one, so that 2 x 1000 tokens x 136 heads (2.08
+    // rounds) take 94 us instead of 102 us, 2048 tokens x 66 heads x 64 wide (2.06 rounds) 97 instead of 110 us;
+    // nothing changes where more than half of the CUs have work in the last round.
+    const int rest = g.n_tiles % kNumCu;
+    const int tail_rows = g.ragged_last || q256 == 1 ? (a.Lq - 1) % 256 + 1 : 256;
+    if (g.n_tiles > kNumCu && rest > 0 && 2 * rest <= kNumCu && halves_pay<D>(tail_rows, a.Lkv, rest)) {
+        g.n_whole = g.n_tiles - rest;
+        return launch_fwd<D, kHalvesLast>(a, g, scale_log2, stream);
     }
     return launch_fwd<D, kWhole>(a, g, scale_log2, stream);
 }

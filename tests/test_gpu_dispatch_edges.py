@@ -1,5 +1,6 @@
 """GPU parity at the sizes where a kernel's tiles, splits and dispatch rules change over, against the CPU oracle."""
 import dataclasses
+import re
 
 import numpy as np
 import pytest
@@ -55,9 +56,10 @@ def test_readout_keys_masked_by_infinite_logits(lib, oracle, dtype, B, H, Lq, Lk
     assert e <= (TOL_F32 if dtype == "f32" else TOL_BF16_OUT), f"{e:.3e}"
 
 
-# Readout: half tiles of 128 rows with two key groups while they fit one round (from 33 keys on: one, two, many key
-# tiles, a last tile with keys for one or both groups), whole tiles of 256 rows beyond, and whole tiles followed by half
-# tiles when the last round would be at most half full (272 and 544 tiles; a last half tile with and without rows).
+# Readout: half tiles of 128 rows with two key groups while they fit one round (more than 128 rows and two or more key
+# tiles, a last tile with keys for one or both groups), whole tiles of 256 rows beyond or with fewer rows or keys, and whole
+# tiles followed by half tiles when the last round would be at most half full (272 and 544 tiles; a last half tile with and
+# without rows).
 @pytest.mark.parametrize("B,H,Lq,Lkv,D", [
     (1, 2, 40, 32, 128), (1, 2, 40, 33, 128), (2, 1, 128, 64, 64), (1, 3, 129, 65, 128), (1, 2, 256, 97, 64), (1, 2, 300, 128, 128),
     (1, 2, 130, 161, 128), (2, 2, 385, 385, 64), (1, 2, 200, 200, 128), (8, 17, 150, 150, 64), (17, 16, 40, 40, 64), (17, 16, 200, 200, 64),
@@ -154,3 +156,23 @@ def test_gate_dense_tiles(lib, B, L, H, D, mode, gdt):  # noqa: F811
     err = (g.cpu().double() - ref).abs().max().item()
     assert err <= (2.0 ** -9 + 2e-6 if gdt == "bf16" else 2e-6), f"{err:.3e}"
     assert bool((buf[B * L * n:] == 7.0).all())
+
+
+# Where the readout's tile split changes over: two key tiles (65 keys) where halving makes more workgroups; ten (D = 128) or
+# eight (D = 64) where it does not, 32 at D = 128 on more than three quarters of the CUs; tails of ragged tiles with few
+# and with many rows.  `split` is the form of the kernel: 0 whole tiles, 1 halves, 2 whole ones, then halves.
+@pytest.mark.parametrize("B,H,Lq,Lkv,D,split", [
+    (1, 2, 130, 64, 128, 0), (1, 2, 130, 65, 128, 1), (2, 3, 200, 64, 64, 0), (2, 3, 200, 65, 64, 1), (2, 12, 64, 64, 128, 0),
+    (1, 2, 100, 639, 128, 0), (1, 2, 100, 640, 128, 1), (1, 3, 33, 511, 64, 0), (1, 3, 33, 512, 64, 1), (2, 12, 128, 128, 64, 0),
+    (14, 14, 20, 2047, 128, 0), (14, 14, 20, 2048, 128, 1), (17, 16, 128, 128, 128, 0), (17, 16, 20, 512, 64, 2), (17, 16, 300, 70, 64, 0),
+    (17, 16, 400, 70, 64, 2)])
+def test_readout_takes_the_faster_tile_split(lib, oracle, B, H, Lq, Lkv, D, split):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"line_{B}_{H}_{Lq}_{Lkv}_{D}", B=B, H=H, L=Lq, D=D)
+    q, _, _, _ = W.pass_inputs(w, 0, 0)
+    k, v = (W.normal(5, w, (B, Lkv, H, D), tag) for tag in (1, 2))
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        out = gpu_fwd(lib, q, k, v, None, None)
+    kernels = [e.key for e in prof.key_averages() if "fwd_bf16_kernel" in e.key]
+    assert len(kernels) == 1 and re.search(rf"<{D}, [^,]*\){split}, false>", kernels[0]), kernels
+    e = rel_err(to_np(out), oracle.fwd(to_np(q), to_np(k), to_np(v)))
+    assert e <= TOL_BF16_OUT, f"{e:.3e}"
