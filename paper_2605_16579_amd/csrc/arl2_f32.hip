@@ -24,9 +24,13 @@ typedef __attribute__((address_space(3))) void lds_void;
 // nobody else reads it), requested while the second product of the block before it runs.  The rows are not padded
 // (the direct load writes 16 bytes per lane in lane order); instead the lane at chunk j of row r loads chunk
 // j ^ r, so that the rows a fragment read touches lie on different banks.
+// The products of a row with a key or with the state are summed in several chains that are added at the end: one chain of
+// D products is the larger error of the two that an output has (relative to 64 bits, two chains for the state: 2.14e-7 ->
+// 1.57e-7 at D = 128; logits of +-20, chains of 16 products at D = 128 and two chains at D = 64: 1.11e-6 -> 4.4e-7 and
+// 8.1e-7 -> 5.2e-7; a vector-ALU kernel with 16 lanes per row has 2.09e-7, 7.8e-7 and 7.9e-7).
 // Measured, 12 heads x 128, 1560 tokens (15.7 GFLOP, 102 us at the 154 TFLOP/s that a large fp32 matrix product
-// reaches): 206 us; the vector-ALU kernel this replaces, 16 lanes per query row and two passes over the keys, took
-// 7160 us.  2 heads x 64, 64 tokens: 9 us against 38 us.
+// reaches): 194 us; the vector-ALU kernel, 16 lanes per query row and two passes over the keys, took 7160 us.
+// 2 heads x 64, 64 tokens: 8.7 us against 38 us.
 template <int D>
 __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb)
 {
@@ -55,14 +59,14 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb)
     // B operand of S^T: lane (row c, hh) holds features 8 t + 4 hh + 0..3 of its row
     f32x4 q[KT];
     auto load_q = [&](const float *src) {
-        float ss = 0.f;
+        f32x4 ss = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
             q[t] = *(const f32x4 *)(src + row_off + 8 * t + 4 * hh);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) ss = fmaf(q[t][j], q[t][j], ss);
+            for (int j = 0; j < 4; ++j) ss[j] = fmaf(q[t][j], q[t][j], ss[j]);
         }
-        return xhalf_sum(ss);
+        return xhalf_sum((ss[0] + ss[1]) + (ss[2] + ss[3]));
     };
     float qss = load_q((const float *)a.q);
 
@@ -84,6 +88,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb)
         }
     };
     float vr[2][4][DB];                       // V rows of four accumulator registers, current and next
+    uint32_t v_off;                           // of this lane in the block's first row: 4 hh tokens and 4 c bytes
     auto fetch_v = [&](__amdgpu_buffer_rsrc_t r, auto quad_) {
         constexpr int quad = decltype(quad_)::value;
 #pragma unroll
@@ -91,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb)
 #pragma unroll
             for (int db = 0; db < DB; ++db)
                 vr[quad & 1][j][db] = __builtin_bit_cast(
-                    float, __builtin_amdgcn_raw_buffer_load_b32(r, (uint32_t)(8 * quad + 4 * hh + j) * tok + 4 * c + 128 * db, 0, 0));
+                    float, __builtin_amdgcn_raw_buffer_load_b32(r, v_off + (uint32_t)(8 * quad + j) * tok + 128 * db, 0, 0));
     };
 
     f32x16 o[DB];
@@ -106,14 +111,44 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb)
 #pragma unroll 1
     for (int blk = wave; blk < nblk; blk += NW) {
         const __amdgpu_buffer_rsrc_t v_rsrc = rsrc_of(vg, blk);
+        v_off = 4 * hh * tok + 4 * c;
+        asm volatile("" : "+v"(v_off));       // (one offset and not sixteen kept over the loop)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // the K block has landed
         fetch_v(v_rsrc, std::integral_constant<int, 0>{});
-        f32x16 s = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        f32x16 s = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, s1 = s;
+        if constexpr (D == 64) {                                    // even and odd steps
 #pragma unroll
-        for (int t = 0; t < KT; ++t) {
-            const f32x4 ka = *(const f32x4 *)(kbuf + c * (D * 4) + 16 * ((2 * t + hh) ^ (c % CPR)));
+            for (int t = 0; t < KT; ++t) {
+                const f32x4 ka = *(const f32x4 *)(kbuf + c * (D * 4) + 16 * ((2 * t + hh) ^ (c % CPR)));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[j], q[t][j], s, 0, 0, 0);
+                for (int j = 0; j < 4; j += 2) {
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[j], q[t][j], s, 0, 0, 0);
+                    s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[j + 1], q[t][j + 1], s1, 0, 0, 0);
+                }
+            }
+            s += s1;
+        } else {                                                    // eight steps from zero, added up while the next eight run
+            static_for<0, KT / 2 + 1>([&](auto g_) {
+                constexpr int g = decltype(g_)::value;
+                const f32x16 done = s1;
+                if constexpr (g < KT / 2) {
+                    f32x16 r = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                    static_for<2 * g, 2 * g + 2>([&](auto t_) {
+                        constexpr int t = decltype(t_)::value;
+                        const f32x4 ka = *(const f32x4 *)(kbuf + c * (D * 4) + 16 * ((2 * t + hh) ^ (c % CPR)));
+                        static_for<0, 4>([&](auto j_) {
+                            constexpr int j = decltype(j_)::value;
+                            r = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[j], q[t][j], r, 0, 0, 0);
+                        });
+                    });
+                    s1 = r;
+                }
+                if constexpr (g > 0) {
+                    s = g == 1 ? done : s + done;
+                    asm volatile("" : "+v"(s));                     // (otherwise all sums are kept and added at the end)
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            });
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the K block has been read: it may be overwritten
         if (blk + NW < nblk) fetch_k(blk + NW);
@@ -187,12 +222,15 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb)
         if (a.q_lin != nullptr) qss = load_q((const float *)a.q_lin);   // the linear branch's own query (Eq. (3))
         const float rq = 1.0f / sqrtf(qss + a.l2_eps);
         const float *Sg = a.S + (size_t)bh * D * D + 32 * wave + c;
-        f32x16 inter = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        f32x16 inter = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, inter1 = inter;   // even and odd steps
 #pragma unroll
         for (int t = 0; t < KT; ++t)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < 4; j += 2) {
                 inter = __builtin_amdgcn_mfma_f32_32x32x2f32(Sg[(8 * t + 4 * hh + j) * D], q[t][j], inter, 0, 0, 0);
+                inter1 = __builtin_amdgcn_mfma_f32_32x32x2f32(Sg[(8 * t + 4 * hh + j + 1) * D], q[t][j + 1], inter1, 0, 0, 0);
+            }
+        inter += inter1;
         const size_t gtok = (size_t)b * Lq + (valid ? row : q0);
         const size_t gi = a.g_per_token ? gtok : gtok * H + h;
 #pragma unroll

@@ -176,3 +176,17 @@ def test_readout_takes_the_faster_tile_split(lib, oracle, B, H, Lq, Lkv, D, spli
     assert len(kernels) == 1 and re.search(rf"<{D}, [^,]*\){split}, false>", kernels[0]), kernels
     e = rel_err(to_np(out), oracle.fwd(to_np(q), to_np(k), to_np(v)))
     assert e <= TOL_BF16_OUT, f"{e:.3e}"
+
+
+# fp32 readout: root mean square error over that of the result.  With `D` products in one chain a rounding random walk gives
+# the linear branch about 2^-24 / sqrt(3) * 0.72 * sqrt(D / 2) (the first two bounds lie below that: 2.0e-7 and 1.4e-7); with
+# logits of +-20 the products of queries and keys decide, where a kernel with 16 partial sums per row has 7.8e-7.
+@pytest.mark.parametrize("D,scale,state,bound", [(128, 0.125, 4.0, 1.8e-7), (64, 0.125, 4.0, 1.35e-7), (128, 2.0, 0.1, 7.8e-7), (64, 2.0, 0.1, 7.8e-7)])
+def test_fp32_readout_error(lib, oracle, D, scale, state, bound):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["tiny"], name=f"f32_err_{D}_{scale}", B=1, H=4, L=500, D=D, qkv_scale=scale)
+    q, k, v, g = W.pass_inputs(w, 0, 0)
+    S = W.normal(6, dataclasses.replace(w, qkv_scale=state), (1, 4, D, D), 3, io_dtype="f32")
+    ref = oracle.fwd(to_np(q), to_np(k), to_np(v), to_np(S).astype(np.float64), to_np(g))
+    e = np.linalg.norm(to_np(gpu_fwd(lib, q, k, v, S, g)) - ref) / np.linalg.norm(ref)
+    print(f"fp32 readout D={D} scale {scale}: {e:.3e}")
+    assert e <= bound, f"{e:.3e}"

@@ -22,7 +22,8 @@ def scratch():
     return scratch_per_kernel(A.binding.LIB_PATH)
 
 
-def test_bf16_readout_kernels_use_no_scratch(scratch):
-    readouts = {name: n for name, n in scratch.items() if "fwd_bf16_kernel" in name}
-    assert len(readouts) == 12, sorted(scratch)           # two head dimensions, three tile splits, with and without the fused map
+def test_readout_kernels_use_no_scratch(scratch):
+    readouts = {name: n for name, n in scratch.items() if "fwd_bf16_kernel" in name or "fwd_f32_kernel" in name}
+    # bf16: two head dimensions, three tile splits, with and without the fused map; fp32: two head dimensions
+    assert len(readouts) == 12 + 2, sorted(scratch)
     assert not any(readouts.values()), {name: n for name, n in readouts.items() if n}
