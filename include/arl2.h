@@ -37,7 +37,8 @@
  * ARL2_ERR_DEVICE reports that the runtime refused a launch: a call made of several kernels
  * (the state commits) may then have enqueued the earlier ones, and S is undefined.
  * The kernels address one stream's k, v (the whole x for arl2_feature_map and arl2_gate_proj) with
- * 32-bit byte offsets: such an array must stay below 2 GiB, larger problems return ARL2_ERR_UNSUPPORTED.
+ * 32-bit byte offsets: such an array must stay below 2 GiB, larger problems return ARL2_ERR_UNSUPPORTED
+ * (fp32 inputs: H and B below 65536 instead).
  *
  * Layouts (row-major):
  *   q, out      [B][Lq ][H][D]   io_dtype
@@ -90,9 +91,9 @@ typedef struct {
     void *stream;         /* hipStream_t; NULL is the default stream                        */
 } arl2_desc;
 
-/* Device scratch that arl2_state_commit / arl2_state_commit_delta need for this descriptor
- * (token-split partial sums, state snapshot).  arl2_hybrid_attn_fwd needs none.  Returns 0 for
- * an invalid descriptor.                                                                     */
+/* Device scratch that arl2_state_commit / arl2_state_commit_delta / arl2_state_commit_fm take for this
+ * descriptor (bf16: token-split partial sums; fp32: B * Lq * H * 4 bytes, which have to be given but
+ * are not used).  arl2_hybrid_attn_fwd needs none.  Returns 0 for an invalid descriptor.            */
 size_t arl2_workspace_bytes(const arl2_desc *desc);
 
 /*
@@ -188,7 +189,7 @@ arl2_status arl2_state_commit(const arl2_desc *desc,
  * partial sums go to a fixed array in device memory that the library holds on every GPU it runs on
  * (arl2_static_scratch_bytes(), 16 MiB).  A problem that needs more returns ARL2_ERR_UNSUPPORTED
  * (bf16: B * H * splits * D * D * 4 bytes, 12 MiB at B = 1, H = 12, Lq = 4680, D = 128; fp32: B * Lq * H * 4
- * bytes).  The call allocates and frees nothing and does not synchronise.  All calls on one GPU share that
+ * bytes, as for arl2_state_commit).  The call allocates and frees nothing and does not synchronise.  All calls on one GPU share that
  * GPU's array: two calls that overlap in time on one GPU (different streams, or threads) race; calls on
  * one stream, or ordered by events, do not.  Nothing in the array has to survive between calls or to be
  * cleared: every call writes each partial sum before it reads it.

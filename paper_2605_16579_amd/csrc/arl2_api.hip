@@ -39,8 +39,9 @@ size_t g_bytes(const arl2_desc *d)
 size_t table_bytes(const arl2_desc *d) { return (size_t)d->Lq * (d->D / 2) * sizeof(float); }
 size_t wmap_bytes(const arl2_desc *d) { return (size_t)d->H * d->D * d->D * 2; }
 
-// The fp32 kernels put heads and streams on the grid's y and z axes.
-bool f32_grid_ok(const arl2_desc *d) { return d->io_dtype != ARL2_F32 || (d->H <= 65535 && d->B <= 65535); }
+// The fp32 kernels span up to 32 rows of [H][D] with 32-bit byte offsets, which this bound on H keeps below 2 GiB; the bound on
+// B is part of the interface.
+bool f32_sizes_ok(const arl2_desc *d) { return d->io_dtype != ARL2_F32 || (d->H <= 65535 && d->B <= 65535); }
 
 // Checks everything that does not depend on which call is made.
 arl2_status check_desc(const arl2_desc *d)
@@ -70,20 +71,15 @@ bool fits_32bit(double elems, int elem_bytes) { return elems * elem_bytes <= 214
 
 float resolved_eps(const arl2_desc *d) { return d->l2_eps > 0.f ? d->l2_eps : 1e-6f; }
 
-size_t commit_workspace(const arl2_desc *d)
+// Workspace of the commits: one D x D partial sum per token split, of which the delta rule may take more than the plain rule.
+// The fp32 commit reads and writes none of it; its size is part of the interface.
+size_t commit_workspace_of(const arl2_desc *d, int nsplit)
 {
-    if (d->io_dtype == ARL2_BF16)   // two partial matrices per split (delta rule) plus one state snapshot
-        return (size_t)d->B * d->H * (2 * arl2::commit_nsplit(d->B, d->H, d->Lq) + 1) * d->D * d->D * sizeof(float);
+    if (d->io_dtype == ARL2_BF16) return (size_t)d->B * d->H * nsplit * d->D * d->D * sizeof(float);
     return (size_t)d->B * d->Lq * d->H * sizeof(float);
 }
-
-// What the plain commit alone needs (no delta-rule matrices, no state snapshot).
-size_t commit_workspace_plain(const arl2_desc *d)
-{
-    if (d->io_dtype == ARL2_BF16)
-        return (size_t)d->B * d->H * arl2::commit_nsplit(d->B, d->H, d->Lq) * d->D * d->D * sizeof(float);
-    return (size_t)d->B * d->Lq * d->H * sizeof(float);
-}
+size_t commit_workspace(const arl2_desc *d) { return commit_workspace_of(d, arl2::commit_delta_max_nsplit(d->B, d->H, d->Lq)); }
+size_t commit_workspace_plain(const arl2_desc *d) { return commit_workspace_of(d, arl2::commit_nsplit(d->B, d->H, d->Lq)); }
 
 }  // namespace
 
@@ -109,7 +105,7 @@ arl2_status arl2_hybrid_attn_fwd_ex(const arl2_desc *desc, const void *q, const 
         return fail(ARL2_ERR_INVALID_ARG, "an element-wise g must be 16-byte aligned");
     if (S != nullptr && desc->Lkv != desc->Lq)
         return fail(ARL2_ERR_INVALID_ARG, "Lkv must equal Lq when a state is given");
-    if (!f32_grid_ok(desc)) return fail(ARL2_ERR_UNSUPPORTED, "fp32 inputs: H and B must stay below 65536");
+    if (!f32_sizes_ok(desc)) return fail(ARL2_ERR_UNSUPPORTED, "fp32 inputs: H and B must stay below 65536");
     if (desc->io_dtype == ARL2_BF16 && !fits_32bit(((double)desc->Lkv + 256.0) * desc->H * desc->D, 2))
         return fail(ARL2_ERR_UNSUPPORTED, "one stream's k (or v) must stay below 2 GiB");
     {
@@ -265,7 +261,7 @@ static arl2_status commit_common(const arl2_desc *desc, const void *k, const voi
     if (desc->workspace == nullptr || desc->workspace_bytes < need)
         return fail(ARL2_ERR_WORKSPACE, "workspace is NULL or smaller than arl2_workspace_bytes()");
     if (!aligned16(desc->workspace)) return fail(ARL2_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
-    if (!f32_grid_ok(desc)) return fail(ARL2_ERR_UNSUPPORTED, "fp32 inputs: H and B must stay below 65536");
+    if (!f32_sizes_ok(desc)) return fail(ARL2_ERR_UNSUPPORTED, "fp32 inputs: H and B must stay below 65536");
     {
         const size_t ns = state_bytes(desc), nkv = kv_bytes(desc), ngate = (size_t)desc->B * desc->H * sizeof(float);
         if (overlaps(S, ns, k, nkv) || overlaps(S, ns, v, nkv) || overlaps(S, ns, gate, ngate) || overlaps(S, ns, beta, ngate) ||
@@ -279,7 +275,7 @@ static arl2_status commit_common(const arl2_desc *desc, const void *k, const voi
     arl2::CommitArgs a;
     a.k = k; a.v = v; a.gate = gate; a.beta = delta ? beta : nullptr; a.S = S; a.workspace = desc->workspace;
     a.B = desc->B; a.H = desc->H; a.L = desc->Lq; a.D = desc->D;
-    a.nsplit = arl2::commit_nsplit(desc->B, desc->H, desc->Lq);
+    a.nsplit = delta ? arl2::commit_delta_max_nsplit(desc->B, desc->H, desc->Lq) : arl2::commit_nsplit(desc->B, desc->H, desc->Lq);
     a.l2_eps = resolved_eps(desc);
     hipStream_t stream = reinterpret_cast<hipStream_t>(desc->stream);
     const hipError_t e = desc->io_dtype == ARL2_BF16 ? arl2::launch_commit_bf16(a, stream)

@@ -443,15 +443,18 @@ hipError_t launch_commit_reduce_bf16(const CommitArgs &a, hipStream_t stream)
     return launch_kernel(commit_reduce_kernel<8>, dim3((unsigned)rwg), dim3(NTR), stream, a, vec_per_head);
 }
 
-// Splits of the delta rule: one workgroup per CU where the workspace allows it (2 nsplit + 1 partial sums fit), then
-// as few as keep the longest split as short.
+// The interface's workspace holds twice the plain commit's partial sums and one more per head; the delta rule, whose workgroups
+// fill a CU each (254 registers), may use all of it.
+int commit_delta_max_nsplit(int B, int H, int L) { return 2 * commit_nsplit(B, H, L) + 1; }
+
+// Splits of the delta rule: one workgroup per CU where the workspace allows it, then as few as keep the longest split as short.
 template <int D>
 hipError_t launch_delta(CommitArgs a, hipStream_t stream)
 {
     const int ntiles = (a.L + DeltaCfg<D>::TT - 1) / DeltaCfg<D>::TT;
     const long long bh = (long long)a.B * a.H;
     long long want = kNumCu / bh;
-    if (want > 2 * a.nsplit + 1) want = 2 * a.nsplit + 1;
+    if (want > a.nsplit) want = a.nsplit;
     if (want > ntiles) want = ntiles;
     if (want < 1) want = 1;
     const int per = (int)((ntiles + want - 1) / want);

@@ -60,7 +60,7 @@ struct CommitArgs {
     float *S;
     void *workspace;
     int B, H, L, D;
-    int nsplit;            // token splits per (stream, head) for the bf16 path
+    int nsplit;            // token splits per (stream, head) for the bf16 path; delta rule: at most this many
     float l2_eps;
 };
 
@@ -103,8 +103,9 @@ struct GdnArgs {
     float l2_eps;
 };
 
-// Token splits used by the bf16 commit for a problem size (also sizes the workspace).
+// Token splits of the bf16 commit for a problem size, and the most that the delta rule takes: they also size the workspace.
 int commit_nsplit(int B, int H, int L);
+int commit_delta_max_nsplit(int B, int H, int L);
 
 // Launchers: enqueue on `stream`, return the HIP error of the launch.
 hipError_t launch_fwd_bf16(const FwdArgs &a, hipStream_t stream);
@@ -112,7 +113,7 @@ hipError_t launch_fwd_f32(const FwdArgs &a, hipStream_t stream);
 hipError_t launch_commit_bf16(const CommitArgs &a, hipStream_t stream);
 hipError_t launch_commit_f32(const CommitArgs &a, hipStream_t stream);
 hipError_t launch_commit_fm_bf16(const CommitFmArgs &a, hipStream_t stream);
-// S = gate * S + the token-split partial sums in a.workspace ([B*H][nsplit][D][D] fp32), added in split order.
+// S = gate * S + beta * the token-split partial sums in a.workspace ([B*H][nsplit][D][D] fp32), added in split order (no beta: 1).
 hipError_t launch_commit_reduce_bf16(const CommitArgs &a, hipStream_t stream);
 hipError_t launch_commit_gdn_bf16(const GdnArgs &a, hipStream_t stream);
 hipError_t launch_feature_map_bf16(const FmapArgs &a, hipStream_t stream);

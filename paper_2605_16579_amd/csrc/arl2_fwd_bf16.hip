@@ -398,7 +398,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             __builtin_amdgcn_sched_barrier(0);
         });
         float psum = ps0 + ps1;
-        // Rarely (always on the first block) a logit exceeded the running maximum by more than the
+        // Rarely a logit exceeded the running maximum (which starts as the first block's) by more than the
         // threshold: take the true block maximum, raise the running maximum, rescale, redo the block.
         if (__builtin_expect(__any(!(psum < kRowSumLimit)), 0)) {      // wave-uniform; also true for inf and NaN
             // (compile-time loops: the compiler unrolls nothing on a path it is told to be rare)

@@ -224,3 +224,13 @@ def test_overlapping_buffers_are_refused(A):
     assert lib.arl2_feature_map(ctypes.byref(d), k, v, None, None, k + 4096) == 1     # y inside x
     assert lib.arl2_gate_proj(ctypes.byref(d), k, v, k + 64) == 1                      # g inside x
     assert lib.arl2_hybrid_attn_fwd_ex(ctypes.byref(d), k, v, gate, 0x50000000, S, None, 0x50000000 + 2048) == 1   # out inside q_lin
+
+
+def test_fp32_inputs_of_too_many_heads_are_refused(A):
+    """The fp32 kernels span 32 rows of [H][D] with 32-bit byte offsets."""
+    lib = A.load_library()
+    d = A.make_desc(1, 65536, 32, 32, 128, A.ARL2_F32, stream=0)
+    d.workspace, d.workspace_bytes = 0x70000000, 1 << 62
+    assert lib.arl2_hybrid_attn_fwd(ctypes.byref(d), 1 << 40, 1 << 41, 1 << 42, None, None, 1 << 43) == 2
+    assert b"65536" in lib.arl2_last_error()
+    assert lib.arl2_state_commit(ctypes.byref(d), 1 << 40, 1 << 41, 0x30000000, 1 << 42) == 2
