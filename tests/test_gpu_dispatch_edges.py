@@ -190,3 +190,61 @@ def test_fp32_readout_error(lib, oracle, D, scale, state, bound):  # noqa: F811
     e = np.linalg.norm(to_np(gpu_fwd(lib, q, k, v, S, g)) - ref) / np.linalg.norm(ref)
     print(f"fp32 readout D={D} scale {scale}: {e:.3e}")
     assert e <= bound, f"{e:.3e}"
+
+
+# Gates of every granularity and type, the linear branch's own query and the fused map, in each form of the readout: halves
+# (two key groups that finish a share of the features each), whole tiles, whole ones and then halves; both head dimensions.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,H,L", [(1, 2, 130), (8, 17, 150), (17, 16, 200)])
+def test_readout_gates_in_every_tile_split(lib, oracle, B, H, L, D):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"gates_{B}_{H}_{L}_{D}", B=B, H=H, L=L, D=D)
+    q, k, v, _ = W.pass_inputs(w, 0, 0)
+    q_lin = W.normal(7, w, (B, L, H, D), 1)
+    S = W.normal(6, w, (B, H, D, D), 3, io_dtype="f32") * 0.2
+    S64 = to_np(S).astype(np.float64)
+    for shape, dtype in (((B, L), torch.bfloat16), ((B, L, H), torch.bfloat16), ((B, L, H, D), torch.float32), ((B, L, H, D), torch.bfloat16)):
+        g = W.uniform(8, w, shape, 0.0, 1.0, len(shape)).to(dtype)
+        e = rel_err(to_np(gpu_fwd(lib, q, k, v, S, g)), oracle.fwd(to_np(q), to_np(k), to_np(v), S64, to_np(g)))
+        assert e <= TOL_BF16_OUT, f"gate {shape} {dtype}: {e:.3e}"
+    g = W.uniform(8, w, (B, L, H), 0.0, 1.0, 9)
+    out = torch.empty_like(q, device="cuda")
+    lib.arl2_hybrid_attn_fwd_ex(dev(q), dev(k), dev(v), dev(q_lin), dev(S), dev(g), out)
+    torch.cuda.synchronize()
+    e = rel_err(to_np(out), oracle.fwd(to_np(q), to_np(k), to_np(v), S64, to_np(g), q_lin=to_np(q_lin)))
+    assert e <= TOL_BF16_OUT, f"own query: {e:.3e}"
+    Wq, _, _ = W.feature_weights(w)
+    cs, sn = W.rope_tables(w)
+    lib.arl2_hybrid_attn_fwd_fm(dev(q), dev(k), dev(v), dev(q_lin), dev(Wq), dev(cs), dev(sn), dev(S), dev(g), out)
+    torch.cuda.synchronize()
+    mapped = torch.from_numpy(oracle.feature_map(to_np(q_lin), to_np(Wq), to_np(cs), to_np(sn))).to(torch.bfloat16)   # as the kernel rounds it
+    e = rel_err(to_np(out), oracle.fwd(to_np(q), to_np(k), to_np(v), S64, to_np(g), q_lin=to_np(mapped)))
+    assert e <= TOL_BF16_OUT, f"fused map: {e:.3e}"
+
+
+# State commits: the values (plain rule) enter as a truncated bf16 part and the rounded rest, which leaves at most 2^-16 of each
+# product, the corrections (delta rule) as two rounded parts, which leaves 2^-18.  The state that the delta rule multiplies enters as three: with two its error is the same for every token and
+# adds up, to what the oracle shows for a state rounded to two parts.
+@pytest.mark.parametrize("D,L", [(128, 3000), (64, 1500)])
+def test_commits_keep_their_split_precision(lib, oracle, D, L):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"split_precision_{D}_{L}", B=1, H=3, L=L, D=D)
+    k, v, gate = W.clean_inputs(w, 0)
+    S = W.normal(6, w, (1, 3, D, D), 3, io_dtype="f32")
+    S64 = to_np(S).astype(np.float64)
+    S_dev = dev(S).clone()
+    gpu_commit(lib, k, v, gate, S_dev)
+    ref = oracle.commit(to_np(k), to_np(v), to_np(gate), S64)
+    e = np.linalg.norm(to_np(S_dev) - ref) / np.linalg.norm(ref)
+    assert e <= 2.0 ** -16, f"plain: {e:.3e}"
+
+    beta = torch.full((1, 3), 0.5 * D / L)
+    v = 0.1 * v                                           # the products of the keys with the state decide
+    S_dev = dev(S).clone()
+    lib.arl2_state_commit_delta(dev(k), dev(v), dev(gate), dev(beta), S_dev, lib.alloc_workspace(1, 3, L, D, torch.bfloat16))
+    torch.cuda.synchronize()
+    ref = oracle.commit_delta(to_np(k), to_np(v), to_np(gate), to_np(beta), S64)
+    hi = S.to(torch.bfloat16).float()
+    two = (hi + (S - hi).to(torch.bfloat16).float()).double().numpy()
+    two = oracle.commit_delta(to_np(k), to_np(v), 0.0 * to_np(gate), to_np(beta), two) + to_np(gate)[..., None, None] * S64
+    e, e_two = (np.linalg.norm(x - ref) / np.linalg.norm(ref) for x in (to_np(S_dev), two))
+    print(f"delta rule D={D} L={L}: {e:.3e}, with a state of two parts at least {e_two:.3e}")
+    assert e <= min(2.0 ** -18, 0.7 * e_two), f"{e:.3e}, two parts {e_two:.3e}"
