@@ -34,9 +34,9 @@
 //
 // What bounds it: the matrix cores and, on real data, the power they draw (a launch that fills the chip holds the
 // clock at 1.73 GHz).  Measured for one pass with state and gate, 12 heads x 128:
-//   4680 tokens (228 tiles of 256 rows)   128 us; 1560 tokens (156 half tiles) 26 us, 43 us with 84 whole tiles;
-//   2 x 3 heads, 328 tokens: 11 us, 17 us before (query rows loaded fragment by fragment, the tiles of the prologue one
-//   after the other, the first block's exponentials computed twice, whole tiles).
+//   4680 tokens (228 tiles of 256 rows)   126 us; 1560 tokens (156 half tiles) 26.5 us, 38 us with 84 whole tiles;
+//   2 x 3 heads, 328 tokens (18 half tiles) 11.9 us, 15.6 us with 12 whole ones (17 us with query rows loaded fragment by
+//   fragment, the tiles of the prologue one after the other and the first block's exponentials computed twice).
 #include "arl2_device.h"
 
 #include <type_traits>
@@ -969,8 +969,9 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
     g.n_tiles = g.n_whole = (int)(heads * q256);
     // more workgroups than CUs, a ragged last query tile per head, and whole heads per XCD
     g.ragged_last = g.n_tiles > kNumCu && a.Lq % 256 != 0 && q256 > 1 && heads % kNumXcd == 0;
-    // Half tiles while they run as one round: 1024 tokens x 16 heads x 128 21.5 us against 28.6 us for whole tiles, x 32
-    // heads (256 half tiles) 26.6 against 29.9 us; just beyond, x 48 heads, 43.9 against 34.9 us.
+    // Half tiles while they run as one round: 1024 tokens x 16 heads x 128 19.6 us against 27.1 us for whole tiles, x 32
+    // heads (256 half tiles) 23.4 against 28.7 us; with the fused map, whose matrix half as many rows share, 24.6 against 31.8
+    // and 28.4 against 33.7 us; just beyond, x 48 heads, 43.9 against 34.9 us.
     if (heads * q128 <= kNumCu && halves_pay<D>(a.Lq, a.Lkv, heads)) {
         g.n_qtiles = (int)q128;
         g.n_tiles = (int)(heads * q128);
@@ -978,9 +979,10 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
         return launch_fwd<D, kHalves>(a, g, scale_log2, stream);
     }
     // The tail of a launch of several rounds: when at most half of the CUs would have a tile in it, these tiles are
-    // halved.  A half tile takes 0.57 of the time of a whole one, so that 2 x 1000 tokens x 136 heads (2.08
-    // rounds) take 94 us instead of 102 us, 2048 tokens x 66 heads x 64 wide (2.06 rounds) 97 instead of 110 us;
-    // nothing changes where more than half of the CUs have work in the last round.
+    // halved.  A half tile takes 0.57 of the time of a whole one, so that 2048 tokens x 66 heads (2.06 rounds) take 156
+    // instead of 172 us, x 64 wide 94 instead of 106 us, 1000 tokens x 272 heads (4.25 rounds) 174 instead of 180 us, and with
+    // the fused map 172, 102 and 200 us instead of 186, 114 and 206 us; nothing changes where more than half of the CUs have
+    // work in the last round.
     const int rest = g.n_tiles % kNumCu;
     const int tail_rows = g.ragged_last || q256 == 1 ? (a.Lq - 1) % 256 + 1 : 256;
     if (g.n_tiles > kNumCu && rest > 0 && 2 * rest <= kNumCu && halves_pay<D>(tail_rows, a.Lkv, rest)) {
