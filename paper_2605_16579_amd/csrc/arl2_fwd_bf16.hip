@@ -16,8 +16,10 @@
 // (ds_read_b64_tr_b16), four keys per read.
 //
 // The unit of the schedule is a slot, the softmax of one 32-key block beside the first GEMM of the next block and the
-// second GEMM of the previous one (see `slot`).  K/V tiles travel HBM/L2 -> registers (buffer loads, zero beyond the
-// last key) -> an LDS ring with one workgroup barrier per tile.  The softmax is optimistic: the running maximum
+// second GEMM of the previous one (see `slot`).  K/V tiles travel (buffer loads, zero beyond the last key) into an LDS
+// ring with one workgroup barrier per tile: at D = 128 in whole tiles straight, requested two barriers ahead, else through
+// registers.  12 heads x 128, 14400 keys: 1.51 us per 64-key tile straight, 1.61 us through registers (on zeros, where power
+// does not bound it, 1.09 and 1.15 us).  The softmax is optimistic: the running maximum
 // starts as the first block's, probabilities are taken relative to it as it stands, and only when a lane's share of
 // the row sum shows that a logit exceeded it by more than ~2^7 is the block maximum computed, the running maximum
 // raised, the accumulators rescaled and the block redone.  This removes the per-block maximum reduction and the
@@ -34,7 +36,7 @@
 //
 // What bounds it: the matrix cores and, on real data, the power they draw (a launch that fills the chip holds the
 // clock at 1.73 GHz).  Measured for one pass with state and gate, 12 heads x 128:
-//   4680 tokens (228 tiles of 256 rows)   126 us; 1560 tokens (156 half tiles) 26.5 us, 38 us with 84 whole tiles;
+//   4680 tokens (228 tiles of 256 rows)   123 us; 1560 tokens (156 half tiles) 26.5 us, 38 us with 84 whole tiles;
 //   2 x 3 heads, 328 tokens (18 half tiles) 11.9 us, 15.6 us with 12 whole ones (17 us with query rows loaded fragment by
 //   fragment, the tiles of the prologue one after the other and the first block's exponentials computed twice).
 #include "arl2_device.h"
@@ -58,8 +60,11 @@ struct FwdCfg {
     static constexpr int CPR = D / 8;            // 16-byte chunks per row
     static constexpr int KROW = 2 * D + 16;      // LDS bytes per K row (padded: conflict-free b128 reads)
     static constexpr int VROW = 2 * D + 64;      // LDS bytes per V row (padded: conflict-free transposing reads)
-    static constexpr int K_BYTES = BN * KROW;
-    static constexpr int V_BYTES = BN * VROW;
+    // Direct copy: tiles go from memory into LDS without passing through registers, 1 KB (four rows) per instruction.
+    static constexpr bool DIRECT = D == 128 && KG == 1;
+    static constexpr int GROUP = 1024 + 16;      // LDS bytes from one group of four rows to the next
+    static constexpr int K_BYTES = DIRECT ? BN / 4 * GROUP : BN * KROW;
+    static constexpr int V_BYTES = DIRECT ? BN / 4 * GROUP : BN * VROW;
     static constexpr int STAGE = K_BYTES + V_BYTES;   // one K/V tile
     static constexpr int KV_BYTES = (KG == 1 ? NSTAGE : 2) * STAGE;
     static constexpr int DBW = DB / KG;          // 32-feature blocks of the output that a wavefront finishes
@@ -74,7 +79,10 @@ struct FwdCfg {
     static constexpr int FM_BYTES = WH_BYTES + RG * TAB_BYTES;
     static constexpr int WCH = ((D / 2) * CPR + NT - 1) / NT;     // 16-byte chunks of the Wq half per thread
     static constexpr int TCH = 32 * (D / 8) / 64;                 // 16-byte chunks of one table tile per lane
-    static constexpr int SMEM0 = (KV_BYTES > ST_BYTES ? (KV_BYTES > OUT_BYTES ? KV_BYTES : OUT_BYTES)
+    // one key group: the query rows pass through ring stages 2 and on, and what they need beyond them
+    static constexpr int Q_END = KG == 1 ? 2 * STAGE + BM * KROW : 0;
+    static constexpr int RING_END = Q_END > KV_BYTES ? Q_END : KV_BYTES;
+    static constexpr int SMEM0 = (RING_END > ST_BYTES ? (RING_END > OUT_BYTES ? RING_END : OUT_BYTES)
                                                       : (ST_BYTES > OUT_BYTES ? ST_BYTES : OUT_BYTES));
     static constexpr int SMEM1 = SMEM0 > FM_BYTES ? SMEM0 : FM_BYTES;
     // with two key groups the ring is half as large and the state has room of its own behind it
@@ -107,6 +115,22 @@ struct FwdCfg {
 // relative to the running maximum) reaches this value, i.e. some logit exceeded it by more than ~2^7.
 constexpr float kRowSumLimit = 4096.0f;
 
+
+// Two groups of four rows straight into LDS (16 bytes per lane, lane l to lds + 16 l; the second OFF2 bytes further).  The
+// instruction's offset moves the source address as well, so `off2` is less by as much.  M0 carries the LDS address; nothing
+// else in these kernels reads it.  There is no output register: the caller waits on vmcnt before the bytes are read.
+template <int OFF2>
+__device__ __forceinline__ void load_pair_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t off2, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\tbuffer_load_dwordx4 %2, %3, 0 offen offset:%4 lds"
+                 ::"s"(lds), "v"(off), "v"(off2), "s"(rsrc), "n"(OFF2) : "memory");
+}
+// Workgroup barrier after all but the last N of this wavefront's loads have arrived, and all of its LDS reads.
+template <int N>
+__device__ __forceinline__ void direct_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
 
 // Query tile qt (of 256 / KG rows) of (stream, head) bh, by one workgroup.
 template <int D, int KG, bool FUSED_MAP>
@@ -228,6 +252,34 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         if constexpr (p == 2 * C::KCH - 1) g_off += BN * tok_bytes;
     };
 
+    // Direct copy.  Row r, 16-byte chunk x of a tile lie at (r / 4) GROUP + 256 (r % 4) + 16 (x ^ 4 (r % 4)): the 16 bytes
+    // between groups and the exchanged chunks keep both kinds of fragment read free of bank conflicts, which a copy of whole
+    // kilobytes cannot do by padding rows.  A wavefront moves two groups of K and two of V; a tile is requested two barrier
+    // intervals before it is read.
+    const uint32_t lds0 = lds_address(smem);
+    uint32_t dsrc[2] = {};            // source offsets of the lane's two chunks, from 64 bytes below the tile
+    int kdx[4] = {}, vdx[4] = {};     // fragment offsets: 64-byte column x of K row c, of V row (lane / 4) % 4 + 4 hh
+    if constexpr (C::DIRECT) {
+        static_assert(!C::DIRECT || BN / 4 == 2 * NT / 64, "two groups of K and of V per wavefront");
+        const int vr = (lane >> 2) & 3;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            kdx[x] = (c >> 2) * C::GROUP + 256 * (c & 3) + 64 * (x ^ (c & 3)) + 16 * hh;
+            vdx[x] = hh * C::GROUP + 256 * vr + 64 * (x ^ vr) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+        }
+        dsrc[0] = (uint32_t)(8 * wave + (lane >> 4)) * tok_bytes + 16 * ((lane & 15) ^ (4 * (lane >> 4))) + 64;
+        dsrc[1] = dsrc[0] + 4 * tok_bytes - C::GROUP;        // (4 tok_bytes >= 1024, hence the 64 bytes)
+    }
+    // K (PART 0) or V (PART 1) of a tile; past the last key nothing is read and zeros are stored.
+    auto direct_part = [&](int tile, auto part_) {
+        constexpr int PART = decltype(part_)::value;
+        const int left = (int)kv_range - tile * (int)(BN * tok_bytes);
+        const bf16_t *base = (PART ? vgl : kgl) + (ptrdiff_t)tile * BN * H * D - 32;
+        load_pair_to_lds<C::GROUP>(make_rsrc(base, left > 0 ? (uint32_t)left + 64 : 0), dsrc[0], dsrc[1],
+                                   lds0 + (tile & (NSTAGE - 1)) * C::STAGE + PART * C::K_BYTES + 2 * wave * C::GROUP);
+    };
+    auto direct_tile = [&](int tile) { static_for<0, 2>([&](auto part_) { direct_part(tile, part_); }); };
+
     // lane roles inside a 32-key block
     const int k_frag_off = c * C::KROW + 16 * hh;                                   // + 32*t
     const int v_frag_off = (((lane & 15) >> 2) + 4 * hh) * C::VROW + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
@@ -249,25 +301,28 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     // Byte offsets in the ring of the K rows / V rows of this wavefront's 32-key block `blk`: half blk % 2 of tile
     // blk / 2, or with two key groups half kg of tile blk.
     auto k_block = [&](int blk) -> int {
-        if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * 32 * C::KROW;
+        if constexpr (C::DIRECT) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * 8 * C::GROUP;
+        else if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * 32 * C::KROW;
         else return (blk & 1) * C::STAGE + kg * 32 * C::KROW;
     };
     auto v_block = [&](int blk) -> int {
-        if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * 32 * C::VROW;
+        if constexpr (C::DIRECT) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * 8 * C::GROUP;
+        else if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * 32 * C::VROW;
         else return (blk & 1) * C::STAGE + C::K_BYTES + kg * 32 * C::VROW;
     };
     auto first_key = [&](int blk) -> int { return KG == 1 ? 32 * blk : BN * blk + 32 * kg; };
     // A-operand fragments: k-step n of S^T = K Q^T (a K row piece), and MFMA n of O^T += V^T P^T
     // (16-key step n / DB, row block n % DB: a transposed V piece).
     auto k_frag = [&](const unsigned char *kp, auto n_) -> bf16x8 {
-        return *(const bf16x8 *)(kp + 32 * decltype(n_)::value);
+        constexpr int n = decltype(n_)::value;
+        if constexpr (C::DIRECT) return *(const bf16x8 *)(kp + kdx[n / 2] + 32 * (n & 1));
+        else return *(const bf16x8 *)(kp + k_frag_off + 32 * n);
     };
     auto v_frag = [&](const unsigned char *vp, auto n_) -> bf16x8 {
         constexpr int n = decltype(n_)::value;
-        const unsigned char *p = vp + 16 * (n / C::DB) * C::VROW + 64 * (n % C::DB);
-        const bf16x4 lo = lds_read_tr(p);                    // keys 16u + 4hh + 0..3
-        const bf16x4 hi = lds_read_tr(p + 8 * C::VROW);      // keys 16u + 8 + 4hh + 0..3
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        // keys 16u + 4hh + 0..3 and 16u + 8 + 4hh + 0..3
+        if constexpr (C::DIRECT) return lds_read_tr_pair(vp + vdx[n % C::DB] + 4 * (n / C::DB) * C::GROUP, 2 * C::GROUP);
+        else return lds_read_tr_pair(vp + v_frag_off + 16 * (n / C::DB) * C::VROW + 64 * (n % C::DB), 8 * C::VROW);
     };
     // exp2 of the 16 logits per lane of one key block relative to the running maximum -> its two P^T
     // fragments; returns this lane's share of the row sum.  (Only on the rare path that raises the maximum.)
@@ -299,7 +354,8 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     // every other step, so that the copy runs under the MFMAs instead of in a burst before the barrier; 3 (several key
     // groups) the whole copy of an interval and its barrier, as soon as the slot has requested its last fragment: the
     // fragments requested after that are the next slot's, from the tiles that the barrier publishes; 4 the same for the last
-    // tile, whose V is all that is left to store (into stage `cstage`).
+    // tile, whose V is all that is left to store (into stage `cstage`).  Direct copy: 5 the barrier, as soon as the slot has
+    // requested its last fragment (those requested after it are the next slot's); 6 the loads of tile `cstage`.
     auto slot = [&](auto par_, auto has_s_, auto has_pv_, auto next_s_, auto masked_, int j, auto copy_, int cstage) {
         constexpr int PAR = decltype(par_)::value;
         constexpr int COPY = decltype(copy_)::value;
@@ -308,10 +364,10 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         constexpr int SL = HAS_S ? C::S_LEN : 0, NS = SL + (HAS_PV ? C::PV_LEN : 0);
         constexpr int LPS = 16 / NS;                 // logits per step
         static_assert(NS % C::RING == 0 && 16 % NS == 0, "slot length");
-        const unsigned char *kp = smem + k_block(j + 1) + k_frag_off;
-        const unsigned char *vp = smem + v_block(j - 1) + v_frag_off;
-        const unsigned char *np = smem + k_block(j + 2) + k_frag_off;      // next slot: S(j+2) (if any) and PV(j)
-        const unsigned char *nvp = smem + v_block(j) + v_frag_off;
+        const unsigned char *kp = smem + k_block(j + 1);
+        const unsigned char *vp = smem + v_block(j - 1);
+        const unsigned char *np = smem + k_block(j + 2);      // next slot: S(j+2) (if any) and PV(j)
+        const unsigned char *nvp = smem + v_block(j);
         const float mneg = -m_run;
         float x[16], ps0 = 0.f, ps1 = 0.f;
         auto op_scale = [&](auto v_) {               // logit v: scaled, relative to the running maximum
@@ -374,7 +430,9 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             if constexpr (COPY == 1 && (n & 1) == 1 && n / 2 < C::KCH) load_tile_part(std::integral_constant<int, n / 2>{});
             if constexpr (COPY == 2 && n >= kStoreStep0 && n < kStoreStep0 + 4 * C::KCH && ((n - kStoreStep0) & 1) == 0)
                 store_tile_part(cstage, std::integral_constant<int, (n - kStoreStep0) / 2>{});
-            if constexpr (COPY >= 3) {
+            if constexpr (COPY == 5 && n == NS - C::PF - 1) direct_barrier<4>();
+            if constexpr (COPY == 6 && (n == 1 || n == 5)) direct_part(cstage, std::integral_constant<int, n / 4>{});
+            if constexpr (COPY == 3 || COPY == 4) {
                 static_for<0, 2 * C::KCH>([&](auto p_) {
                     constexpr int p = decltype(p_)::value;
                     if constexpr (p * (NS - C::PF) / (2 * C::KCH) == n) {
@@ -427,11 +485,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     const std::integral_constant<int, 2> copy2{};
     const std::integral_constant<int, 3> copy3{};
     const std::integral_constant<int, 4> copy4{};
+    const std::integral_constant<int, 5> copy5{};
+    const std::integral_constant<int, 6> copy6{};
 
     // S(0), plain: nothing to overlap it with
     auto first_product = [&]() {
-        const unsigned char *kp = smem + k_block(0) + k_frag_off;
-        const unsigned char *np = smem + k_block(1) + k_frag_off;
+        const unsigned char *kp = smem + k_block(0);
+        const unsigned char *np = smem + k_block(1);
         static_for<0, C::PF>([&](auto m_) { fr[decltype(m_)::value] = k_frag(kp, m_); });
         static_for<0, C::S_LEN>([&](auto n_) {
             constexpr int n = decltype(n_)::value;
@@ -461,7 +521,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     // second GEMM of the last key block `blk` of parity P (its first fragments are in flight)
     auto last_product = [&](auto p_, int blk) {
         constexpr int P = decltype(p_)::value;
-        const unsigned char *vp = smem + v_block(blk) + v_frag_off;
+        const unsigned char *vp = smem + v_block(blk);
         static_for<0, C::PV_LEN>([&](auto n_) {
             constexpr int n = decltype(n_)::value;
             constexpr int m = n + C::PF;
@@ -514,28 +574,39 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         // ---- prologue: tiles 0 and 1 into the ring, all their loads and those of the query rows in flight together
         {
             u32x4 k1[C::KCH], v1[C::KCH], x[QCH];
-            load_k(0, kst);
-            if (q0 < Lq) fetch_rows(x);
-            load_v(0, vst);
-            load_k(1, k1);
-            load_v(1, v1);
-            store_k(0, kst);
+            if constexpr (C::DIRECT) {
+                if (q0 < Lq) fetch_rows(x);
+                direct_tile(0);
+                direct_tile(1);
+            } else {
+                load_k(0, kst);
+                if (q0 < Lq) fetch_rows(x);
+                load_v(0, vst);
+                load_k(1, k1);
+                load_v(1, v1);
+                store_k(0, kst);
+            }
             unsigned char *mine = smem + 2 * C::STAGE + wave * 32 * C::KROW;     // in stages that tile 2 and on will use
-            static_assert(KG > 1 || 8 * 32 * C::KROW <= 2 * C::STAGE, "the query rows pass through two ring stages");
             if (q0 < Lq) put_rows(mine, x);
-            store_v(0, vst);
-            store_k(1, k1);
-            store_v(1, v1);
+            if constexpr (!C::DIRECT) {
+                store_v(0, vst);
+                store_k(1, k1);
+                store_v(1, v1);
+            }
             if (q0 < Lq) {              // (wavefronts without rows keep off the LDS: 128 rows over 300 keys 8.7 -> 8.2 us)
                 get_rows(mine);
                 square_rows();
             }
         }
-        __syncthreads();
+        if constexpr (C::DIRECT) direct_barrier<0>();
+        else __syncthreads();
         clear_output();
 
-        // Barrier interval i covers the slots of key blocks 2i and 2i+1: they read K of tiles i and i+1 and V of
-        // tiles i-1 and i.  Tile i+2 is fetched into registers at its start and written at its end to the ring
+        // Interval i covers the slots of key blocks 2i and 2i+1: they read K of tiles i and i+1 and V of tiles i-1 and i.
+        // Direct copy: the barrier of interval i stands near the end of its first slot.  Behind it tile i-1 is no longer read
+        // and tile i+3 is requested into its stage; tile i+1, requested two barriers earlier, has arrived when all loads but
+        // the last tile's have.
+        // Else the barrier closes the interval: tile i+2 is fetched into registers at its start and written at its end to the ring
         // stage of tile i-2 (four stages); the barrier that closes the interval publishes it.
         auto close_interval = [&](int i) {
             store_k((i + 2) & (NSTAGE - 1), kst);
@@ -547,9 +618,11 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             load_v(tile, vst);
         };
         g_off += 3 * BN * tok_bytes;
+        if constexpr (C::DIRECT) direct_tile(2);
         if (q0 < Lq) {
             first_product();
-            load_tile(2);
+            if constexpr (C::DIRECT) direct_tile(3);
+            else load_tile(2);
             first_maximum();
             if (ntiles == 1) {
                 slot(par0, yes, no, no, yes, 0, copy0, 0);
@@ -558,9 +631,14 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
                 slot(par0, yes, no, yes, no, 0, copy0, 0);
                 slot(par1, yes, yes, yes, no, 1, copy0, 0);
             }
-            close_interval(0);
+            if constexpr (!C::DIRECT) close_interval(0);
 #pragma unroll 1
             for (int i = 1; i < ntiles - 1; ++i) {
+                if constexpr (C::DIRECT) {
+                    slot(par0, yes, yes, yes, no, 2 * i, copy5, 0);
+                    slot(par1, yes, yes, yes, no, 2 * i + 1, copy6, i + 3);
+                    continue;
+                }
                 slot(par0, yes, yes, yes, no, 2 * i, copy1, 0);
                 slot(par1, yes, yes, yes, no, 2 * i + 1, copy2, (i + 2) & (NSTAGE - 1));
                 // the writes are complete once at most the LDS reads issued after the last of them are still
@@ -577,15 +655,26 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             // A wavefront whose 32 rows all lie past the last query (the ragged last workgroup of a head) only
             // helps to move the tiles: the same loads, stores and barriers, no arithmetic.  Its rows are never
             // stored.
-            load_tile(2);
-            close_interval(0);
+            if constexpr (C::DIRECT) {
+                direct_tile(3);
 #pragma unroll 1
-            for (int i = 1; i < ntiles - 1; ++i) {
-                load_tile(i + 2);
-                close_interval(i);
+                for (int i = 1; i < ntiles - 1; ++i) {
+                    direct_barrier<4>();
+                    direct_tile(i + 3);
+                }
+            } else {
+                load_tile(2);
+                close_interval(0);
+#pragma unroll 1
+                for (int i = 1; i < ntiles - 1; ++i) {
+                    load_tile(i + 2);
+                    close_interval(i);
+                }
             }
             l_run = 1.0f;
         }
+        // the loads of the tiles past the last one write zeros into the ring: they end before it is used for anything else
+        if constexpr (C::DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     } else {
         // ---- several key groups: a wavefront works on one 32-key block of every tile, one slot per tile.  Slot j reads
         // K(j + 1) and V(j - 1); K(j + 2) and V(j) are written during it, so two ring stages are enough.
@@ -625,7 +714,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
                 ++j;
             }
             // the last slot has no first product: its fragments start with V(nt - 2)
-            const unsigned char *vp = smem + v_block(j - 1) + v_frag_off;
+            const unsigned char *vp = smem + v_block(j - 1);
             static_for<0, C::PF>([&](auto m_) { fr[decltype(m_)::value] = v_frag(vp, m_); });
             // An ending for each parity, or one, to whose registers the even parity's logits and probabilities are moved: with
             // two the largest form of this function does not fit the registers.

@@ -93,6 +93,20 @@ def test_readout_tile_splits(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
     assert rel_err(to_np(out), to_np(ref)) <= 2.0 ** -7
 
 
+# Whole tiles: the ring of four key tiles (fewer tiles than stages, one more, a ragged last tile of one key or one short of
+# full), with rows of one head (the smallest row distance) and of several, and wavefronts without query rows.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,H,Lq,Lkv", [
+    (1, 1, 100, 1), (1, 1, 100, 63), (1, 1, 33, 64), (2, 1, 100, 65), (1, 1, 100, 128), (1, 2, 100, 129), (1, 1, 128, 193), (1, 3, 70, 256),
+    (1, 1, 100, 257), (1, 1, 1, 320), (2, 2, 100, 383), (65, 4, 200, 321)])
+def test_readout_key_ring(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"ring_{B}_{H}_{Lq}_{Lkv}_{D}", B=B, H=H, L=Lq, D=D)
+    q, _, _, _ = W.pass_inputs(w, 0, 0)
+    k, v = (W.normal(5, w, (B, Lkv, H, D), tag) for tag in (1, 2))
+    e = rel_err(to_np(gpu_fwd(lib, q, k, v, None, None)), oracle.fwd(to_np(q), to_np(k), to_np(v)))
+    assert e <= TOL_BF16_OUT, f"{e:.3e}"
+
+
 # Delta rule: tiles of 64 (D = 128) or 128 (D = 64) tokens shared by two or four token groups, one split per CU as far as
 # heads, tiles and the workspace allow (one tile, a ragged tile of one group, several rounds of the load ring, more heads
 # than CUs).
