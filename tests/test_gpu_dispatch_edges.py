@@ -13,12 +13,14 @@ from test_gpu_parity import dev, gpu_commit, gpu_fwd, lib  # noqa: F401  (lib is
 pytestmark = pytest.mark.gpu
 
 
-# fp32: 32-row workgroups whose four wavefronts take every fourth block of 32 keys (fewer than four blocks, a ragged
-# last one, more than one round), groups of 16 tokens over eight wavefronts in the commit, 32- and 64-wide state blocks
+# fp32: workgroups of 32 query rows, or of 16 for what is left beyond a multiple of the CUs (all tiles, some, none; a last tile
+# with rows for one of its halves or for both), whose four wavefronts take every fourth block of 32 keys (fewer than four
+# blocks, a ragged last one, more than one round), groups of 16 tokens over eight wavefronts in the commit, 32- and 64-wide state blocks
 # (64-wide from 64 heads at D = 128, 256 at D = 64).
 @pytest.mark.parametrize("B,H,Lq,Lkv,D", [
     (1, 2, 1, 1, 64), (1, 2, 31, 31, 128), (2, 1, 33, 33, 64), (1, 3, 64, 127, 128), (1, 1, 129, 129, 128), (1, 2, 40, 161, 64),
-    (2, 32, 17, 17, 128), (4, 64, 33, 33, 64), (1, 2, 300, 300, 128)])
+    (2, 32, 17, 17, 128), (4, 64, 33, 33, 64), (1, 2, 300, 300, 128),
+    (1, 43, 200, 200, 64), (1, 43, 208, 208, 128), (3, 48, 49, 49, 128), (4, 32, 64, 70, 128), (2, 43, 64, 70, 64)])
 def test_fp32_tiles_and_key_groups(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
     w = dataclasses.replace(W.WORKLOADS["tiny"], name=f"f32_{B}_{H}_{Lq}_{Lkv}_{D}", B=B, H=H, L=Lq, D=D, qkv_scale=1.0)
     q, _, _, g = W.pass_inputs(w, 0, 0)
