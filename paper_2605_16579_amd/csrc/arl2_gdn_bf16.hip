@@ -705,6 +705,9 @@ __global__ __launch_bounds__(256) void gdn_walk_kernel(GdnArgs a, const unsigned
 //     against S hi and S lo, one accumulator per half; the K operand is gathered from the record's 32 x 32 x 16
 //     fragments, 16 bytes per lane), and forms R for those tokens;
 //   * S <- gam S + Z^T R for its own 32 rows: Z^T hi/lo against R hi/lo, three terms.
+// Where a launch is one short chain per CU (GROUPED), S hi and S lo have accumulators of their own, half as long a chain of
+// products.  Measured with the other kernels of the commit, 12 heads, 4680 tokens: 57.7 us before the exchange without bank
+// conflicts and the shorter chains, 56.3 with the one, 55.3 with both; 96 heads (not grouped) 301 and 294 us.
 // Two LDS-only barriers per step (S published, R published).  K and Z^T fragments have two register sets
 // (refilled two steps ahead), V^T and the per-token scalars one (refilled one step ahead).
 // Run decoding, identity columns and the composite-map record are those of the four-wavefront kernel above.
@@ -713,7 +716,7 @@ __global__ __launch_bounds__(512) void gdn_walk8_kernel(GdnArgs a, const unsigne
 {
     constexpr int D = 128;
     constexpr int KS = D / 16, NB = D / 32, NSL = D / 64;
-    constexpr int SROW = 2 * D + 16, RROW = 2 * CT + 16;
+    constexpr int SROW = 2 * D, RROW = 2 * CT + 16;
     constexpr int S_BYTES = 64 * SROW, R_BYTES = 64 * RROW;
     constexpr int TROW = 2 * 64 + 16;                    // row of the [D][64] bf16 tile that transposes M_g
     static_assert(2 * D * TROW <= 2 * S_BYTES + 2 * R_BYTES, "the transposing tiles reuse the exchange buffers");
@@ -747,6 +750,9 @@ __global__ __launch_bounds__(512) void gdn_walk8_kernel(GdnArgs a, const unsigne
     const int col = 32 * cb + c32, gcol = 64 * slice + col;          // column within the slice / within the state
     float *Sg = a.S + (size_t)bh * D * D + gcol;
 
+    // S is exchanged as [column][16-byte chunk]: chunk x of column n lies at x ^ n % 16, on which neither the 16-column
+    // fragment reads nor the writes have bank conflicts (padded rows had: 43 % of the kernel's LDS cycles)
+    const int s_wr = col * SROW + 16 * ((4 * rbF) ^ (col & 15)) + 8 * hh, s_rd = (32 * cb + c16) * SROW + 16 * (g ^ c16);
     f32x16 s_acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -809,23 +815,27 @@ __global__ __launch_bounds__(512) void gdn_walk8_kernel(GdnArgs a, const unsigne
                 h4[e] = to_bf16(x);
                 l4[e] = to_bf16(x - (float)h4[e]);
             }
-            const int off = col * SROW + 2 * (32 * rbF + 8 * q + 4 * hh);
+            const int off = s_wr ^ (16 * q);
             *(bf16x4 *)(Shi + off) = h4;
             *(bf16x4 *)(Slo + off) = l4;
         }
         lds_barrier();                                   // (not __syncthreads: the operand loads stay in flight)
         // ---- T = K S for this member's 16 tokens x 32 columns, all 128 features: 16 x 16 x 32 MFMAs, two column
         // halves; lane (column c16, g) ends up with tokens 4 g + 0..3 of both halves
-        f32x4 tq[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+        f32x4 tq[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}}, tlo[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
         static_for<0, 4>([&](auto s_) {
             constexpr int sx = decltype(s_)::value;
 #pragma unroll
             for (int ch = 0; ch < 2; ++ch) {
-                const int o = (32 * cb + 16 * ch + c16) * SROW + 64 * sx + 16 * g;
+                const int o = (s_rd ^ (64 * sx)) + 16 * ch * SROW;
+                f32x4 &tl = GROUPED ? tlo[ch] : tq[ch];
                 tq[ch] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[bi][sx], *(const bf16x8 *)(Shi + o), tq[ch], 0, 0, 0);
-                tq[ch] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[bi][sx], *(const bf16x8 *)(Slo + o), tq[ch], 0, 0, 0);
+                tl = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[bi][sx], *(const bf16x8 *)(Slo + o), tl, 0, 0, 0);
             }
         });
+        if constexpr (GROUPED)
+#pragma unroll
+            for (int ch = 0; ch < 2; ++ch) tq[ch] += tlo[ch];
         fetch_k(blk + 2, b_);
         // ---- R = beta V + (-beta gamma- r) T for tokens 32 rbT + 16 m + 4 g + e
 #pragma unroll
