@@ -1,4 +1,5 @@
-"""ctypes binding of the C ABI in ``include/arl2.h``: argument marshalling only.
+"""Binding of the C ABI in ``include/arl2.h``: argument marshalling only, of plain calls in ``csrc/arl2_host.cpp``, of the
+others and of what is to be refused through ctypes.
 
 Every step of the hybrid attention path runs in the HIP kernels of ``libarl2_hip.so``;
 torch is used for device memory and streams.  There is no fallback: if the library is
@@ -7,6 +8,7 @@ missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -14,6 +16,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libarl2_hip.so")
+HOST_PATH = os.path.join(_PKG, "_arl2_host.so")
 
 ARL2_OK, ARL2_ERR_INVALID_ARG, ARL2_ERR_UNSUPPORTED, ARL2_ERR_WORKSPACE, ARL2_ERR_DEVICE = range(5)
 ARL2_F32, ARL2_BF16 = 0, 1
@@ -40,15 +43,18 @@ class Arl2Error(RuntimeError):
 
 
 _lib = None
+_host_call = None     # _arl2_host.call
+_addr = {}            # entry point -> its address in _lib
 
 
 def load_library() -> ctypes.CDLL:
     """Loads the built library (build it first with ``python -m paper_2605_16579_amd.build``)."""
-    global _lib
+    global _lib, _host_call
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise FileNotFoundError(
-                f"{LIB_PATH} is missing: run `python -m paper_2605_16579_amd.build` (there is no fallback path)")
+        for path in (LIB_PATH, HOST_PATH):
+            if not os.path.exists(path):
+                raise FileNotFoundError(
+                    f"{path} is missing: run `python -m paper_2605_16579_amd.build` (there is no fallback path)")
         lib = ctypes.CDLL(LIB_PATH)
         vp = ctypes.c_void_p
         dp = ctypes.POINTER(arl2_desc)
@@ -84,8 +90,24 @@ def load_library() -> ctypes.CDLL:
         lib.arl2_last_error.restype = ctypes.c_char_p
         lib.arl2_version.argtypes = []
         lib.arl2_version.restype = ctypes.c_int
-        _lib = lib
+        spec = importlib.util.spec_from_file_location("_arl2_host", HOST_PATH)
+        host = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(host)
+        _addr.update({name: ctypes.cast(getattr(lib, name), vp).value for name in EXPORTS})
+        _lib, _host_call = lib, host.call
     return _lib
+
+
+def _plain_call(name: str, kinds: bytes, sm_scale, l2_eps, stream, workspace, *tensors) -> bool:
+    """Makes the call if its tensors are as a plain call has them (``kinds`` says what: csrc/arl2_host.cpp), else does nothing
+    and returns False: the caller's own checks then say what is wrong, or marshal what only they can."""
+    if _lib is None:
+        load_library()
+    st = _host_call(_addr[name], kinds, sm_scale, l2_eps, _current_stream() if stream is None else stream, workspace, *tensors)
+    if st is None:
+        return False
+    _check(st)
+    return True
 
 
 def _check(status: int) -> None:
@@ -102,8 +124,7 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise TypeError(f"unsupported dtype {t.dtype}: use float32 or bfloat16")
 
 
-# A small call is bound by its host side: building the descriptor through torch.cuda.current_stream() and field by field
-# cost 3.8 of the 10.8 us that one call took to issue (3.5 of them inside the library and the runtime's launch).
+# A small call is bound by its host side: torch.cuda.current_stream() cost several times as much as the handle alone.
 def _current_stream() -> int:
     """Handle of the current stream of the current device (0 without a GPU)."""
     if torch.cuda.is_initialized():
@@ -155,6 +176,8 @@ def arl2_hybrid_attn_fwd(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
                          S: Optional[torch.Tensor], g: Optional[torch.Tensor], out: torch.Tensor,
                          *, sm_scale: float = 0.0, l2_eps: float = 0.0, stream: Optional[int] = None) -> None:
     """Read-only denoising pass, enqueued on the current (or given) stream; writes ``out``."""
+    if _plain_call("arl2_hybrid_attn_fwd", b"qkkSgq", sm_scale, l2_eps, stream, None, q, k, v, S, g, out):
+        return
     if q.dim() != 4 or k.dim() != 4:
         raise ValueError("q and k must be [B, L, H, D]")
     B, Lq, H, D = q.shape
@@ -175,6 +198,8 @@ def arl2_hybrid_attn_fwd_ex(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, q
                             S: Optional[torch.Tensor], g: Optional[torch.Tensor], out: torch.Tensor,
                             *, sm_scale: float = 0.0, l2_eps: float = 0.0, stream: Optional[int] = None) -> None:
     """The readout pass with the linear branch's own query ``q_lin`` (None: ``q``)."""
+    if _plain_call("arl2_hybrid_attn_fwd_ex", b"qkkqSgq", sm_scale, l2_eps, stream, None, q, k, v, q_lin, S, g, out):
+        return
     if q.dim() != 4 or k.dim() != 4:
         raise ValueError("q and k must be [B, L, H, D]")
     B, Lq, H, D = q.shape
@@ -197,6 +222,9 @@ def arl2_hybrid_attn_fwd_fm(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, x
                             S: torch.Tensor, g: Optional[torch.Tensor], out: torch.Tensor,
                             *, sm_scale: float = 0.0, l2_eps: float = 0.0, stream: Optional[int] = None) -> None:
     """The readout pass with the linear branch's query feature map RoPE(Wq[h] xq) computed inside the kernel."""
+    if _plain_call("arl2_hybrid_attn_fwd_fm", b"qkkqWrrSgq", sm_scale, l2_eps, stream, None,
+                   q, k, v, xq, Wq, rope_cos, rope_sin, S, g, out):
+        return
     if q.dim() != 4 or k.dim() != 4:
         raise ValueError("q and k must be [B, L, H, D]")
     B, Lq, H, D = q.shape
@@ -218,6 +246,8 @@ def arl2_feature_map(x: torch.Tensor, W: torch.Tensor, rope_cos: Optional[torch.
                      rope_sin: Optional[torch.Tensor], y: torch.Tensor, *, stream: Optional[int] = None) -> None:
     """y = RoPE(W[h] x) per (token, head): the feature map of Eq. (3) without its L2Norm.
     x, y [B, L, H, D] bf16; W [H, D, D] bf16 indexed [head, out, in]; rope_cos, rope_sin [L, D/2] fp32 or None."""
+    if _plain_call("arl2_feature_map", b"qWrrq", 0.0, 0.0, stream, None, x, W, rope_cos, rope_sin, y):
+        return
     if x.dim() != 4:
         raise ValueError("x must be [B, L, H, D]")
     B, L, H, D = x.shape
@@ -257,6 +287,8 @@ def arl2_gate_proj(x: torch.Tensor, Wg: torch.Tensor, g: torch.Tensor, *, heads:
 def arl2_state_commit(k: torch.Tensor, v: torch.Tensor, gate: torch.Tensor, S: torch.Tensor,
                       workspace: torch.Tensor, *, l2_eps: float = 0.0, stream: Optional[int] = None) -> None:
     """Post-denoise update of ``S`` in place, enqueued on the current (or given) stream."""
+    if _plain_call("arl2_state_commit", b"qqaS", 0.0, l2_eps, stream, workspace, k, v, gate, S):
+        return
     if k.dim() != 4:
         raise ValueError("k must be [B, L, H, D]")
     B, L, H, D = k.shape
@@ -274,6 +306,8 @@ def arl2_static_scratch_bytes() -> int:
 def arl2_state_commit_static(k: torch.Tensor, v: torch.Tensor, gate: torch.Tensor, S: torch.Tensor, *,
                              l2_eps: float = 0.0, stream: Optional[int] = None) -> None:
     """``arl2_state_commit`` without a workspace: the partial sums go to the library's fixed device array."""
+    if _plain_call("arl2_state_commit_static", b"qqaS", 0.0, l2_eps, stream, None, k, v, gate, S):
+        return
     if k.dim() != 4:
         raise ValueError("k must be [B, L, H, D]")
     B, L, H, D = k.shape
@@ -288,6 +322,9 @@ def arl2_state_commit_fm(xk: torch.Tensor, Wk: torch.Tensor, rope_cos: Optional[
                          xv: torch.Tensor, Wv: torch.Tensor, gate: torch.Tensor, S: torch.Tensor,
                          workspace: torch.Tensor, *, l2_eps: float = 0.0, stream: Optional[int] = None) -> None:
     """``arl2_state_commit`` on RoPE(Wk xk) and Wv xv, the two feature maps computed inside the commit kernel."""
+    if _plain_call("arl2_state_commit_fm", b"qWrrqWaS", 0.0, l2_eps, stream, workspace,
+                   xk, Wk, rope_cos, rope_sin, xv, Wv, gate, S):
+        return
     if xk.dim() != 4:
         raise ValueError("xk must be [B, L, H, D]")
     B, L, H, D = xk.shape
@@ -304,6 +341,8 @@ def arl2_state_commit_delta(k: torch.Tensor, v: torch.Tensor, gate: torch.Tensor
                             S: torch.Tensor, workspace: torch.Tensor, *, l2_eps: float = 0.0,
                             stream: Optional[int] = None) -> None:
     """Delta-rule update of ``S`` in place (Eq. (4) literally), enqueued on the current (or given) stream."""
+    if _plain_call("arl2_state_commit_delta", b"qqaaS", 0.0, l2_eps, stream, workspace, k, v, gate, beta, S):
+        return
     if k.dim() != 4:
         raise ValueError("k must be [B, L, H, D]")
     B, L, H, D = k.shape
@@ -325,6 +364,8 @@ def arl2_state_commit_gdn(k: torch.Tensor, v: torch.Tensor, alpha: torch.Tensor,
                           stream: Optional[int] = None) -> None:
     """Token-sequential gated delta rule on ``S`` in place (Eq. (4) per token, per-token gates
     ``alpha``, ``beta`` of shape [B, L, H]), enqueued on the current (or given) stream."""
+    if _plain_call("arl2_state_commit_gdn", b"qqttS", 0.0, l2_eps, stream, workspace, k, v, alpha, beta, S):
+        return
     if k.dim() != 4:
         raise ValueError("k must be [B, L, H, D]")
     B, L, H, D = k.shape

@@ -1,13 +1,15 @@
-"""Builds the gfx950 shared library (hipcc, in-tree).  Run as ``python -m paper_2605_16579_amd.build``."""
+"""Builds the gfx950 shared library (hipcc) and the host module of the binding (g++), in-tree.  Run as ``python -m paper_2605_16579_amd.build``."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libarl2_hip.so")
+HOST = os.path.join(PKG, "_arl2_host.so")
 SOURCES = ["arl2_api.hip", "arl2_fwd_bf16.hip", "arl2_commit_bf16.hip", "arl2_commit_fm_bf16.hip", "arl2_gdn_bf16.hip", "arl2_fmap_bf16.hip", "arl2_gate_bf16.hip", "arl2_f32.hip"]
 
 HIPCC_FLAGS = [
@@ -16,6 +18,23 @@ HIPCC_FLAGS = [
     # never let the compiler form packed-fp32 VALU ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+
+
+def build_host(verbose: bool = False) -> str:
+    import torch
+    from torch.utils import cpp_extension
+
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for path in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", path]
+    cmd += ["-o", HOST, os.path.join(CSRC, "arl2_host.cpp"), "-L", lib_dir, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout)
+    return HOST
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
@@ -30,6 +49,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         raise RuntimeError("hipcc failed:\n" + out)
     if verbose and out.strip():
         print(out)
+    build_host(verbose)
     return LIB
 
 
