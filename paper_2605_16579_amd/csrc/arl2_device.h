@@ -123,15 +123,20 @@ hipError_t launch_gate_proj_bf16(const GateArgs &a, hipStream_t stream);
 size_t gdn_workspace_bytes(int B, int H, int L, int D);
 
 // ---- launching ------------------------------------------------------------------------
-// Enqueues `kernel` and returns the status of this launch alone (an error that an earlier, unrelated HIP call
-// of the caller left behind is neither reported nor cleared).
+// Enqueues `kernel` with `lds` bytes of LDS beyond what it declares and returns the status of this launch alone (an error
+// that an earlier, unrelated HIP call of the caller left behind is neither reported nor cleared).
 template <class... Params, class... Args>
-inline hipError_t launch_kernel(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, Args... args)
+inline hipError_t launch_kernel_lds(void (*kernel)(Params...), dim3 grid, dim3 block, unsigned lds, hipStream_t stream, Args... args)
 {
     std::tuple<Params...> vals{static_cast<Params>(args)...};
     void *ptrs[sizeof...(Params) > 0 ? sizeof...(Params) : 1];
     fill_arg_pointers(ptrs, vals, std::index_sequence_for<Params...>{});
-    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, 0, stream);
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, lds, stream);
+}
+template <class... Params, class... Args>
+inline hipError_t launch_kernel(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, Args... args)
+{
+    return launch_kernel_lds(kernel, grid, block, 0, stream, args...);
 }
 
 // ---- small device helpers -------------------------------------------------------------

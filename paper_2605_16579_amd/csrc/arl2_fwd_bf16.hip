@@ -1,9 +1,9 @@
 // Read-only denoising pass on bf16 MFMA (gfx950):
 //   out = softmax(q k^T * sm_scale) v + g * L2Norm(q) S            paper Eq. (2), (3), (5), (6)
 //
-// One workgroup (8 wavefronts, two per SIMD, 256 registers each) owns 256 query rows of one (stream, head), each
-// wavefront 32 of them, or half a tile, 128 rows, with two wavefronts on the same rows and half of every key tile
-// each.  Everything is computed transposed so that no operand is re-laid out between the two GEMMs:
+// One workgroup owns 256 query rows of one (stream, head): eight wavefronts with 32 of them each, or at D = 64 four with 64
+// (`Whole`), or half a tile, 128 rows, with two wavefronts on the same rows and half of every key tile each.  A SIMD has two
+// wavefronts, of one workgroup or two, with 256 registers each.  Everything is computed transposed so that no operand is re-laid out between the two GEMMs:
 //
 //   S^T[kv][q]  = K[kv][:] . Q[q][:]      A = K tile rows from LDS,  B = Q fragments in registers
 //   O^T[d][q]  += V^T[d][kv] . P^T[kv][q] A = V^T fragments from LDS, B = exp'd S^T accumulators
@@ -17,8 +17,8 @@
 //
 // The unit of the schedule is a slot, the softmax of one 32-key block beside the first GEMM of the next block and the
 // second GEMM of the previous one (see `slot`).  K/V tiles travel (buffer loads, zero beyond the last key) into an LDS
-// ring with one workgroup barrier per tile: at D = 128 in whole tiles straight, requested two barriers ahead, else through
-// registers.  12 heads x 128, 14400 keys: 1.51 us per 64-key tile straight, 1.61 us through registers (on zeros, where power
+// ring with one workgroup barrier per tile: straight, requested two barriers ahead, or through registers (half tiles, and
+// eight wavefronts at D = 64, where that is the faster by up to 3 %).  12 heads x 128, 14400 keys: 1.51 us per 64-key tile straight, 1.61 us through registers (on zeros, where power
 // does not bound it, 1.09 and 1.15 us).  The softmax is optimistic: the running maximum
 // starts as the first block's, probabilities are taken relative to it as it stands, and only when a lane's share of
 // the row sum shows that a logit exceeded it by more than ~2^7 is the block maximum computed, the running maximum
@@ -36,7 +36,7 @@
 //
 // What bounds it: the matrix cores and, on real data, the power they draw (a launch that fills the chip holds the
 // clock at 1.73 GHz).  Measured for one pass with state and gate, 12 heads x 128:
-//   4680 tokens (228 tiles of 256 rows)   123 us; 1560 tokens (156 half tiles) 26.5 us, 38 us with 84 whole tiles;
+//   4680 tokens (228 tiles of 256 rows)   123 us; 3 x 24 heads x 64, 999 tokens (288 tiles) 28 us; 1560 tokens (156 half tiles) 26.5 us, 38 us with 84 whole tiles;
 //   2 x 3 heads, 328 tokens (18 half tiles) 11.9 us, 15.6 us with 12 whole ones (17 us with query rows loaded fragment by
 //   fragment, the tiles of the prologue one after the other and the first block's exponentials computed twice).
 #include "arl2_device.h"
@@ -47,24 +47,26 @@ namespace arl2 {
 namespace {
 
 constexpr int BN = 64;    // keys per tile
-constexpr int NT = 512;   // threads per workgroup
 constexpr int NSTAGE = 4; // LDS ring depth (a power of two)
-constexpr int kStoreStep0 = 4;   // the tile copy's LDS writes go into steps 4, 6, ... of an interval's second slot
+constexpr int kStoreStep0 = 4;   // the tile copy's LDS writes begin in this step of an interval's second slot
 
-template <int D, int KG>
+template <int D, int KG, int RB, int NW>
 struct FwdCfg {
-    static constexpr int BM = 256 / KG;          // query rows per workgroup
-    static constexpr int RG = 8 / KG;            // wavefronts that share their rows' keys with KG - 1 others each
+    static constexpr int NT = 64 * NW;           // threads per workgroup
+    static constexpr int RG = NW / KG;           // wavefronts that share their rows' keys with KG - 1 others each
+    static constexpr int WR = 32 * RB;           // query rows per wavefront
+    static constexpr int BM = WR * RG;           // query rows per workgroup
     static constexpr int KS = D / 16;            // k-steps of the QK^T contraction
     static constexpr int DB = D / 32;            // 32-row blocks of O^T
     static constexpr int CPR = D / 8;            // 16-byte chunks per row
     static constexpr int KROW = 2 * D + 16;      // LDS bytes per K row (padded: conflict-free b128 reads)
     static constexpr int VROW = 2 * D + 64;      // LDS bytes per V row (padded: conflict-free transposing reads)
-    // Direct copy: tiles go from memory into LDS without passing through registers, 1 KB (four rows) per instruction.
-    static constexpr bool DIRECT = D == 128 && KG == 1;
-    static constexpr int GROUP = 1024 + 16;      // LDS bytes from one group of four rows to the next
-    static constexpr int K_BYTES = DIRECT ? BN / 4 * GROUP : BN * KROW;
-    static constexpr int V_BYTES = DIRECT ? BN / 4 * GROUP : BN * VROW;
+    // Direct copy: tiles go from memory into LDS without passing through registers, 1 KB per instruction.
+    static constexpr bool DIRECT = KG == 1 && (D == 128 || NW == 4);
+    static constexpr int GROUP_ROWS = 512 / D;   // rows of such a kilobyte
+    static constexpr int GROUP = D == 128 ? 1024 + 16 : 1024;    // LDS bytes from one to the next
+    static constexpr int K_BYTES = DIRECT ? BN / GROUP_ROWS * GROUP : BN * KROW;
+    static constexpr int V_BYTES = DIRECT ? BN / GROUP_ROWS * GROUP : BN * VROW;
     static constexpr int STAGE = K_BYTES + V_BYTES;   // one K/V tile
     static constexpr int KV_BYTES = (KG == 1 ? NSTAGE : 2) * STAGE;
     static constexpr int DBW = DB / KG;          // 32-feature blocks of the output that a wavefront finishes
@@ -75,12 +77,14 @@ struct FwdCfg {
     // fused feature map: half of Wq[h] (D/2 rows) plus, per wavefront, the rotation tables of its 32 tokens
     static constexpr int WH_BYTES = (D / 2) * KROW;
     static constexpr int TST = D / 2 + 2;        // floats per staged table row (conflict-free 8-byte reads)
-    static constexpr int TAB_BYTES = 2 * 32 * TST * 4;
+    static constexpr int TAB_BYTES = 2 * WR * TST * 4;
     static constexpr int FM_BYTES = WH_BYTES + RG * TAB_BYTES;
     static constexpr int WCH = ((D / 2) * CPR + NT - 1) / NT;     // 16-byte chunks of the Wq half per thread
-    static constexpr int TCH = 32 * (D / 8) / 64;                 // 16-byte chunks of one table tile per lane
+    static constexpr int TCH = WR * (D / 8) / 64;                 // 16-byte chunks of one table tile per lane
     // one key group: the query rows pass through ring stages 2 and on, and what they need beyond them
-    static constexpr int Q_END = KG == 1 ? 2 * STAGE + BM * KROW : 0;
+    static constexpr int Q_GROUPS = WR / GROUP_ROWS;     // of a wavefront's query rows
+    static constexpr int Q_BYTES = DIRECT ? Q_GROUPS * GROUP : WR * KROW;
+    static constexpr int Q_END = KG == 1 ? 2 * STAGE + NW * Q_BYTES : 0;
     static constexpr int RING_END = Q_END > KV_BYTES ? Q_END : KV_BYTES;
     static constexpr int SMEM0 = (RING_END > ST_BYTES ? (RING_END > OUT_BYTES ? RING_END : OUT_BYTES)
                                                       : (ST_BYTES > OUT_BYTES ? ST_BYTES : OUT_BYTES));
@@ -88,15 +92,15 @@ struct FwdCfg {
     // with two key groups the ring is half as large and the state has room of its own behind it
     static constexpr int S_OFF = KG == 1 ? 0 : KV_BYTES;
     static constexpr int ML_OFF = KG == 1 ? SMEM1 : (KV_BYTES + ST_BYTES > SMEM1 ? KV_BYTES + ST_BYTES : SMEM1);
-    static constexpr int SMEM = ML_OFF + (KG == 1 ? 0 : 8 * 2 * 32 * 4);
+    static constexpr int SMEM = ML_OFF + (KG == 1 ? 0 : NW * 2 * 32 * 4);
     static_assert(SMEM <= 160 * 1024, "more LDS than a CU has");
-    static_assert(KG == 1 || 8 * DBW * 16 * 64 * 4 <= KV_BYTES, "the partial outputs pass through the ring");
+    static_assert(KG == 1 || NW * RB * DBW * 16 * 64 * 4 <= KV_BYTES, "the partial outputs pass through the ring");
     static constexpr int KCH = BN * CPR / NT;    // 16-byte chunks per thread per tile (K and V each)
     static constexpr int ROWS_PER_PASS = NT / CPR;
-    static constexpr int S_LEN = KS;             // MFMAs of the S^T chain of one 32-key block
-    static constexpr int PV_LEN = 2 * DB;        // MFMAs of the PV chain of one 32-key block
+    static constexpr int S_LEN = KS;             // K fragments of one 32-key block, each for RB MFMAs
+    static constexpr int PV_LEN = 2 * DB;        // V^T fragments of one 32-key block, each for RB MFMAs
     static constexpr int RING = 4;               // fragment registers in flight from LDS
-    static constexpr int PF = RING - 1;          // operand fragments are read from LDS this many MFMAs ahead
+    static constexpr int PF = RING - 1;          // operand fragments are read from LDS this many steps ahead
     // LDS reads a full slot issues after step `first` (its own fragments, then the next slot's; S fragments,
     // at even positions, are one read, V^T fragments two)
     static constexpr int lds_reads_from(int first)
@@ -105,8 +109,11 @@ struct FwdCfg {
         for (int n = first; n < S_LEN + PV_LEN; ++n) c += ((n + PF) & 1) == 0 ? 1 : 2;
         return c;
     }
-    static constexpr int LDS_AFTER_COPY = lds_reads_from(kStoreStep0 + 4 * KCH - 1);
-    static_assert(kStoreStep0 + 4 * KCH - 2 < S_LEN + PV_LEN && 2 * KCH - 1 < S_LEN + PV_LEN, "the copy must fit into one slot");
+    // the copy's writes go into every other step if they all fit, else into every step
+    static constexpr int STORE_STRIDE = kStoreStep0 + 4 * KCH - 2 < S_LEN + PV_LEN ? 2 : 1;
+    static constexpr int LAST_STORE = kStoreStep0 + STORE_STRIDE * (2 * KCH - 1);
+    static constexpr int LDS_AFTER_COPY = lds_reads_from(LAST_STORE + 1);
+    static_assert(LAST_STORE < S_LEN + PV_LEN && 2 * KCH - 1 < S_LEN + PV_LEN, "the copy must fit into one slot");
     static_assert(KCH >= 1, "tile too small for the workgroup");
     static_assert(S_LEN % RING == 0 && PV_LEN % RING == 0, "chain lengths must be multiples of the fragment ring");
 };
@@ -116,7 +123,7 @@ struct FwdCfg {
 constexpr float kRowSumLimit = 4096.0f;
 
 
-// Two groups of four rows straight into LDS (16 bytes per lane, lane l to lds + 16 l; the second OFF2 bytes further).  The
+// Two kilobytes straight into LDS (16 bytes per lane, lane l to lds + 16 l; the second OFF2 bytes further).  The
 // instruction's offset moves the source address as well, so `off2` is less by as much.  M0 carries the LDS address; nothing
 // else in these kernels reads it.  There is no output register: the caller waits on vmcnt before the bytes are read.
 template <int OFF2>
@@ -133,11 +140,11 @@ __device__ __forceinline__ void direct_barrier()
 }
 
 // Query tile qt (of 256 / KG rows) of (stream, head) bh, by one workgroup.
-template <int D, int KG, bool FUSED_MAP>
+template <int D, int KG, int RB, int NW, bool FUSED_MAP>
 __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int bh, int qt, unsigned char *smem)
 {
-    using C = FwdCfg<D, KG>;
-    constexpr int BM = C::BM;
+    using C = FwdCfg<D, KG, RB, NW>;
+    constexpr int BM = C::BM, NT = C::NT, WR = C::WR;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, c = lane & 31, hh = lane >> 5;
@@ -154,14 +161,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     const __amdgpu_buffer_rsrc_t v_rsrc = make_rsrc(vgl, kv_range);
 
     // ---- Q fragments (B operand of S^T = K Q^T): lane (c, hh) holds Q[row][16 t + 8 hh + 0..7]
-    const int q0 = qt * BM + rg * 32;
-    const int qrow = q0 + c;
-    bf16x8 qf[C::KS];
-    float qss = 0.f;                  // |row|^2 over the full head dimension
+    const int q0 = qt * BM + rg * WR;
+    bf16x8 qf[RB][C::KS];
+    float qss[RB];                    // |row|^2 over the full head dimension
     // The rows travel whole (16-byte chunks, D / 8 lanes per row) through LDS rows of KROW bytes to the fragments:
     // fragment loads straight from memory touch 32 cache lines per instruction.  The key groups of a row group move
     // a share of its rows each.  Rows past the last query read as zero.
-    constexpr int QCH = 32 * C::CPR / 64 / KG;             // chunks per lane
+    constexpr int QCH = WR * C::CPR / 64 / KG;             // chunks per lane
     const int q_rows = Lq - qt * BM < BM ? Lq - qt * BM : BM;
     const __amdgpu_buffer_rsrc_t q_rsrc = make_rsrc((const bf16_t *)a.q + ((size_t)(b * (size_t)Lq + qt * BM) * H + h) * D,
                                                     (uint32_t)(q_rows - 1) * tok_bytes + 2 * D);
@@ -169,7 +175,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
 #pragma unroll
         for (int i = 0; i < QCH; ++i) {
             const int id = lane + 64 * (kg * QCH + i);
-            x[i] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, (uint32_t)(32 * rg + id / C::CPR) * tok_bytes + 16 * (id % C::CPR), 0, 0);
+            x[i] = __builtin_amdgcn_raw_buffer_load_b128(q_rsrc, (uint32_t)(WR * rg + id / C::CPR) * tok_bytes + 16 * (id % C::CPR), 0, 0);
         }
     };
     auto put_rows = [&](unsigned char *dst, const u32x4 *x) {
@@ -179,26 +185,43 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             *(u32x4 *)(dst + (id / C::CPR) * C::KROW + 16 * (id % C::CPR)) = x[i];
         }
     };
+    // Direct copy: fragment offsets, 64-byte (D = 64: 32-byte) column x of K row c and 64-byte column x of V row vr + 4 hh
+    int kdx[4] = {}, vdx[4] = {};
     auto get_rows = [&](const unsigned char *src) {
 #pragma unroll
-        for (int t = 0; t < C::KS; ++t) qf[t] = *(const bf16x8 *)(src + c * C::KROW + 32 * t + 16 * hh);
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int t = 0; t < C::KS; ++t) {
+                if constexpr (C::DIRECT) qf[rb][t] = *(const bf16x8 *)(src + rb * (C::K_BYTES / 2) + (D == 128 ? kdx[t / 2] + 32 * (t & 1) : kdx[t]));
+                else qf[rb][t] = *(const bf16x8 *)(src + (32 * rb + c) * C::KROW + 32 * t + 16 * hh);
+            }
     };
     // the same fragments straight from memory (the other query arrays of the epilogue)
-    const size_t row_off = ((size_t)(b * (size_t)Lq + (qrow < Lq ? qrow : 0)) * H + h) * D;   // rows past the last query read row 0, unused
-    auto load_rows = [&](const bf16_t *src, bf16x8 *x) {
+    auto row_token = [&](int rb) -> size_t {              // rows past the last query read row 0, unused
+        const int qrow = q0 + 32 * rb + c;
+        return b * (size_t)Lq + (qrow < Lq ? qrow : 0);
+    };
+    auto load_rows = [&](const bf16_t *src, bf16x8 (*x)[C::KS]) {
 #pragma unroll
-        for (int t = 0; t < C::KS; ++t) x[t] = *(const bf16x8 *)(src + row_off + 8 * hh + 16 * t);
+        for (int rb = 0; rb < RB; ++rb) {
+            const bf16_t *row = src + (row_token(rb) * H + h) * D + 8 * hh;
+#pragma unroll
+            for (int t = 0; t < C::KS; ++t) x[rb][t] = *(const bf16x8 *)(row + 16 * t);
+        }
     };
     auto square_rows = [&]() {
-        qss = 0.f;
 #pragma unroll
-        for (int t = 0; t < C::KS; ++t)
+        for (int rb = 0; rb < RB; ++rb) {
+            float ss = 0.f;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float f = (float)qf[t][j];
-                qss = fmaf(f, f, qss);
-            }
-        qss = xhalf_sum(qss);
+            for (int t = 0; t < C::KS; ++t)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float f = (float)qf[rb][t][j];
+                    ss = fmaf(f, f, ss);
+                }
+            qss[rb] = xhalf_sum(ss);
+        }
     };
 
     // ---- global -> registers -> LDS copies: 16-byte chunks, chunk id = tid + NT*i -> (row, col)
@@ -252,31 +275,58 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         if constexpr (p == 2 * C::KCH - 1) g_off += BN * tok_bytes;
     };
 
-    // Direct copy.  Row r, 16-byte chunk x of a tile lie at (r / 4) GROUP + 256 (r % 4) + 16 (x ^ 4 (r % 4)): the 16 bytes
-    // between groups and the exchanged chunks keep both kinds of fragment read free of bank conflicts, which a copy of whole
-    // kilobytes cannot do by padding rows.  A wavefront moves two groups of K and two of V; a tile is requested two barrier
-    // intervals before it is read.
+    // Direct copy.  A copy of whole kilobytes cannot pad rows to keep the fragment reads free of bank conflicts; the 16-byte
+    // chunks x of a row r are exchanged instead:
+    //   D = 128: at (r / 4) GROUP + 256 (r % 4) + 16 (x ^ 4 (r % 4)), the groups of four rows 16 bytes apart;
+    //   D = 64:  at 128 r + 16 (x ^ r / 2 % 8) in K tiles (32 rows are read at one chunk), and 128 r + 16 (x ^ 4 (r / 2 % 2)) in
+    //            V tiles (four rows at four chunks).
+    // A wavefront moves two kilobytes of K and of V; a tile is requested two barrier intervals before it is read.
     const uint32_t lds0 = lds_address(smem);
-    uint32_t dsrc[2] = {};            // source offsets of the lane's two chunks, from 64 bytes below the tile
-    int kdx[4] = {}, vdx[4] = {};     // fragment offsets: 64-byte column x of K row c, of V row (lane / 4) % 4 + 4 hh
+    uint32_t dsrc[2][2] = {};         // source offsets of the lane's two chunks of K and V, from BELOW bytes below the tile
+    constexpr int BELOW = D == 128 ? 64 : 0;
     if constexpr (C::DIRECT) {
-        static_assert(!C::DIRECT || BN / 4 == 2 * NT / 64, "two groups of K and of V per wavefront");
+        static_assert(!C::DIRECT || BN / C::GROUP_ROWS == 2 * NW, "two kilobytes of K and of V per wavefront");
         const int vr = (lane >> 2) & 3;
+        if constexpr (D == 128) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            kdx[x] = (c >> 2) * C::GROUP + 256 * (c & 3) + 64 * (x ^ (c & 3)) + 16 * hh;
-            vdx[x] = hh * C::GROUP + 256 * vr + 64 * (x ^ vr) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+            for (int x = 0; x < 4; ++x) {
+                kdx[x] = (c >> 2) * C::GROUP + 256 * (c & 3) + 64 * (x ^ (c & 3)) + 16 * hh;
+                vdx[x] = hh * C::GROUP + 256 * vr + 64 * (x ^ vr) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+            }
+            dsrc[0][0] = (uint32_t)(8 * wave + (lane >> 4)) * tok_bytes + 16 * ((lane & 15) ^ (4 * (lane >> 4))) + BELOW;
+            dsrc[0][1] = dsrc[0][0] + 4 * tok_bytes - C::GROUP;        // (4 tok_bytes >= 1024, hence the 64 bytes)
+            dsrc[1][0] = dsrc[0][0];
+            dsrc[1][1] = dsrc[0][1];
+        } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) kdx[x] = 128 * c + 32 * (x ^ ((c >> 2) & 3)) + 16 * (hh ^ ((c >> 1) & 1));
+#pragma unroll
+            for (int x = 0; x < 2; ++x) vdx[x] = 128 * (vr + 4 * hh) + 64 * (x ^ (vr >> 1)) + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+            const uint32_t row = (uint32_t)(16 * wave + (lane >> 3)) * tok_bytes;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {                              // (8 tok_bytes >= 1024)
+                dsrc[0][i] = row + i * (8 * tok_bytes - C::GROUP) + 16 * ((lane & 7) ^ (4 * i + (lane >> 4)));
+                dsrc[1][i] = row + i * (8 * tok_bytes - C::GROUP) + 16 * ((lane & 7) ^ (4 * ((lane >> 4) & 1)));
+            }
         }
-        dsrc[0] = (uint32_t)(8 * wave + (lane >> 4)) * tok_bytes + 16 * ((lane & 15) ^ (4 * (lane >> 4))) + 64;
-        dsrc[1] = dsrc[0] + 4 * tok_bytes - C::GROUP;        // (4 tok_bytes >= 1024, hence the 64 bytes)
     }
     // K (PART 0) or V (PART 1) of a tile; past the last key nothing is read and zeros are stored.
     auto direct_part = [&](int tile, auto part_) {
         constexpr int PART = decltype(part_)::value;
         const int left = (int)kv_range - tile * (int)(BN * tok_bytes);
-        const bf16_t *base = (PART ? vgl : kgl) + (ptrdiff_t)tile * BN * H * D - 32;
-        load_pair_to_lds<C::GROUP>(make_rsrc(base, left > 0 ? (uint32_t)left + 64 : 0), dsrc[0], dsrc[1],
+        const bf16_t *base = (PART ? vgl : kgl) + (ptrdiff_t)tile * BN * H * D - BELOW / 2;
+        load_pair_to_lds<C::GROUP>(make_rsrc(base, left > 0 ? (uint32_t)left + BELOW : 0), dsrc[PART][0], dsrc[PART][1],
                                    lds0 + (tile & (NSTAGE - 1)) * C::STAGE + PART * C::K_BYTES + 2 * wave * C::GROUP);
+    };
+    // This wavefront's query rows, laid out like those of a K tile, to `lds`.
+    auto direct_rows = [&](uint32_t lds) {
+        const __amdgpu_buffer_rsrc_t rsrc = make_rsrc((const bf16_t *)a.q + ((size_t)(b * (size_t)Lq + qt * BM) * H + h) * D - BELOW / 2,
+                                                      (uint32_t)(q_rows - 1) * tok_bytes + 2 * D + BELOW);
+#pragma unroll
+        for (int g = 0; g < C::Q_GROUPS; g += 2) {
+            const uint32_t off = (uint32_t)(WR * rg + C::GROUP_ROWS * (g - 2 * wave)) * tok_bytes;
+            load_pair_to_lds<C::GROUP>(rsrc, dsrc[0][0] + off, dsrc[0][1] + off, lds + g * C::GROUP);
+        }
     };
     auto direct_tile = [&](int tile) { static_for<0, 2>([&](auto part_) { direct_part(tile, part_); }); };
 
@@ -285,28 +335,30 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     const int v_frag_off = (((lane & 15) >> 2) + 4 * hh) * C::VROW + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
 
     // ---- running softmax state and accumulators
-    f32x16 o_acc[C::DB];         // O^T blocks
-    f32x16 s_acc[2];             // S^T of the key block whose softmax runs, and of the next one
-    bf16x8 pf[4];                // P^T fragments (B operands of the second GEMM): two per key block
+    f32x16 o_acc[C::DB][RB];     // O^T blocks
+    f32x16 s_acc[2][RB];         // S^T of the key block whose softmax runs, and of the next one
+    bf16x8 pf[2][RB][2];         // P^T fragments (B operands of the second GEMM): two per key block
     bf16x8 fr[C::RING];          // A-operand fragments in flight from LDS
-    float m_run = -INFINITY;     // running max of scaled logits (log2 domain)
-    float l_run = 0.f;           // this lane's share of the running sum
+    float m_run[RB];             // running max of scaled logits (log2 domain)
+    float l_run[RB] = {};        // this lane's share of the running sum
     auto clear_output = [&]() {
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o_acc[db][rb][r] = 0.f;
     };
 
     // Byte offsets in the ring of the K rows / V rows of this wavefront's 32-key block `blk`: half blk % 2 of tile
     // blk / 2, or with two key groups half kg of tile blk.
     auto k_block = [&](int blk) -> int {
-        if constexpr (C::DIRECT) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * 8 * C::GROUP;
+        if constexpr (C::DIRECT) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * (C::K_BYTES / 2);
         else if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + (blk & 1) * 32 * C::KROW;
         else return (blk & 1) * C::STAGE + kg * 32 * C::KROW;
     };
     auto v_block = [&](int blk) -> int {
-        if constexpr (C::DIRECT) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * 8 * C::GROUP;
+        if constexpr (C::DIRECT) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * (C::K_BYTES / 2);
         else if constexpr (KG == 1) return ((blk >> 1) & (NSTAGE - 1)) * C::STAGE + C::K_BYTES + (blk & 1) * 32 * C::VROW;
         else return (blk & 1) * C::STAGE + C::K_BYTES + kg * 32 * C::VROW;
     };
@@ -315,28 +367,46 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     // (16-key step n / DB, row block n % DB: a transposed V piece).
     auto k_frag = [&](const unsigned char *kp, auto n_) -> bf16x8 {
         constexpr int n = decltype(n_)::value;
-        if constexpr (C::DIRECT) return *(const bf16x8 *)(kp + kdx[n / 2] + 32 * (n & 1));
+        if constexpr (C::DIRECT && D == 128) return *(const bf16x8 *)(kp + kdx[n / 2] + 32 * (n & 1));
+        else if constexpr (C::DIRECT) return *(const bf16x8 *)(kp + kdx[n]);
         else return *(const bf16x8 *)(kp + k_frag_off + 32 * n);
     };
     auto v_frag = [&](const unsigned char *vp, auto n_) -> bf16x8 {
         constexpr int n = decltype(n_)::value;
         // keys 16u + 4hh + 0..3 and 16u + 8 + 4hh + 0..3
-        if constexpr (C::DIRECT) return lds_read_tr_pair(vp + vdx[n % C::DB] + 4 * (n / C::DB) * C::GROUP, 2 * C::GROUP);
+        if constexpr (C::DIRECT) return lds_read_tr_pair(vp + vdx[n % C::DB] + (n / C::DB) * (C::V_BYTES / 4), C::V_BYTES / 8);
         else return lds_read_tr_pair(vp + v_frag_off + 16 * (n / C::DB) * C::VROW + 64 * (n % C::DB), 8 * C::VROW);
+    };
+    // Products of a step: K fragment n (or V^T fragment n) with the query rows (the probabilities) of every row block.
+    auto s_mfma = [&](auto buf_, auto n_, bf16x8 x) {
+        constexpr int buf = decltype(buf_)::value, t = decltype(n_)::value;
+        const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+        static_for<0, RB>([&](auto r_) {
+            constexpr int rb = decltype(r_)::value;
+            if constexpr (t == 0) s_acc[buf][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, qf[rb][t], zero, 0, 0, 0);
+            else s_acc[buf][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, qf[rb][t], s_acc[buf][rb], 0, 0, 0);
+        });
+    };
+    auto pv_mfma = [&](auto buf_, auto n_, bf16x8 x) {
+        constexpr int buf = decltype(buf_)::value, u = decltype(n_)::value / C::DB, db = decltype(n_)::value % C::DB;
+        static_for<0, RB>([&](auto r_) {
+            constexpr int rb = decltype(r_)::value;
+            o_acc[db][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, pf[buf][rb][u], o_acc[db][rb], 0, 0, 0);
+        });
     };
     // exp2 of the 16 logits per lane of one key block relative to the running maximum -> its two P^T
     // fragments; returns this lane's share of the row sum.  (Only on the rare path that raises the maximum.)
-    auto exp_block = [&](auto par_) -> float {
-        constexpr int PAR = decltype(par_)::value;
-        const float mneg = -m_run;
+    auto exp_block = [&](auto par_, auto r_) -> float {
+        constexpr int PAR = decltype(par_)::value, rb = decltype(r_)::value;
+        const float mneg = -m_run[rb];
         float psum = 0.f;
-        static_for<0, 8>([&](auto r_) {
-            constexpr int r = 2 * decltype(r_)::value;
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(s_acc[PAR][r], scale_log2, mneg));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(s_acc[PAR][r + 1], scale_log2, mneg));
+        static_for<0, 8>([&](auto i_) {
+            constexpr int r = 2 * decltype(i_)::value;
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(s_acc[PAR][rb][r], scale_log2, mneg));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(s_acc[PAR][rb][r + 1], scale_log2, mneg));
             psum += p0 + p1;
-            pf[2 * PAR + (r >> 3)][r & 7] = to_bf16(p0);
-            pf[2 * PAR + (r >> 3)][(r & 7) + 1] = to_bf16(p1);
+            pf[PAR][rb][r >> 3][r & 7] = to_bf16(p0);
+            pf[PAR][rb][r >> 3][(r & 7) + 1] = to_bf16(p1);
         });
         return psum;
     };
@@ -362,38 +432,40 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         constexpr bool HAS_S = decltype(has_s_)::value, HAS_PV = decltype(has_pv_)::value;
         constexpr bool NEXT_S = decltype(next_s_)::value, MASKED = decltype(masked_)::value;
         constexpr int SL = HAS_S ? C::S_LEN : 0, NS = SL + (HAS_PV ? C::PV_LEN : 0);
-        constexpr int LPS = 16 / NS;                 // logits per step
-        static_assert(NS % C::RING == 0 && 16 % NS == 0, "slot length");
+        constexpr int NL = 16 * RB, LPS = NL / NS;   // logits per lane, and per step
+        static_assert(NS % C::RING == 0 && NL % NS == 0, "slot length");
         const unsigned char *kp = smem + k_block(j + 1);
         const unsigned char *vp = smem + v_block(j - 1);
         const unsigned char *np = smem + k_block(j + 2);      // next slot: S(j+2) (if any) and PV(j)
         const unsigned char *nvp = smem + v_block(j);
-        const float mneg = -m_run;
-        float x[16], ps0 = 0.f, ps1 = 0.f;
+        float x[NL], ps0[RB] = {}, ps1[RB] = {};
+        int key0 = first_key(j) + 4 * hh;            // key of the lane's first logit
+        if constexpr (MASKED && RB > 1) asm volatile("" : "+v"(key0));    // (sixteen keys would otherwise be kept from the first block to the last)
         auto op_scale = [&](auto v_) {               // logit v: scaled, relative to the running maximum
             constexpr int v = decltype(v_)::value;
-            if constexpr (v < 16) {
+            if constexpr (v < NL) {
+                constexpr int rb = v >> 4, r = v & 15;
                 if constexpr (MASKED) {              // keys past the end of the sequence (last tile only)
-                    const int kvl = 8 * (v >> 2) + 4 * hh + (v & 3);
-                    if (first_key(j) + kvl >= Lkv) s_acc[PAR][v] = -INFINITY;
+                    if (key0 >= Lkv - (8 * (r >> 2) + (r & 3))) s_acc[PAR][rb][r] = -INFINITY;
                 }
-                x[v] = fmaf(s_acc[PAR][v], scale_log2, mneg);
+                x[v] = fmaf(s_acc[PAR][rb][r], scale_log2, -m_run[rb]);
             }
         };
         auto op_exp = [&](auto v_) {
             constexpr int v = decltype(v_)::value;
-            if constexpr (v < 16) x[v] = __builtin_amdgcn_exp2f(x[v]);
+            if constexpr (v < NL) x[v] = __builtin_amdgcn_exp2f(x[v]);
         };
         auto op_sum = [&](auto v_) {                 // row-sum share, and the P^T pair (v-1, v) for odd v
             constexpr int v = decltype(v_)::value;
+            constexpr int rb = v >> 4, u = (v >> 3) & 1;
             if constexpr (v & 1) {
-                ps1 += x[v];
+                ps1[rb] += x[v];
                 bf16x2 pk = {to_bf16(x[v - 1]), to_bf16(x[v])};
                 asm volatile("" : "+v"(pk));         // the conversion stays in this step
-                pf[2 * PAR + (v >> 3)][(v & 7) - 1] = pk[0];
-                pf[2 * PAR + (v >> 3)][v & 7] = pk[1];
+                pf[PAR][rb][u][(v & 7) - 1] = pk[0];
+                pf[PAR][rb][u][v & 7] = pk[1];
             } else {
-                ps0 += x[v];
+                ps0[rb] += x[v];
             }
         };
         // MFMA n of the slot: with both chains present they alternate (S at even n), so that MFMAs which
@@ -415,21 +487,11 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         static_for<0, NS>([&](auto n_) {
             constexpr int n = decltype(n_)::value;
             fetch(std::integral_constant<int, n + C::PF>{});
-            if constexpr (is_s(n)) {
-                constexpr int t = idx(n);
-                if constexpr (t == 0) {
-                    const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                    s_acc[PAR ^ 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[t], zero, 0, 0, 0);
-                } else {
-                    s_acc[PAR ^ 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[t], s_acc[PAR ^ 1], 0, 0, 0);
-                }
-            } else {
-                constexpr int u = idx(n) / C::DB, db = idx(n) % C::DB;
-                o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], pf[2 * (PAR ^ 1) + u], o_acc[db], 0, 0, 0);
-            }
+            if constexpr (is_s(n)) s_mfma(std::integral_constant<int, PAR ^ 1>{}, std::integral_constant<int, idx(n)>{}, fr[n % C::RING]);
+            else pv_mfma(std::integral_constant<int, PAR ^ 1>{}, std::integral_constant<int, idx(n)>{}, fr[n % C::RING]);
             if constexpr (COPY == 1 && (n & 1) == 1 && n / 2 < C::KCH) load_tile_part(std::integral_constant<int, n / 2>{});
-            if constexpr (COPY == 2 && n >= kStoreStep0 && n < kStoreStep0 + 4 * C::KCH && ((n - kStoreStep0) & 1) == 0)
-                store_tile_part(cstage, std::integral_constant<int, (n - kStoreStep0) / 2>{});
+            if constexpr (COPY == 2 && n >= kStoreStep0 && n <= C::LAST_STORE && (n - kStoreStep0) % C::STORE_STRIDE == 0)
+                store_tile_part(cstage, std::integral_constant<int, (n - kStoreStep0) / C::STORE_STRIDE>{});
             if constexpr (COPY == 5 && n == NS - C::PF - 1) direct_barrier<4>();
             if constexpr (COPY == 6 && (n == 1 || n == 5)) direct_part(cstage, std::integral_constant<int, n / 4>{});
             if constexpr (COPY == 3 || COPY == 4) {
@@ -455,25 +517,34 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             });
             __builtin_amdgcn_sched_barrier(0);
         });
-        float psum = ps0 + ps1;
         // Rarely a logit exceeded the running maximum (which starts as the first block's) by more than the
         // threshold: take the true block maximum, raise the running maximum, rescale, redo the block.
-        if (__builtin_expect(__any(!(psum < kRowSumLimit)), 0)) {      // wave-uniform; also true for inf and NaN
-            // (compile-time loops: the compiler unrolls nothing on a path it is told to be rare)
-            float mx = s_acc[PAR][0];
-            static_for<1, 16>([&](auto r_) { mx = fmaxf(mx, s_acc[PAR][decltype(r_)::value]); });
-            mx = xhalf_max(mx) * scale_log2;
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = m_new == m_run ? 1.0f : __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-            l_run *= alpha;
-            if constexpr (HAS_PV)
-                static_for<0, C::DB>([&](auto db_) {
-                    static_for<0, 16>([&](auto r_) { o_acc[decltype(db_)::value][decltype(r_)::value] *= alpha; });
-                });
-            psum = exp_block(par_);
+        bool over = false;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            ps0[rb] += ps1[rb];
+            over |= !(ps0[rb] < kRowSumLimit);
         }
-        l_run += psum;
+        if (__builtin_expect(__any(over), 0)) {      // wave-uniform; also true for inf and NaN
+            // (compile-time loops: the compiler unrolls nothing on a path it is told to be rare)
+            static_for<0, RB>([&](auto b_) {
+                constexpr int rb = decltype(b_)::value;
+                float mx = s_acc[PAR][rb][0];
+                static_for<1, 16>([&](auto r_) { mx = fmaxf(mx, s_acc[PAR][rb][decltype(r_)::value]); });
+                mx = xhalf_max(mx) * scale_log2;
+                const float m_new = fmaxf(m_run[rb], mx);
+                const float alpha = m_new == m_run[rb] ? 1.0f : __builtin_amdgcn_exp2f(m_run[rb] - m_new);
+                m_run[rb] = m_new;
+                l_run[rb] *= alpha;
+                if constexpr (HAS_PV)
+                    static_for<0, C::DB>([&](auto db_) {
+                        static_for<0, 16>([&](auto r_) { o_acc[decltype(db_)::value][rb][decltype(r_)::value] *= alpha; });
+                    });
+                ps0[rb] = exp_block(par_, b_);
+            });
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) l_run[rb] += ps0[rb];
     };
 
     const std::false_type no{};
@@ -498,35 +569,33 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             constexpr int m = n + C::PF;
             if constexpr (m < C::S_LEN) fr[m % C::RING] = k_frag(kp, std::integral_constant<int, m>{});
             else fr[m % C::RING] = k_frag(np, std::integral_constant<int, m - C::S_LEN>{});
-            if constexpr (n == 0) {
-                const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-                s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[n], zero, 0, 0, 0);
-            } else {
-                s_acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], qf[n], s_acc[0], 0, 0, 0);
-            }
+            s_mfma(par0, n_, fr[n % C::RING]);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
     // The running maximum starts as the true maximum of the first block (which always holds a key: with two key groups
     // Lkv > 32), so that its slot need not find out by computing every exponential twice.
     auto first_maximum = [&]() {
-        float mx = -INFINITY;
+        int key0 = first_key(0) + 4 * hh;
+        if constexpr (RB > 1) asm volatile("" : "+v"(key0));
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = first_key(0) + 8 * (r >> 2) + 4 * hh + (r & 3);
-            mx = fmaxf(mx, key < Lkv ? s_acc[0][r] : -INFINITY);
+        for (int rb = 0; rb < RB; ++rb) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                mx = fmaxf(mx, key0 < Lkv - (8 * (r >> 2) + (r & 3)) ? s_acc[0][rb][r] : -INFINITY);
+            }
+            m_run[rb] = fmaxf(xhalf_max(mx) * scale_log2, -FLT_MAX);     // finite also where every logit of the block is -inf
         }
-        m_run = fmaxf(xhalf_max(mx) * scale_log2, -FLT_MAX);     // finite also where every logit of the block is -inf
     };
     // second GEMM of the last key block `blk` of parity P (its first fragments are in flight)
     auto last_product = [&](auto p_, int blk) {
-        constexpr int P = decltype(p_)::value;
         const unsigned char *vp = smem + v_block(blk);
         static_for<0, C::PV_LEN>([&](auto n_) {
             constexpr int n = decltype(n_)::value;
             constexpr int m = n + C::PF;
             if constexpr (m < C::PV_LEN) fr[m % C::RING] = v_frag(vp, std::integral_constant<int, m>{});
-            o_acc[n % C::DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[n % C::RING], pf[2 * P + n / C::DB], o_acc[n % C::DB], 0, 0, 0);
+            pv_mfma(p_, n_, fr[n % C::RING]);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
@@ -570,12 +639,14 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     constexpr bool ONE_ENDING = D == 128 && !FUSED_MAP;
 
     if constexpr (KG == 1) {
-        const int ntiles = (Lkv + BN - 1) / BN;
+        // Two row blocks: a single tile gets an empty second one, whose keys are all masked, and the first tile's keys are
+        // masked in any case (with a path of its own for a single tile registers would spill).
+        const int nt0 = (Lkv + BN - 1) / BN, ntiles = RB > 1 && nt0 == 1 ? 2 : nt0;
         // ---- prologue: tiles 0 and 1 into the ring, all their loads and those of the query rows in flight together
         {
             u32x4 k1[C::KCH], v1[C::KCH], x[QCH];
             if constexpr (C::DIRECT) {
-                if (q0 < Lq) fetch_rows(x);
+                if (q0 < Lq) direct_rows(lds0 + 2 * C::STAGE + wave * C::Q_BYTES);
                 direct_tile(0);
                 direct_tile(1);
             } else {
@@ -586,9 +657,11 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
                 load_v(1, v1);
                 store_k(0, kst);
             }
-            unsigned char *mine = smem + 2 * C::STAGE + wave * 32 * C::KROW;     // in stages that tile 2 and on will use
-            if (q0 < Lq) put_rows(mine, x);
-            if constexpr (!C::DIRECT) {
+            unsigned char *mine = smem + 2 * C::STAGE + wave * C::Q_BYTES;       // in stages that tile 2 and on will use
+            if constexpr (C::DIRECT) {
+                asm volatile("s_waitcnt vmcnt(8)" ::: "memory");                 // the query rows are there, the two tiles may not
+            } else {
+                if (q0 < Lq) put_rows(mine, x);
                 store_v(0, vst);
                 store_k(1, k1);
                 store_v(1, v1);
@@ -600,7 +673,6 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         }
         if constexpr (C::DIRECT) direct_barrier<0>();
         else __syncthreads();
-        clear_output();
 
         // Interval i covers the slots of key blocks 2i and 2i+1: they read K of tiles i and i+1 and V of tiles i-1 and i.
         // Direct copy: the barrier of interval i stands near the end of its first slot.  Behind it tile i-1 is no longer read
@@ -624,11 +696,17 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             if constexpr (C::DIRECT) direct_tile(3);
             else load_tile(2);
             first_maximum();
-            if (ntiles == 1) {
+            if constexpr (RB > 1) {
+                slot(par0, yes, no, yes, yes, 0, copy0, 0);
+                clear_output();
+                slot(par1, yes, yes, yes, yes, 1, copy0, 0);
+            } else if (ntiles == 1) {
                 slot(par0, yes, no, no, yes, 0, copy0, 0);
+                clear_output();
                 slot(par1, no, yes, no, yes, 1, copy0, 0);
             } else {
                 slot(par0, yes, no, yes, no, 0, copy0, 0);
+                clear_output();
                 slot(par1, yes, yes, yes, no, 1, copy0, 0);
             }
             if constexpr (!C::DIRECT) close_interval(0);
@@ -655,6 +733,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             // A wavefront whose 32 rows all lie past the last query (the ragged last workgroup of a head) only
             // helps to move the tiles: the same loads, stores and barriers, no arithmetic.  Its rows are never
             // stored.
+            clear_output();
             if constexpr (C::DIRECT) {
                 direct_tile(3);
 #pragma unroll 1
@@ -671,7 +750,8 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
                     close_interval(i);
                 }
             }
-            l_run = 1.0f;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) l_run[rb] = 1.0f;
         }
         // the loads of the tiles past the last one write zeros into the ring: they end before it is used for anything else
         if constexpr (C::DIRECT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -688,14 +768,14 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             load_v(0, vst);
             g_off += BN * tok_bytes;
             store_k(0, k0);
-            put_rows(smem + C::S_OFF + rg * 32 * C::KROW, x);
-            static_assert(KG == 1 || C::RG * 32 * C::KROW <= C::ST_BYTES, "the query rows pass through the state's room");
+            put_rows(smem + C::S_OFF + rg * WR * C::KROW, x);
+            static_assert(KG == 1 || C::RG * WR * C::KROW <= C::ST_BYTES, "the query rows pass through the state's room");
             store_k(1, k1);
         }
         lds_barrier();
         if (EARLY_STATE && Sg != nullptr) load_state();      // arrives under the first products
         if (q0 < Lq) {
-            get_rows(smem + C::S_OFF + rg * 32 * C::KROW);
+            get_rows(smem + C::S_OFF + rg * WR * C::KROW);
             square_rows();
             first_product();
             lds_barrier();            // every wavefront has read K(0), whose stage slot 0 overwrites, and its query rows
@@ -720,9 +800,12 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             // two the largest form of this function does not fit the registers.
             if constexpr (ONE_ENDING) {
                 if ((j & 1) == 0) {
-                    s_acc[1] = s_acc[0];
-                    pf[0] = pf[2];
-                    pf[1] = pf[3];
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) {
+                        s_acc[1][rb] = s_acc[0][rb];
+                        pf[0][rb][0] = pf[1][rb][0];
+                        pf[0][rb][1] = pf[1][rb][1];
+                    }
                 }
                 slot(par1, no, yes, no, yes, j, copy4, j & 1);
                 last_product(par1, j);
@@ -742,29 +825,36 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
                 static_for<0, 2 * C::KCH>([&](auto p_) { copy_part(j & 1, p_); });
                 lds_barrier();
             }
-            l_run = 1.0f;
-            m_run = 0.f;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                l_run[rb] = 1.0f;
+                m_run[rb] = 0.f;
+            }
         }
     }
 
     // ---- epilogue ------------------------------------------------------------------------
     // The output blocks that this wavefront finishes: all of its rows' features, or with several key groups a share of
     // them, after the groups' partial results (each relative to its own maximum) have been exchanged through LDS.
-    f32x16 out[C::DBW];
+    f32x16 out[C::DBW][RB];
     const int db0 = KG == 1 ? 0 : C::DBW * kg;
-    l_run = xhalf_sum(l_run);
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) l_run[rb] = xhalf_sum(l_run[rb]);
     if constexpr (KG == 1) {
-        const float inv_l = 1.0f / l_run;
 #pragma unroll
-        for (int db = 0; db < C::DB; ++db)
+        for (int rb = 0; rb < RB; ++rb) {
+            const float inv_l = 1.0f / l_run[rb];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) out[db][r] = o_acc[db][r] * inv_l;
+            for (int db = 0; db < C::DB; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) out[db][rb][r] = o_acc[db][rb][r] * inv_l;
+        }
     } else {
-        static_assert(KG <= 2, "the exchange is written for two key groups");
+        static_assert(KG <= 2 && (KG == 1 || RB == 1), "the exchange is written for two key groups of 32 rows");
         float *ml = (float *)(smem + C::ML_OFF);                       // [wavefront][maximum, sum][row]
         f32x4 *ox = (f32x4 *)smem;                                     // [wavefront][block][register quad][lane]
         const int peer = wave ^ C::RG;
-        ml[(wave * 2 + hh) * 32 + c] = hh ? l_run : m_run;
+        ml[(wave * 2 + hh) * 32 + c] = hh ? l_run[0] : m_run[0];
         __syncthreads();                                               // the ring is no longer read
 #pragma unroll
         for (int i = 0; i < C::DBW; ++i)
@@ -772,13 +862,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             for (int q = 0; q < 4; ++q) {                              // the peer's blocks go to the peer
                 f32x4 x;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = kg ? o_acc[i][4 * q + e] : o_acc[C::DBW + i][4 * q + e];
+                for (int e = 0; e < 4; ++e) x[e] = kg ? o_acc[i][0][4 * q + e] : o_acc[C::DBW + i][0][4 * q + e];
                 ox[((wave * C::DBW + i) * 4 + q) * 64 + lane] = x;
             }
         const float m_peer = ml[peer * 2 * 32 + c], l_peer = ml[(peer * 2 + 1) * 32 + c];
-        const float mm = fmaxf(m_run, m_peer);
-        const float f0 = __builtin_amdgcn_exp2f(m_run - mm), f1 = __builtin_amdgcn_exp2f(m_peer - mm);
-        const float inv_l = 1.0f / fmaf(l_run, f0, l_peer * f1);
+        const float mm = fmaxf(m_run[0], m_peer);
+        const float f0 = __builtin_amdgcn_exp2f(m_run[0] - mm), f1 = __builtin_amdgcn_exp2f(m_peer - mm);
+        const float inv_l = 1.0f / fmaf(l_run[0], f0, l_peer * f1);
         const float f = f0 * inv_l, f_peer = f1 * inv_l;
         __syncthreads();
 #pragma unroll
@@ -788,16 +878,20 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
                 const f32x4 x = ox[((peer * C::DBW + i) * 4 + q) * 64 + lane];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    out[i][4 * q + e] = fmaf(kg ? o_acc[C::DBW + i][4 * q + e] : o_acc[i][4 * q + e], f, x[e] * f_peer);
+                    out[i][0][4 * q + e] = fmaf(kg ? o_acc[C::DBW + i][0][4 * q + e] : o_acc[i][0][4 * q + e], f, x[e] * f_peer);
             }
     }
 
     if (Sg != nullptr) {
-        const size_t gtok = (size_t)b * Lq + (qrow < Lq ? qrow : 0);
-        const size_t gi = a.g_per_token ? gtok : gtok * H + h;
-        float g_row = 1.0f;                                   // requested here, used after the products
-        if (a.g != nullptr && !a.g_per_element)
-            g_row = a.g_is_bf16 ? (float)((const bf16_t *)a.g)[gi] : ((const float *)a.g)[gi];
+        size_t gi[RB];
+        float g_row[RB];                                      // requested here, used after the products
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            gi[rb] = a.g_per_token ? row_token(rb) : row_token(rb) * H + h;
+            g_row[rb] = 1.0f;
+            if (a.g != nullptr && !a.g_per_element)
+                g_row[rb] = a.g_is_bf16 ? (float)((const bf16_t *)a.g)[gi[rb]] : ((const float *)a.g)[gi[rb]];
+        }
         // O_inter^T[e][q] = sum_d S[d][e] * q[q][d]: the fp32 state is split into bf16 hi + lo parts
         // (fp32 accumulate), both staged row-major [d][e] in LDS and read as S^T fragments through the
         // transposing LDS read, exactly like V.
@@ -814,13 +908,14 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
         // wavefront stages the rotation table rows of its 32 tokens in a region of its own: read straight
         // from global memory, fragment by fragment, these operands cost ~13 us of cache-line requests.
         if constexpr (FUSED_MAP) {
-            bf16x8 xf[C::KS];
+            bf16x8 xf[RB][C::KS];
             load_rows((const bf16_t *)a.xq, xf);
             unsigned char *smW = smem;                                           // D/2 rows of Wq[h], KROW bytes each
-            float *cosT = (float *)(smem + C::WH_BYTES + rg * C::TAB_BYTES);   // [32][TST] tables of this wavefront's rows
-            float *sinT = cosT + 32 * C::TST;
+            float *cosT = (float *)(smem + C::WH_BYTES + rg * C::TAB_BYTES);   // [WR][TST] tables of this wavefront's rows
+            float *sinT = cosT + WR * C::TST;
             const bool rope = a.cs != nullptr;
-            qss = 0.f;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) qss[rb] = 0.f;
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 __syncthreads();                      // the K/V ring (or the previous half of Wq) is no longer read
@@ -851,36 +946,45 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
 #pragma unroll
                 for (int e2 = 0; e2 < C::DB / 2; ++e2) {
                     const int eb = half * (C::DB / 2) + e2;
-                    f32x16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+                    f32x16 acc[RB];
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[rb][r] = 0.f;
 #pragma unroll
                     for (int t = 0; t < C::KS; ++t) {
                         const bf16x8 wf = *(const bf16x8 *)(smW + (32 * e2 + c) * C::KROW + 32 * t + 16 * hh);
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, xf[t], acc, 0, 0, 0);
+#pragma unroll
+                        for (int rb = 0; rb < RB; ++rb) acc[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, xf[rb][t], acc[rb], 0, 0, 0);
                     }
-                    if (rope) {
 #pragma unroll
-                        for (int j4 = 0; j4 < 4; ++j4) {      // registers 4 j4 .. +3: features 32 eb + 8 j4 + 4 hh + 0..3
-                            const f32x2 c2 = *(const f32x2 *)(cosT + c * C::TST + 16 * eb + 4 * j4 + 2 * hh);
-                            const f32x2 s2 = *(const f32x2 *)(sinT + c * C::TST + 16 * eb + 4 * j4 + 2 * hh);
+                    for (int rb = 0; rb < RB; ++rb) {
+                        if (rope) {
 #pragma unroll
-                            for (int p = 0; p < 2; ++p) {
-                                const float y0 = acc[4 * j4 + 2 * p], y1 = acc[4 * j4 + 2 * p + 1];
-                                acc[4 * j4 + 2 * p] = y0 * c2[p] - y1 * s2[p];
-                                acc[4 * j4 + 2 * p + 1] = fmaf(y0, s2[p], y1 * c2[p]);
+                            for (int j4 = 0; j4 < 4; ++j4) {      // registers 4 j4 .. +3: features 32 eb + 8 j4 + 4 hh + 0..3
+                                const f32x2 c2 = *(const f32x2 *)(cosT + (32 * rb + c) * C::TST + 16 * eb + 4 * j4 + 2 * hh);
+                                const f32x2 s2 = *(const f32x2 *)(sinT + (32 * rb + c) * C::TST + 16 * eb + 4 * j4 + 2 * hh);
+#pragma unroll
+                                for (int p = 0; p < 2; ++p) {
+                                    const float y0 = acc[rb][4 * j4 + 2 * p], y1 = acc[rb][4 * j4 + 2 * p + 1];
+                                    acc[rb][4 * j4 + 2 * p] = y0 * c2[p] - y1 * s2[p];
+                                    acc[rb][4 * j4 + 2 * p + 1] = fmaf(y0, s2[p], y1 * c2[p]);
+                                }
                             }
                         }
+#pragma unroll
+                        for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+                            for (int j = 0; j < 8; ++j) {
+                                const bf16_t y = to_bf16(acc[rb][8 * tt + j]);
+                                qf[rb][2 * eb + tt][j] = y;
+                                qss[rb] = fmaf((float)y, (float)y, qss[rb]);
+                            }
                     }
-#pragma unroll
-                    for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            const bf16_t y = to_bf16(acc[8 * tt + j]);
-                            qf[2 * eb + tt][j] = y;
-                            qss = fmaf((float)y, (float)y, qss);
-                        }
                 }
             }
-            qss = xhalf_sum(qss);
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) qss[rb] = xhalf_sum(qss[rb]);
         }
         if constexpr (!EARLY_STATE) {
             __syncthreads();                              // every wave is done with the K/V ring
@@ -888,11 +992,13 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             store_state();
             __syncthreads();
         }
-        f32x16 inter[C::DBW];
+        f32x16 inter[C::DBW][RB];
 #pragma unroll
         for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) inter[db][r] = 0.f;
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) inter[db][rb][r] = 0.f;
         // k-slot j of half-wave hh must be d = 16t + 8hh + j to match q fragments loaded from memory, and
         // d = 16t + 8(j/4) + 4hh + j%4 to match fragments that were accumulator registers (fused feature map)
         const int s_row = FUSED_MAP ? ((lane & 15) >> 2) + 4 * hh : 8 * hh + ((lane & 15) >> 2);
@@ -904,36 +1010,41 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             for (int db = 0; db < C::DBW; ++db) {
                 const unsigned char *p = smHi + s_frag_off + 16 * t * C::VROW + 64 * (db0 + db);
                 const bf16x8 sh = lds_read_tr_pair(p, s_second), sl = lds_read_tr_pair(p + C::SS_BYTES, s_second);
-                inter[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sh, qf[t], inter[db], 0, 0, 0);
-                inter[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sl, qf[t], inter[db], 0, 0, 0);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) inter[db][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sh, qf[rb][t], inter[db][rb], 0, 0, 0);
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) inter[db][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(sl, qf[rb][t], inter[db][rb], 0, 0, 0);
             }
-        const float gq = (1.0f / sqrtf(qss + a.l2_eps)) * g_row;       // gate * L2 norm scale for this lane's query row
-        if (a.g != nullptr && a.g_per_element) {
-            // one gate per output feature: registers 4 j .. 4 j + 3 of block db are features 32 db + 8 j + 4 hh + 0..3
 #pragma unroll
-            for (int db = 0; db < C::DBW; ++db)
+        for (int rb = 0; rb < RB; ++rb) {
+            const float gq = (1.0f / sqrtf(qss[rb] + a.l2_eps)) * g_row[rb];       // gate * L2 norm scale for this lane's query row
+            if (a.g != nullptr && a.g_per_element) {
+                // one gate per output feature: registers 4 j .. 4 j + 3 of block db are features 32 db + 8 j + 4 hh + 0..3
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const size_t ge = gi * D + 32 * (db0 + db) + 8 * j + 4 * hh;
-                    float g4[4];
-                    if (a.g_is_bf16) {
-                        const bf16x4 x = *(const bf16x4 *)((const bf16_t *)a.g + ge);
+                for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) g4[i] = (float)x[i];
-                    } else {
-                        const f32x4 x = *(const f32x4 *)((const float *)a.g + ge);
+                    for (int j = 0; j < 4; ++j) {
+                        const size_t ge = gi[rb] * D + 32 * (db0 + db) + 8 * j + 4 * hh;
+                        float g4[4];
+                        if (a.g_is_bf16) {
+                            const bf16x4 x = *(const bf16x4 *)((const bf16_t *)a.g + ge);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) g4[i] = x[i];
+                            for (int i = 0; i < 4; ++i) g4[i] = (float)x[i];
+                        } else {
+                            const f32x4 x = *(const f32x4 *)((const float *)a.g + ge);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) g4[i] = x[i];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            out[db][rb][4 * j + i] = fmaf(gq * g4[i], inter[db][rb][4 * j + i], out[db][rb][4 * j + i]);
                     }
+            } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        out[db][4 * j + i] = fmaf(gq * g4[i], inter[db][4 * j + i], out[db][4 * j + i]);
-                }
-        } else {
+                for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
-            for (int db = 0; db < C::DBW; ++db)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) out[db][r] = fmaf(gq, inter[db][r], out[db][r]);
+                    for (int r = 0; r < 16; ++r) out[db][rb][r] = fmaf(gq, inter[db][rb][r], out[db][rb][r]);
+            }
         }
     }
 
@@ -941,21 +1052,23 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     // 32 rows x 32 DBW features.  With two key groups the block lies where the wavefront has just read its peer's
     // partial result (nobody else touches that part); with one it may lie where others still read the state.
     constexpr int OROW = 64 * C::DBW + 16, OCPR = 4 * C::DBW;          // LDS bytes and 16-byte chunks per row
-    static_assert(32 * OROW <= C::DBW * 16 * 64 * 4, "the block fits the peer's partial result");
-    unsigned char *region = smem + (KG == 1 ? wave * 32 * OROW : (wave ^ C::RG) * (C::DBW * 16 * 64 * 4));
+    static_assert(WR * OROW <= RB * C::DBW * 16 * 64 * 4, "the block fits the peer's partial result");
+    unsigned char *region = smem + (KG == 1 ? wave * WR * OROW : (wave ^ C::RG) * (C::DBW * 16 * 64 * 4));
     if (KG == 1 || FUSED_MAP) __syncthreads();
 #pragma unroll
     for (int db = 0; db < C::DBW; ++db)
 #pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) {
-            bf16x4 w;
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) w[i] = to_bf16(out[db][4 * j4 + i]);
-            *(bf16x4 *)(region + c * OROW + 2 * (32 * db + 8 * j4 + 4 * hh)) = w;
-        }
+            for (int j4 = 0; j4 < 4; ++j4) {
+                bf16x4 w;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = to_bf16(out[db][rb][4 * j4 + i]);
+                *(bf16x4 *)(region + (32 * rb + c) * OROW + 2 * (32 * db + 8 * j4 + 4 * hh)) = w;
+            }
     bf16_t *og = (bf16_t *)a.out;
 #pragma unroll
-    for (int i = 0; i < 32 * OCPR / 64; ++i) {
+    for (int i = 0; i < WR * OCPR / 64; ++i) {
         const int idx = lane + 64 * i;
         const int row = idx / OCPR, col = idx % OCPR;
         const int orow = q0 + row;
@@ -975,13 +1088,31 @@ struct FwdGrid {
     int n_tiles;         // all tiles
     int n_whole;         // kHalvesLast: tiles that are served whole
     int ragged_last;
+    int one_per_cu;      // kWhole, D = 64: workgroups of eight wavefronts with 32 rows each, not of four with 64
+};
+
+// Whole tiles.  D = 128: eight wavefronts of 32 rows, whose accumulators fill the registers.  D = 64: four wavefronts of 64
+// rows, for which every operand fragment read from LDS serves two products, and two workgroups per CU.  While there is at most
+// one tile per CU, where four wavefronts would each be alone on a SIMD, eight of 32 rows here too (12 heads x 64, 4680 tokens,
+// 228 tiles: 76 us, 88 us with four; 3 x 24 heads, 999 tokens, 288 tiles: 28.0 us, 33.3 us with eight; 8 x 12 heads, 4680
+// tokens 566 and 614 us).  The half tiles of a launch's tail have the whole tiles' number of wavefronts.
+template <int D>
+struct Whole {
+    static constexpr int RB = D == 64 ? 2 : 1, NW = 8 / RB;
+    static constexpr int SMEM = FwdCfg<D, 1, RB, NW>::SMEM, SMEM8 = FwdCfg<D, 1, 1, 8>::SMEM;
+    static_assert(D == 128 || SMEM <= 80 * 1024, "two workgroups per CU");
 };
 
 template <int D, FwdSplit SPLIT, bool FUSED_MAP>
-__global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, FwdGrid g, float scale_log2)
+__global__ __launch_bounds__(SPLIT == kWhole || SPLIT == kHalves ? 512 : 64 * Whole<D>::NW, 2)
+void fwd_bf16_kernel(FwdArgs a, FwdGrid g, float scale_log2)
 {
-    constexpr int SMEM1 = FwdCfg<D, 1>::SMEM, SMEM2 = FwdCfg<D, 2>::SMEM;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[SPLIT == kWhole ? SMEM1 : SPLIT == kHalves ? SMEM2 : SMEM1 > SMEM2 ? SMEM1 : SMEM2];
+    constexpr int RB = Whole<D>::RB, NW = SPLIT == kHalves ? 8 : Whole<D>::NW, KH = NW / 4;     // KH: key groups of a half tile
+    constexpr bool TWO_FORMS = SPLIT == kWhole && RB > 1;       // the launch says how much LDS
+    constexpr int SMEM1 = Whole<D>::SMEM, SMEM2 = FwdCfg<D, KH, 1, NW>::SMEM;
+    __shared__ __attribute__((aligned(16))) unsigned char fixed_smem[TWO_FORMS ? 16 : SPLIT == kWhole ? SMEM1 : SPLIT == kHalves ? SMEM2 : SMEM1 > SMEM2 ? SMEM1 : SMEM2];
+    extern __shared__ __attribute__((aligned(16))) unsigned char launch_smem[];
+    unsigned char *smem = TWO_FORMS ? launch_smem : fixed_smem;
     int id = blockIdx.x, half = -1;
     if (SPLIT == kHalvesLast && id >= g.n_whole) {
         const int n_rest = g.n_tiles - g.n_whole;
@@ -1009,13 +1140,19 @@ __global__ __launch_bounds__(NT, 2) void fwd_bf16_kernel(FwdArgs a, FwdGrid g, f
         bh = work / g.n_qtiles;
     }
     if constexpr (SPLIT == kWhole) {
-        fwd_tile<D, 1, FUSED_MAP>(a, scale_log2, bh, qt, smem);
+        if constexpr (TWO_FORMS) {
+            if (g.one_per_cu) {
+                fwd_tile<D, 1, 1, 8, FUSED_MAP>(a, scale_log2, bh, qt, smem);
+                return;
+            }
+        }
+        fwd_tile<D, 1, RB, NW, FUSED_MAP>(a, scale_log2, bh, qt, smem);
     } else if constexpr (SPLIT == kHalves) {
-        fwd_tile<D, 2, FUSED_MAP>(a, scale_log2, bh, qt, smem);
+        fwd_tile<D, KH, 1, NW, FUSED_MAP>(a, scale_log2, bh, qt, smem);
     } else if (half < 0) {
-        fwd_tile<D, 1, FUSED_MAP>(a, scale_log2, bh, qt, smem);
+        fwd_tile<D, 1, RB, NW, FUSED_MAP>(a, scale_log2, bh, qt, smem);
     } else if ((2 * qt + half) * 128 < a.Lq) {
-        fwd_tile<D, 2, FUSED_MAP>(a, scale_log2, bh, 2 * qt + half, smem);
+        fwd_tile<D, KH, 1, NW, FUSED_MAP>(a, scale_log2, bh, 2 * qt + half, smem);
     }
 }
 
@@ -1023,9 +1160,11 @@ template <int D, FwdSplit SPLIT>
 hipError_t launch_fwd(const FwdArgs &a, FwdGrid g, float scale_log2, hipStream_t stream)
 {
     const int n_wg = SPLIT == kHalvesLast ? 2 * g.n_tiles - g.n_whole : g.n_tiles;
-    const dim3 grid((unsigned)n_wg), block(NT);
-    if (a.xq != nullptr) return launch_kernel(fwd_bf16_kernel<D, SPLIT, true>, grid, block, stream, a, g, scale_log2);
-    return launch_kernel(fwd_bf16_kernel<D, SPLIT, false>, grid, block, stream, a, g, scale_log2);
+    const bool eight = SPLIT == kHalves || Whole<D>::NW == 8 || (SPLIT == kWhole && g.one_per_cu);
+    const dim3 grid((unsigned)n_wg), block(eight ? 512 : 256);
+    const unsigned lds = SPLIT != kWhole || Whole<D>::NW == 8 ? 0 : g.one_per_cu ? Whole<D>::SMEM8 : Whole<D>::SMEM;
+    if (a.xq != nullptr) return launch_kernel_lds(fwd_bf16_kernel<D, SPLIT, true>, grid, block, lds, stream, a, g, scale_log2);
+    return launch_kernel_lds(fwd_bf16_kernel<D, SPLIT, false>, grid, block, lds, stream, a, g, scale_log2);
 }
 
 // Whether `tiles` query tiles of up to `rows` rows are faster in half tiles, as far as rows and keys decide it.  A half tile
@@ -1053,7 +1192,7 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
     const long long heads = (long long)a.B * a.H;
     const long long q256 = (a.Lq + 255) / 256, q128 = (a.Lq + 127) / 128;
     if (heads * q128 > 0x3fffffffLL) return hipErrorInvalidValue;
-    FwdGrid g;
+    FwdGrid g = {};
     g.n_qtiles = (int)q256;
     g.n_tiles = g.n_whole = (int)(heads * q256);
     // more workgroups than CUs, a ragged last query tile per head, and whole heads per XCD
@@ -1078,6 +1217,7 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
         g.n_whole = g.n_tiles - rest;
         return launch_fwd<D, kHalvesLast>(a, g, scale_log2, stream);
     }
+    g.one_per_cu = g.n_tiles <= kNumCu;
     return launch_fwd<D, kWhole>(a, g, scale_log2, stream);
 }
 

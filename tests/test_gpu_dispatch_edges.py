@@ -61,11 +61,13 @@ def test_readout_keys_masked_by_infinite_logits(lib, oracle, dtype, B, H, Lq, Lk
 # Readout: half tiles of 128 rows with two key groups while they fit one round (more than 128 rows and two or more key
 # tiles, a last tile with keys for one or both groups), whole tiles of 256 rows beyond or with fewer rows or keys, and whole
 # tiles followed by half tiles when the last round would be at most half full (272 and 544 tiles; a last half tile with and
-# without rows).
+# without rows).  At D = 64 whole tiles are of four wavefronts with 64 rows each from 257 tiles on (rows for one of a wavefront's
+# two blocks, for some of the wavefronts; one key tile).
 @pytest.mark.parametrize("B,H,Lq,Lkv,D", [
     (1, 2, 40, 32, 128), (1, 2, 40, 33, 128), (2, 1, 128, 64, 64), (1, 3, 129, 65, 128), (1, 2, 256, 97, 64), (1, 2, 300, 128, 128),
     (1, 2, 130, 161, 128), (2, 2, 385, 385, 64), (1, 2, 200, 200, 128), (8, 17, 150, 150, 64), (17, 16, 40, 40, 64), (17, 16, 200, 200, 64),
-    (17, 16, 300, 70, 64), (17, 16, 130, 40, 128), (3, 43, 290, 290, 128)])
+    (17, 16, 300, 70, 64), (17, 16, 130, 40, 128), (3, 43, 290, 290, 128), (17, 16, 1, 64, 64), (17, 16, 65, 65, 64), (17, 16, 193, 193, 64),
+    (43, 6, 257, 129, 64), (65, 4, 129, 20, 64)])
 def test_readout_tile_splits(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
     w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"split_{B}_{H}_{Lq}_{Lkv}_{D}", B=B, H=H, L=Lq, D=D)
     q, _, _, g = W.pass_inputs(w, 0, 0)
