@@ -750,8 +750,8 @@ __global__ __launch_bounds__(512) void gdn_walk8_kernel(GdnArgs a, const unsigne
     const int col = 32 * cb + c32, gcol = 64 * slice + col;          // column within the slice / within the state
     float *Sg = a.S + (size_t)bh * D * D + gcol;
 
-    // S is exchanged as [column][16-byte chunk]: chunk x of column n lies at x ^ n % 16, on which neither the 16-column
-    // fragment reads nor the writes have bank conflicts (padded rows had: 43 % of the kernel's LDS cycles)
+    // S is exchanged as [column][16-byte chunk]: chunk x of column n lies at x ^ n % 16, without bank conflicts for the
+    // 16-column fragment reads (with padded columns 43 % of the kernel's LDS cycles were conflicts, 25 % are: the writes of R)
     const int s_wr = col * SROW + 16 * ((4 * rbF) ^ (col & 15)) + 8 * hh, s_rd = (32 * cb + c16) * SROW + 16 * (g ^ c16);
     f32x16 s_acc;
 #pragma unroll
