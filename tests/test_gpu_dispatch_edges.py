@@ -111,6 +111,28 @@ def test_readout_key_ring(lib, oracle, B, H, Lq, Lkv, D):  # noqa: F811
     assert e <= TOL_BF16_OUT, f"{e:.3e}"
 
 
+# Whole tiles at D = 64 take their LDS at launch, one size per form: also in a captured graph, several replays between other work.
+@pytest.mark.parametrize("B,H,L", [(2, 30, 600), (3, 43, 600)])
+def test_readout_in_a_graph_with_lds_of_the_launch(lib, B, H, L):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"graph_{B}_{H}_{L}", B=B, H=H, L=L, D=64)
+    q, k, v, _ = (dev(x) for x in W.pass_inputs(w, 0, 0))
+    out, ref = torch.zeros_like(q), torch.empty_like(q)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        lib.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lib.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    for i in range(3):
+        q.mul_(0.5)
+        out.zero_()
+        lib.arl2_hybrid_attn_fwd(q, k, v, None, None, ref)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), i
+
+
 # Delta rule: tiles of 64 (D = 128) or 128 (D = 64) tokens shared by two or four token groups, one split per CU as far as
 # heads, tiles and the workspace allow (one tile, a ragged tile of one group, several rounds of the load ring, more heads
 # than CUs).
