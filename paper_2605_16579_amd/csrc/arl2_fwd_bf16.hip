@@ -1159,7 +1159,8 @@ void fwd_bf16_kernel(FwdArgs a, FwdGrid g, float scale_log2)
 template <int D, FwdSplit SPLIT>
 hipError_t launch_fwd(const FwdArgs &a, FwdGrid g, float scale_log2, hipStream_t stream)
 {
-    const int n_wg = SPLIT == kHalvesLast ? 2 * g.n_tiles - g.n_whole : g.n_tiles;
+    // (a tile of up to 128 rows has no second half)
+    const int n_wg = SPLIT == kHalvesLast && a.Lq > 128 ? 2 * g.n_tiles - g.n_whole : g.n_tiles;
     const bool eight = SPLIT == kHalves || Whole<D>::NW == 8 || (SPLIT == kWhole && g.one_per_cu);
     const dim3 grid((unsigned)n_wg), block(eight ? 512 : 256);
     const unsigned lds = SPLIT != kWhole || Whole<D>::NW == 8 ? 0 : g.one_per_cu ? Whole<D>::SMEM8 : Whole<D>::SMEM;
@@ -1185,6 +1186,23 @@ bool halves_pay(int rows, int keys, long long tiles)
     return keys >= (D == 128 ? 10 : 8) * BN;
 }
 
+// D = 64, more 256-row tiles than CUs: whether tiles of 128 rows, four wavefronts with 32 each, serve the whole launch.  Where
+// the 64-row wavefronts of a whole tile find no rows, or only one key tile, they are slower than the eight of 32 rows that
+// they replaced; the small tiles are slower than neither.  In us, softmax alone, eight wavefronts / 64-row ones / small tiles:
+//   up to 128 rows, which leave two of the four 64-row wavefronts without any: 288 heads, 65 rows, 64 keys 7.1 / 8.3 / 5.1; 128
+//     rows, 384 keys 14.0 / 15.9 / 11.1; 512 heads, 128 rows, 640 keys 21.2 / 25.6 / 21.9; 2048 heads, 128 rows, 1024 keys
+//     149 / 136 / 122; up to 64 rows, one wavefront's, it is the other way from eight key tiles on while two rounds of tiles
+//     are not full: 320 heads, 64 rows, 640 keys 18.5 / 15.5 / 16.5; 426 heads, 2048 keys 44.8 / 37.1 / 38.8; 464 heads, 1024
+//     keys 27.8 / 27.7 / 26.4;
+//   one key tile, to which the 64-row wavefronts add an empty one: 200 heads, 384 rows 9.0 / 9.7 / 8.3, 600 rows 12.7 / 13.7 /
+//     10.1; 256 heads, 1000 rows 22.1 / 19.8 / 18.5; beyond four rounds they have made up for it: 768 heads, 1000 rows
+//     57.8 / 46.8 / 48.4.
+bool small_tiles_pay(int rows, int keys, int tiles)
+{
+    if (rows > 128) return keys <= BN && tiles <= 4 * kNumCu;
+    return rows > 64 || keys < 8 * BN || 4 * tiles > 7 * kNumCu;
+}
+
 template <int D>
 hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
 {
@@ -1206,14 +1224,25 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
         g.ragged_last = 0;
         return launch_fwd<D, kHalves>(a, g, scale_log2, stream);
     }
-    // The tail of a launch of several rounds: when at most half of the CUs would have a tile in it, these tiles are
-    // halved.  A half tile takes 0.57 of the time of a whole one, so that 2048 tokens x 66 heads (2.06 rounds) take 156
-    // instead of 172 us, x 64 wide 94 instead of 106 us, 1000 tokens x 272 heads (4.25 rounds) 174 instead of 180 us, and with
-    // the fused map 172, 102 and 200 us instead of 186, 114 and 206 us; nothing changes where more than half of the CUs have
-    // work in the last round.
+    if constexpr (D == 64)
+        if (g.n_tiles > kNumCu && small_tiles_pay(a.Lq, a.Lkv, g.n_tiles)) {
+            g.n_whole = 0;
+            return launch_fwd<D, kHalvesLast>(a, g, scale_log2, stream);
+        }
+    // The tail of a launch of several rounds: when at most half of the CUs would have a tile in it, these tiles are halved.
+    // D = 128: a half tile takes 0.57 of the time of a whole one, so that 2048 tokens x 66 heads (2.06 rounds) take 156 instead
+    // of 172 us, 1000 tokens x 272 heads (4.25 rounds) 174 instead of 180 us, and with the fused map 172 and 200 us instead of
+    // 186 and 206 us.  D = 64, where a half tile has four wavefronts of 32 rows and one key group, and a CU two workgroups that
+    // share its time: 2048 tokens x 66 heads 82.5 instead of 93.9 us, 1000 tokens x 272 heads 79.6 instead of 85.2 us, with the
+    // fused map 92 and 95 instead of 106 and 103 us.  Nothing
+    // changes where more than half of the CUs have work in the last round: 1024 tokens x 100 heads x 64 (1.56 rounds) 35.9 us,
+    // 40.1 us halved.  With up to 128 rows in the tail's tiles the whole ones of D = 64 leave wavefronts idle: 136 heads, 257
+    // rows and keys 13.0 us, 10.6 us halved (10.7 us with eight wavefronts of 32 rows); 192 heads, 384 rows and keys 16.8 and
+    // 13.8 us; so these are halved in a second round for any number of keys, beyond it from halves_pay's line on as at D = 128.
     const int rest = g.n_tiles % kNumCu;
     const int tail_rows = g.ragged_last || q256 == 1 ? (a.Lq - 1) % 256 + 1 : 256;
-    if (g.n_tiles > kNumCu && rest > 0 && 2 * rest <= kNumCu && halves_pay<D>(tail_rows, a.Lkv, rest)) {
+    const bool pays = (D == 64 && tail_rows <= 128 && g.n_tiles <= 2 * kNumCu) || halves_pay<D>(tail_rows, a.Lkv, rest);
+    if (g.n_tiles > kNumCu && rest > 0 && 2 * rest <= kNumCu && pays) {
         g.n_whole = g.n_tiles - rest;
         return launch_fwd<D, kHalvesLast>(a, g, scale_log2, stream);
     }

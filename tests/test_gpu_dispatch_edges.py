@@ -1,5 +1,6 @@
 """GPU parity at the sizes where a kernel's tiles, splits and dispatch rules change over, against the CPU oracle."""
 import dataclasses
+import json
 import re
 
 import numpy as np
@@ -218,6 +219,29 @@ def test_readout_takes_the_faster_tile_split(lib, oracle, B, H, Lq, Lkv, D, spli
     assert e <= TOL_BF16_OUT, f"{e:.3e}"
 
 
+# D = 64, where a whole tile's four wavefronts have 64 rows each and a small one's 32: eight wavefronts up to 256 tiles of 256
+# rows; beyond, small tiles for up to 128 rows (from 65 rows on, with fewer than eight key tiles, or with more than 448 tiles)
+# and for one key tile (up to 1024 tiles); halves behind whole tiles where the last ones have up to 128 rows (up to 512 tiles).
+@pytest.mark.parametrize("B,H,Lq,Lkv,split,threads,workgroups", [
+    (16, 16, 200, 70, 0, 512, 256), (1, 257, 200, 70, 2, 256, 258), (16, 25, 200, 70, 0, 256, 400),
+    (1, 257, 128, 128, 2, 256, 257), (16, 25, 128, 640, 2, 256, 400), (16, 25, 1, 1, 2, 256, 400), (16, 25, 64, 511, 2, 256, 400),
+    (16, 25, 64, 512, 0, 256, 400), (16, 25, 65, 512, 2, 256, 400), (32, 14, 20, 512, 0, 256, 448), (1, 449, 20, 512, 2, 256, 449),
+    (16, 25, 129, 64, 2, 256, 800), (16, 25, 129, 65, 0, 256, 400), (1, 256, 1000, 33, 2, 256, 2048), (41, 5, 1100, 64, 0, 256, 1025),
+    (17, 8, 257, 257, 2, 256, 288), (24, 8, 384, 200, 2, 256, 512), (25, 8, 384, 200, 0, 256, 400)])
+def test_readout_small_tiles(lib, oracle, tmp_path, B, H, Lq, Lkv, split, threads, workgroups):  # noqa: F811
+    w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"small_{B}_{H}_{Lq}_{Lkv}", B=B, H=H, L=Lq, D=64)
+    q, _, _, _ = W.pass_inputs(w, 0, 0)
+    k, v = (W.normal(5, w, (B, Lkv, H, 64), tag) for tag in (1, 2))
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+        out = gpu_fwd(lib, q, k, v, None, None)
+    prof.export_chrome_trace(str(tmp_path / "trace.json"))
+    kernels = [e for e in json.loads((tmp_path / "trace.json").read_text())["traceEvents"] if "fwd_bf16_kernel" in e.get("name", "") and "grid" in e.get("args", {})]
+    assert len(kernels) == 1 and re.search(rf"<64, [^,]*\){split}, false>", kernels[0]["name"]), kernels
+    assert kernels[0]["args"]["block"][0] == threads and kernels[0]["args"]["grid"][0] == workgroups, kernels
+    e = rel_err(to_np(out), oracle.fwd(to_np(q), to_np(k), to_np(v)))
+    assert e <= TOL_BF16_OUT, f"{e:.3e}"
+
+
 # fp32 readout: root mean square error over that of the result.  With `D` products in one chain a rounding random walk gives
 # the linear branch about 2^-24 / sqrt(3) * 0.72 * sqrt(D / 2) (the first two bounds lie below that: 2.0e-7 and 1.4e-7); with
 # logits of +-20 the products of queries and keys decide, where a kernel with 16 partial sums per row has 7.8e-7.
@@ -233,9 +257,10 @@ def test_fp32_readout_error(lib, oracle, D, scale, state, bound):  # noqa: F811
 
 
 # Gates of every granularity and type, the linear branch's own query and the fused map, in each form of the readout: halves
-# (two key groups that finish a share of the features each), whole tiles, whole ones and then halves; both head dimensions.
+# (two key groups that finish a share of the features each), whole tiles, whole ones and then halves, small tiles of D = 64; both
+# head dimensions.
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("B,H,L", [(1, 2, 130), (8, 17, 150), (17, 16, 200)])
+@pytest.mark.parametrize("B,H,L", [(1, 2, 130), (8, 17, 150), (17, 16, 200), (16, 17, 100)])
 def test_readout_gates_in_every_tile_split(lib, oracle, B, H, L, D):  # noqa: F811
     w = dataclasses.replace(W.WORKLOADS["ragged_small"], name=f"gates_{B}_{H}_{L}_{D}", B=B, H=H, L=L, D=D)
     q, k, v, _ = W.pass_inputs(w, 0, 0)
