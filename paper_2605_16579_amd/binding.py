@@ -3,13 +3,16 @@ others and of what is to be refused through ctypes.
 
 Every step of the hybrid attention path runs in the HIP kernels of ``libarl2_hip.so``;
 torch is used for device memory and streams.  There is no fallback: if the library is
-missing or a call fails, an exception is raised.
+missing or a call fails, an exception is raised.  Without the compiled module, or with one
+built for another Python or torch, every call is marshalled through ctypes, with a warning.
 """
 from __future__ import annotations
 
 import ctypes
 import importlib.util
 import os
+import sys
+import warnings
 from typing import Optional
 
 import torch
@@ -17,6 +20,7 @@ import torch
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libarl2_hip.so")
 HOST_PATH = os.path.join(_PKG, "_arl2_host.so")
+HOST_FOR = f"Python {sys.version_info[0]}.{sys.version_info[1]}, torch {torch.__version__}"     # what the compiled module is built for
 
 ARL2_OK, ARL2_ERR_INVALID_ARG, ARL2_ERR_UNSUPPORTED, ARL2_ERR_WORKSPACE, ARL2_ERR_DEVICE = range(5)
 ARL2_F32, ARL2_BF16 = 0, 1
@@ -43,18 +47,36 @@ class Arl2Error(RuntimeError):
 
 
 _lib = None
-_host_call = None     # _arl2_host.call
+_host_call = None     # _arl2_host.call, or _no_host_call
 _addr = {}            # entry point -> its address in _lib
+
+
+def _no_host_call(*args) -> None:
+    """In the place of _arl2_host.call: no call is a plain one."""
+    return None
+
+
+def _load_host_call():
+    try:
+        spec = importlib.util.spec_from_file_location("_arl2_host", HOST_PATH)
+        host = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(host)
+        if host.built_for != HOST_FOR:
+            raise ImportError(f"built for {host.built_for}, this is {HOST_FOR}")
+        return host.call
+    except (ImportError, OSError, AttributeError) as e:
+        warnings.warn(f"{HOST_PATH}: {e}; calls go through ctypes and take longer to issue "
+                      "(run `python -m paper_2605_16579_amd.build`)", RuntimeWarning, stacklevel=3)
+        return _no_host_call
 
 
 def load_library() -> ctypes.CDLL:
     """Loads the built library (build it first with ``python -m paper_2605_16579_amd.build``)."""
     global _lib, _host_call
     if _lib is None:
-        for path in (LIB_PATH, HOST_PATH):
-            if not os.path.exists(path):
-                raise FileNotFoundError(
-                    f"{path} is missing: run `python -m paper_2605_16579_amd.build` (there is no fallback path)")
+        if not os.path.exists(LIB_PATH):
+            raise FileNotFoundError(
+                f"{LIB_PATH} is missing: run `python -m paper_2605_16579_amd.build` (there is no fallback path)")
         lib = ctypes.CDLL(LIB_PATH)
         vp = ctypes.c_void_p
         dp = ctypes.POINTER(arl2_desc)
@@ -90,11 +112,9 @@ def load_library() -> ctypes.CDLL:
         lib.arl2_last_error.restype = ctypes.c_char_p
         lib.arl2_version.argtypes = []
         lib.arl2_version.restype = ctypes.c_int
-        spec = importlib.util.spec_from_file_location("_arl2_host", HOST_PATH)
-        host = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(host)
         _addr.update({name: ctypes.cast(getattr(lib, name), vp).value for name in EXPORTS})
-        _lib, _host_call = lib, host.call
+        _host_call = _load_host_call()
+        _lib = lib                        # last: another thread that sees it finds the rest
     return _lib
 
 

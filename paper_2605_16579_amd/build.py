@@ -24,8 +24,11 @@ def build_host(verbose: bool = False) -> str:
     import torch
     from torch.utils import cpp_extension
 
+    from paper_2605_16579_amd.binding import HOST_FOR
+
     lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
-    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd = ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DARL2_HOST_FOR="{HOST_FOR}"']
     for path in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", path]
     cmd += ["-o", HOST, os.path.join(CSRC, "arl2_host.cpp"), "-L", lib_dir, "-lc10", "-ltorch_cpu", "-ltorch_python"]

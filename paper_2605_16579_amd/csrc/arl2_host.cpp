@@ -140,4 +140,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_arl2_host", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__arl2_host(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__arl2_host(void)
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_for", ARL2_HOST_FOR) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,4 +1,6 @@
 """Shared helpers of the GPU parity tests (no arithmetic of the method lives here)."""
+import os
+
 import numpy as np
 import torch
 
@@ -8,6 +10,15 @@ import workloads as W
 TOL_BF16_OUT = 2e-2     # bf16 outputs
 TOL_STATE = 1e-4        # fp32 state, also after 64 chained commits
 TOL_F32 = 1e-5          # fp32-throughout configuration
+
+
+def built_package():
+    """The package, built first where one of its two binaries is missing (they are not under version control)."""
+    import paper_2605_16579_amd as A
+    if not all(os.path.exists(path) for path in (A.binding.LIB_PATH, A.binding.HOST_PATH)):
+        from paper_2605_16579_amd import build
+        build.build()
+    return A
 
 
 def rel_err(got, ref) -> float:

@@ -4,7 +4,14 @@ import pytest
 import torch
 
 import paper_2605_16579_amd as A
+from helpers import built_package
 from paper_2605_16579_amd import binding
+
+
+@pytest.fixture(autouse=True, scope="module")
+def built():
+    built_package().load_library()
+    assert binding._host_call is not binding._no_host_call
 
 
 class Checked(torch.Tensor):
@@ -102,3 +109,21 @@ def test_plain_calls_leave_everything_else_to_the_checked_path():
         assert binding._host_call(addr, *args) is None, args
     with pytest.raises(ValueError):
         A.arl2_hybrid_attn_fwd(q, q, q, None, None, q)
+
+
+def test_without_the_compiled_module_every_call_is_marshalled_in_python(monkeypatch, tmp_path):
+    broken = tmp_path / "broken.so"
+    broken.write_bytes(b"no shared object")
+    q = torch.zeros((1, 8, 2, 64), dtype=torch.bfloat16)
+    for name, value, why in (("HOST_PATH", str(tmp_path / "missing.so"), "missing"), ("HOST_PATH", str(broken), "broken"),
+                             ("HOST_FOR", "Python 2.7, torch 0.1", "this is Python 2.7")):
+        with monkeypatch.context() as m:
+            m.setattr(binding, "_lib", None)
+            m.setattr(binding, "_host_call", None)
+            m.setattr(binding, name, value)
+            with pytest.warns(RuntimeWarning, match=why):
+                lib = A.load_library()
+            assert binding._host_call is binding._no_host_call
+            assert A.arl2_version() == lib.arl2_version() >= 100
+            with pytest.raises(ValueError, match="q must live in device memory"):
+                A.arl2_hybrid_attn_fwd(q, q, q, None, None, q)

@@ -6,15 +6,14 @@ import re
 
 import pytest
 
+from helpers import built_package
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(scope="module")
 def A():
-    import paper_2605_16579_amd as A
-    if not os.path.exists(A.binding.LIB_PATH):
-        from paper_2605_16579_amd import build
-        build.build()
+    A = built_package()
     A.load_library()
     return A
 

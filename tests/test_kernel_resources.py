@@ -1,8 +1,9 @@
 """What the compiler gave the kernels, read from the code objects' metadata in the built library (no GPU needed)."""
-import os
 import re
 
 import pytest
+
+from helpers import built_package
 
 
 def scratch_per_kernel(path):
@@ -15,11 +16,7 @@ def scratch_per_kernel(path):
 
 @pytest.fixture(scope="module")
 def scratch():
-    import paper_2605_16579_amd as A
-    if not os.path.exists(A.binding.LIB_PATH):
-        from paper_2605_16579_amd import build
-        build.build()
-    return scratch_per_kernel(A.binding.LIB_PATH)
+    return scratch_per_kernel(built_package().binding.LIB_PATH)
 
 
 def test_readout_kernels_use_no_scratch(scratch):
