@@ -4,7 +4,7 @@
 //
 // None means that something is not as a plain call has it (another type than torch.Tensor, not in device memory, not
 // contiguous, another shape or type): nothing has been called, and the Python binding goes through its own checks, which
-// raise what is to be raised.  One character of `kinds` per tensor says what it must be; None stands for NULL:
+// raise what is to be raised.  One character of `kinds` per tensor says what it must be; None stands for NULL except for k:
 //   q  [B][Lq][H][D], the inputs' type (the first tensor, which names the sizes and the type)      k  [B][Lkv][H][D], likewise
 //   S  [B][H][D][D] fp32    W  [H][D][D], the inputs' type    r  [Lq][D/2] fp32    a  [B][H] fp32    t  [B][Lq][H] fp32
 //   g  [B][Lq][H], [B][Lq] or [B][Lq][H][D], fp32 or bf16: sets the descriptor's gate mode and type
@@ -42,7 +42,7 @@ const at::Tensor *plain(PyObject *o)
 bool check(Checked &c, char kind, PyObject *o, int i)
 {
     arl2_desc &d = c.d;
-    if (o == Py_None && i > 0) return true;
+    if (o == Py_None && i > 0) return kind != 'k';      // (keys name a size: the binding's checks refuse None)
     const at::Tensor *t = plain(o);
     if (t == nullptr) return false;
     const int type = type_code(*t);

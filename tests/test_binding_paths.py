@@ -74,6 +74,16 @@ def outcome(fn, ts, **kw):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_plain_and_checked_calls_agree_about_none(dtype):
+    for name, (fn, ts, _) in calls("cuda", 64, dtype).items():
+        for i in range(1, len(ts)):
+            args = ts[:i] + [None] + ts[i + 1:]
+            assert outcome(fn, args) == outcome(fn, [args[0].as_subclass(Checked)] + args[1:]), (name, i)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("D", [64, 128])
 def test_plain_and_checked_calls_agree(D, dtype):
     for name, (fn, ts, written) in calls("cuda", D, dtype).items():
