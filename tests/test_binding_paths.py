@@ -1,5 +1,7 @@
 """The binding's two ways into the C ABI, the compiled one for plain calls and the checked one behind it, accept, refuse and
 compute the same."""
+import inspect
+
 import pytest
 import torch
 
@@ -85,22 +87,36 @@ def test_plain_and_checked_calls_agree_about_none(dtype):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("D", [64, 128])
-def test_plain_and_checked_calls_agree(D, dtype):
+def test_plain_and_checked_calls_agree(D, dtype, monkeypatch):
+    seen, host_call = [], binding._host_call
+
+    def recorded(*args):
+        seen.append(host_call(*args))
+        return seen[-1]
+
+    monkeypatch.setattr(binding, "_host_call", recorded)
     for name, (fn, ts, written) in calls("cuda", D, dtype).items():
         start = [ts[i].clone() for i in written]
 
-        def results(args, **kw):
+        def results(args, status, **kw):
             for i, x in zip(written, start):
                 ts[i].copy_(x)
+            seen.clear()
             assert outcome(fn, args, **kw) is None, name
+            assert seen == [status], name              # the compiled way was taken, or left
             torch.cuda.synchronize()
             return [ts[i].clone() for i in written]
 
         checked = [ts[0].as_subclass(Checked)] + ts[1:]
-        for kw in ({}, {"stream": torch.cuda.current_stream().cuda_stream}):
-            plain = results(ts, **kw)
-            assert all(torch.equal(a, b) for a, b in zip(plain, results(checked, **kw))), name
+        scales = {key: x for key, x in (("sm_scale", 0.3), ("l2_eps", 0.5)) if key in inspect.signature(fn).parameters}
+        for kw in ({}, {"stream": torch.cuda.current_stream().cuda_stream}, scales):
+            plain = results(ts, 0, **kw)
+            assert all(torch.equal(a, b) for a, b in zip(plain, results(checked, None, **kw))), name
             assert all(not torch.equal(a, b) for a, b in zip(plain, start)), name
+            if kw is not scales:
+                usual = plain
+            elif kw:
+                assert all(not torch.equal(a, b) for a, b in zip(plain, usual)), name
         for i, bad in wrong(ts):
             got = outcome(fn, bad)
             assert got is not None, (name, i)
