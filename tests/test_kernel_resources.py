@@ -1,4 +1,7 @@
-"""What the compiler gave the kernels, read from the code objects' metadata in the built library (no GPU needed)."""
+"""What the compiler gave the kernels, read from the code objects' metadata in the built library, and what it is told about inline
+assembly (no GPU needed)."""
+import glob
+import os
 import re
 
 import pytest
@@ -24,3 +27,15 @@ def test_readout_kernels_use_no_scratch(scratch):
     # bf16: two head dimensions, three tile splits, with and without the fused map; fp32: two head dimensions
     assert len(readouts) == 12 + 2, sorted(scratch)
     assert not any(readouts.values()), {name: n for name, n in readouts.items() if n}
+
+
+def test_assembly_that_needs_m0_is_given_it_or_hands_it_back():
+    csrc = os.path.join(os.path.dirname(built_package().binding.LIB_PATH), "csrc")
+    statements = [a for path in sorted(glob.glob(os.path.join(csrc, "*"))) for a in re.findall(r"asm volatile\((.*?)\);", open(path).read(), re.S)]
+    needing = [a for a in statements if re.search(r"buffer_load_\w+ .* lds", a)]
+    assert len(needing) >= 2
+    for a in needing:          # the compiler does not honour "m0" in a list of clobbers
+        if '"{m0}"' in a:
+            assert " m0," not in a, a
+        else:
+            assert re.search(r'"s_mov_b32 (%\d), m0\\n.*s_mov_b32 m0, \1"', a, re.S), a
