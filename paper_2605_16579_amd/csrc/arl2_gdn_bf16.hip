@@ -961,8 +961,9 @@ static hipError_t launch_gdn(const GdnArgs &a, int nblk, unsigned nwg, hipStream
         if constexpr (D == 128)
             return launch_kernel(gdn_walk8_kernel<false>, dim3(owners8 * NSL), dim3(512), stream, a, recs, nblk, 1,
                                  (unsigned char *)nullptr);
-        return launch_kernel(gdn_walk_kernel<D, false>, dim3(owners8 * NSL), dim3(256), stream, a, recs, nblk, 1,
-                             (unsigned char *)nullptr);
+        else
+            return launch_kernel(gdn_walk_kernel<D, false>, dim3(owners8 * NSL), dim3(256), stream, a, recs, nblk, 1,
+                                 (unsigned char *)nullptr);
     }
     // the runs after the first (c and M slices), then the first runs (c slices)
     const unsigned late8 = (unsigned)((heads * (groups - 1) + kNumXcd - 1) / kNumXcd * kNumXcd);

@@ -29,6 +29,12 @@ def test_readout_kernels_use_no_scratch(scratch):
     assert not any(readouts.values()), {name: n for name, n in readouts.items() if n}
 
 
+def test_no_walk_kernel_that_nothing_launches(scratch):
+    walks = [name for name in scratch if "gdn_walk" in name]
+    # four wavefronts at D = 64 and eight at D = 128, each with one run of blocks and with several
+    assert len(walks) == 4 and not any("gdn_walk_kernelILi128E" in name for name in walks), walks
+
+
 def test_assembly_that_needs_m0_is_given_it_or_hands_it_back():
     csrc = os.path.join(os.path.dirname(built_package().binding.LIB_PATH), "csrc")
     statements = [a for path in sorted(glob.glob(os.path.join(csrc, "*"))) for a in re.findall(r"asm volatile\((.*?)\);", open(path).read(), re.S)]
