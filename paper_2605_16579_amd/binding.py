@@ -1,5 +1,5 @@
 """Binding of the C ABI in ``include/arl2.h``: argument marshalling only, of plain calls in ``csrc/arl2_host.cpp``, of the
-others and of what is to be refused through ctypes.
+others, of the gate projection's and of what is to be refused through ctypes.
 
 Every step of the hybrid attention path runs in the HIP kernels of ``libarl2_hip.so``;
 torch is used for device memory and streams.  There is no fallback: if the library is

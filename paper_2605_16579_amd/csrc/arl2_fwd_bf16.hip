@@ -2,8 +2,10 @@
 //   out = softmax(q k^T * sm_scale) v + g * L2Norm(q) S            paper Eq. (2), (3), (5), (6)
 //
 // One workgroup owns 256 query rows of one (stream, head): eight wavefronts with 32 of them each, or at D = 64 four with 64
-// (`Whole`), or half a tile, 128 rows, with two wavefronts on the same rows and half of every key tile each.  A SIMD has two
-// wavefronts, of one workgroup or two, with 256 registers each.  Everything is computed transposed so that no operand is re-laid out between the two GEMMs:
+// (`Whole`); or half a tile, 128 rows: eight wavefronts, two on the same rows with half of every key tile each (two key
+// groups), or in launches of more tiles than CUs at D = 64 four with 32 rows each and one key group.  A SIMD has two
+// wavefronts, of one workgroup or two, with 256 registers each.  Everything is computed transposed so that no operand is
+// re-laid out between the two GEMMs:
 //
 //   S^T[kv][q]  = K[kv][:] . Q[q][:]      A = K tile rows from LDS,  B = Q fragments in registers
 //   O^T[d][q]  += V^T[d][kv] . P^T[kv][q] A = V^T fragments from LDS, B = exp'd S^T accumulators
@@ -17,9 +19,11 @@
 //
 // The unit of the schedule is a slot, the softmax of one 32-key block beside the first GEMM of the next block and the
 // second GEMM of the previous one (see `slot`).  K/V tiles travel (buffer loads, zero beyond the last key) into an LDS
-// ring with one workgroup barrier per tile: straight, requested two barriers ahead, or through registers (half tiles, and
-// eight wavefronts at D = 64, where that is the faster by up to 3 %).  12 heads x 128, 14400 keys: 1.51 us per 64-key tile straight, 1.61 us through registers (on zeros, where power
-// does not bound it, 1.09 and 1.15 us).  The softmax is optimistic: the running maximum
+// ring with one workgroup barrier per tile: straight, requested two barriers ahead, or through registers (two key groups, and
+// eight wavefronts at D = 64, where that is the faster by up to 3 %).  12 heads x 128, 14400 keys: 1.51 us per 64-key tile
+// straight, 1.61 us through registers (on zeros, where power does not bound it, 1.09 and 1.15 us).  At 65 to 400 rows and
+// 64 KB or more from token to token (256 heads x 128) straight copies are the slower by up to 7 %; 192 heads, 257 to 700 rows
+// are 2 to 4 % the faster.  The softmax is optimistic: the running maximum
 // starts as the first block's, probabilities are taken relative to it as it stands, and only when a lane's share of
 // the row sum shows that a logit exceeded it by more than ~2^7 is the block maximum computed, the running maximum
 // raised, the accumulators rescaled and the block redone.  This removes the per-block maximum reduction and the
@@ -35,7 +39,7 @@
 // directly.  The gate is one value per (token, head) (Eq. (6)), per token, or per output feature.
 //
 // What bounds it: the matrix cores and, on real data, the power they draw (a launch that fills the chip holds the
-// clock at 1.73 GHz).  Measured for one pass with state and gate, 12 heads x 128:
+// clock at 1.73 to 1.83 GHz, by card).  Measured for one pass with state and gate, 12 heads x 128:
 //   4680 tokens (228 tiles of 256 rows)   123 us; 3 x 24 heads x 64, 999 tokens (288 tiles) 28 us; 1560 tokens (156 half tiles) 26.5 us, 38 us with 84 whole tiles;
 //   2 x 3 heads, 328 tokens (18 half tiles) 11.9 us, 15.6 us with 12 whole ones (17 us with query rows loaded fragment by
 //   fragment, the tiles of the prologue one after the other and the first block's exponentials computed twice).
@@ -74,7 +78,7 @@ struct FwdCfg {
     static constexpr int ST_BYTES = 2 * SS_BYTES;
     static constexpr int SCH = (D * CPR + NT - 1) / NT;   // 8-float state pieces per thread
     static constexpr int OUT_BYTES = BM * KROW;  // output staging [q][e]
-    // fused feature map: half of Wq[h] (D/2 rows) plus, per wavefront, the rotation tables of its 32 tokens
+    // fused feature map: half of Wq[h] (D/2 rows) plus, per wavefront, the rotation tables of its tokens
     static constexpr int WH_BYTES = (D / 2) * KROW;
     static constexpr int TST = D / 2 + 2;        // floats per staged table row (conflict-free 8-byte reads)
     static constexpr int TAB_BYTES = 2 * WR * TST * 4;
@@ -139,7 +143,7 @@ __device__ __forceinline__ void direct_barrier()
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
-// Query tile qt (of 256 / KG rows) of (stream, head) bh, by one workgroup.
+// Query tile qt (of FwdCfg's BM rows) of (stream, head) bh, by one workgroup.
 template <int D, int KG, int RB, int NW, bool FUSED_MAP>
 __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int bh, int qt, unsigned char *smem)
 {
@@ -730,7 +734,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
             }
             last_product(par1, 2 * ntiles - 1);
         } else {
-            // A wavefront whose 32 rows all lie past the last query (the ragged last workgroup of a head) only
+            // A wavefront whose rows all lie past the last query (the ragged last workgroup of a head) only
             // helps to move the tiles: the same loads, stores and barriers, no arithmetic.  Its rows are never
             // stored.
             clear_output();
@@ -1049,7 +1053,7 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     }
 
     // Transpose through LDS so that rows are written as contiguous 16-byte pieces, each wavefront its own block of
-    // 32 rows x 32 DBW features.  With two key groups the block lies where the wavefront has just read its peer's
+    // WR rows x 32 DBW features.  With two key groups the block lies where the wavefront has just read its peer's
     // partial result (nobody else touches that part); with one it may lie where others still read the state.
     constexpr int OROW = 64 * C::DBW + 16, OCPR = 4 * C::DBW;          // LDS bytes and 16-byte chunks per row
     static_assert(WR * OROW <= RB * C::DBW * 16 * 64 * 4, "the block fits the peer's partial result");
@@ -1079,8 +1083,8 @@ __device__ __forceinline__ void fwd_tile(const FwdArgs &a, float scale_log2, int
     }
 }
 
-// How the workgroups of a launch divide the query tiles: whole 256-row tiles, half tiles of 128 rows with two key
-// groups, or whole tiles first and half ones at the end.
+// How the workgroups of a launch divide the query tiles: whole 256-row tiles, half tiles of 128 rows with two key groups, or
+// whole tiles first (D = 64: or none) and half ones behind them, which at D = 64 have one key group.
 enum FwdSplit { kWhole, kHalves, kHalvesLast };
 
 struct FwdGrid {
@@ -1093,9 +1097,10 @@ struct FwdGrid {
 
 // Whole tiles.  D = 128: eight wavefronts of 32 rows, whose accumulators fill the registers.  D = 64: four wavefronts of 64
 // rows, for which every operand fragment read from LDS serves two products, and two workgroups per CU.  While there is at most
-// one tile per CU, where four wavefronts would each be alone on a SIMD, eight of 32 rows here too (12 heads x 64, 4680 tokens,
-// 228 tiles: 76 us, 88 us with four; 3 x 24 heads, 999 tokens, 288 tiles: 28.0 us, 33.3 us with eight; 8 x 12 heads, 4680
-// tokens 566 and 614 us).  The half tiles of a launch's tail have the whole tiles' number of wavefronts.
+// one tile per CU, where four wavefronts would each be alone on a SIMD, eight of 32 rows here too.  With a state, tails
+// halved, eight wavefronts and four: 12 heads x 64, 4680 tokens (228 tiles) 77 and 82 us; 3 x 24 heads, 999 tokens (288 tiles)
+// 33.3 and 27.6 us; 8 x 12 heads, 4680 tokens 579 and 529 us.
+// The half tiles behind whole ones have the whole tiles' number of wavefronts, at D = 64 four, and with that one key group.
 template <int D>
 struct Whole {
     static constexpr int RB = D == 64 ? 2 : 1, NW = 8 / RB;
@@ -1168,9 +1173,9 @@ hipError_t launch_fwd(const FwdArgs &a, FwdGrid g, float scale_log2, hipStream_t
     return launch_kernel_lds(fwd_bf16_kernel<D, SPLIT, false>, grid, block, lds, stream, a, g, scale_log2);
 }
 
-// Whether `tiles` query tiles of up to `rows` rows are faster in half tiles, as far as rows and keys decide it.  A half tile
-// has a longer start and end (two key groups and their exchange); what it shortens is the key loop.  Half against whole
-// tiles, in us, softmax alone (with a state, gate or fused map the lines are the same):
+// Whether `tiles` query tiles of up to `rows` rows are faster in half tiles of two key groups, as far as rows and keys decide
+// it.  Such a half tile has a longer start and end (the key groups' exchange); what it shortens is the key loop.  Half against
+// whole tiles of eight wavefronts, in us, softmax alone (with a state, gate or fused map the lines are the same):
 //   more than 128 rows, so that halving makes more workgroups: from two key tiles on (128 heads x 128, 200 rows: 64 keys
 //     7.7 and 7.4, 65 keys 7.6 and 8.5; x 64: 5.7 and 5.3, 5.7 and 6.1);
 //   up to 128 rows, where two wavefronts share a loop and nothing else is gained: 24 heads x 128, 128 rows: 384 keys 9.6
@@ -1232,13 +1237,14 @@ hipError_t launch_fwd(const FwdArgs &a, hipStream_t stream)
     // The tail of a launch of several rounds: when at most half of the CUs would have a tile in it, these tiles are halved.
     // D = 128: a half tile takes 0.57 of the time of a whole one, so that 2048 tokens x 66 heads (2.06 rounds) take 156 instead
     // of 172 us, 1000 tokens x 272 heads (4.25 rounds) 174 instead of 180 us, and with the fused map 172 and 200 us instead of
-    // 186 and 206 us.  D = 64, where a half tile has four wavefronts of 32 rows and one key group, and a CU two workgroups that
-    // share its time: 2048 tokens x 66 heads 82.5 instead of 93.9 us, 1000 tokens x 272 heads 79.6 instead of 85.2 us, with the
-    // fused map 92 and 95 instead of 106 and 103 us.  Nothing
-    // changes where more than half of the CUs have work in the last round: 1024 tokens x 100 heads x 64 (1.56 rounds) 35.9 us,
-    // 40.1 us halved.  With up to 128 rows in the tail's tiles the whole ones of D = 64 leave wavefronts idle: 136 heads, 257
-    // rows and keys 13.0 us, 10.6 us halved (10.7 us with eight wavefronts of 32 rows); 192 heads, 384 rows and keys 16.8 and
-    // 13.8 us; so these are halved in a second round for any number of keys, beyond it from halves_pay's line on as at D = 128.
+    // 186 and 206 us.  D = 64, where a round is 256 tiles too, as the two workgroups of a CU share its time: 2048 tokens x 66
+    // heads 82.5 instead of 93.9 us, 1000 tokens x 272 heads 79.6 instead of 85.2 us, with the fused map 92 and 95 instead of
+    // 106 and 103 us.  Nothing changes where more than half of the CUs have work in the last round: 1024 tokens x 100 heads x 64
+    // (1.56 rounds) 35.9 us, 40.1 us halved.
+    // With up to 128 rows in the tail's tiles the whole ones of D = 64 leave wavefronts idle: 136 heads, 257 rows and keys
+    // 13.0 us, 10.6 us halved (10.7 us with eight wavefronts of 32 rows); 192 heads, 384 rows and keys 16.8 and 13.8 us; so
+    // these are halved in a second round for any number of keys.  Beyond it the line is halves_pay's, of which D = 64 could do
+    // without: 272 heads, 300 rows, 70 keys (2.13 rounds) 12.5 us, 11.1 us halved (13.7 us with eight wavefronts).
     const int rest = g.n_tiles % kNumCu;
     const int tail_rows = g.ragged_last || q256 == 1 ? (a.Lq - 1) % 256 + 1 : 256;
     const bool pays = (D == 64 && tail_rows <= 128 && g.n_tiles <= 2 * kNumCu) || halves_pay<D>(tail_rows, a.Lkv, rest);

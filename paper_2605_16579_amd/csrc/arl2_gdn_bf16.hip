@@ -90,11 +90,12 @@ __host__ __device__ constexpr size_t gdn_ops_bytes(int D) { return (size_t)CT * 
 
 // Kernel 1: the operands of one block's solve,
 //   S_out = gam S + Z^T (diag(beta) V + diag(-beta gamma- r) (K S)),    Z = (I + A)^-T diag(tail r) K.
-// Bound by latency (loads, the gate products, the inverses, the solve: a chain inside each workgroup), so what counts is
-// how many workgroups a CU holds: 39 KB of LDS (the fp32 matrix takes the place of V once V^T has left) and at most 128
-// registers, four per CU.  The solve itself needs no exchange: fp32 matrix instructions, whose 16 x 16 results are in the
-// register order of the next product's operand, so that a wavefront takes its own features through all four
-// token blocks.
+// Bound by the bytes of its records, half of which are K and V^T once more: 12 heads x 128, 4680 tokens read 32 MB and write
+// 59 MB, 4.3 TB/s, nine tenths of what a large copy reaches.  It takes several workgroups per CU to get there, each a chain
+// (loads, the gate products, the inverses, the solve) that waits for most of its time: 39 KB of LDS (the fp32 matrix takes the
+// place of V once V^T has left) and at most 128 registers, four per CU.  The solve itself needs no exchange: fp32 matrix
+// instructions, whose 16 x 16 results are in the register order of the next product's operand, so that a wavefront takes its
+// own features through all four token blocks.
 // Measured, 12 heads x 128, 4680 tokens (888 workgroups, 86 registers): 21.2 us; 31.1 us with the diagonal systems solved
 // by one thread per feature, hi + lo bf16 updates exchanged through LDS and two workgroups per CU (75 KB of LDS).  8 x 4
 // heads, 2000 tokens: 21.8 against 31.6 us.
