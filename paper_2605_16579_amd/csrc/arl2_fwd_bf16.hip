@@ -128,13 +128,16 @@ constexpr float kRowSumLimit = 4096.0f;
 
 
 // Two kilobytes straight into LDS (16 bytes per lane, lane l to lds + 16 l; the second OFF2 bytes further).  The
-// instruction's offset moves the source address as well, so `off2` is less by as much.  M0 carries the LDS address, of which
-// the compiler is told.  There is no output register: the caller waits on vmcnt before the bytes are read.
+// instruction's offset moves the source address as well, so `off2` is less by as much.  M0 carries the LDS address and is
+// the statement's output, so that the compiler knows it overwritten (it does not honour M0 in a list of clobbers; with the
+// address as an input in M0 whole tiles of D = 128 take 0.2 % longer).  The loads have no output register: the caller waits on
+// vmcnt before the bytes are read.
 template <int OFF2>
 __device__ __forceinline__ void load_pair_to_lds(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t off2, uint32_t lds)
 {
-    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %1, %3, 0 offen lds\n\tbuffer_load_dwordx4 %2, %3, 0 offen offset:%4 lds"
-                 ::"{m0}"(lds), "v"(off), "v"(off2), "s"(rsrc), "n"(OFF2) : "memory");
+    uint32_t m0;
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %4, 0 offen lds\n\tbuffer_load_dwordx4 %3, %4, 0 offen offset:%5 lds"
+                 : "={m0}"(m0) : "s"(lds), "v"(off), "v"(off2), "s"(rsrc), "n"(OFF2) : "memory");
 }
 // Workgroup barrier after all but the last N of this wavefront's loads have arrived, and all of its LDS reads.
 template <int N>

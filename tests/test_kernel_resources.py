@@ -35,13 +35,10 @@ def test_no_walk_kernel_that_nothing_launches(scratch):
     assert len(walks) == 4 and not any("gdn_walk_kernelILi128E" in name for name in walks), walks
 
 
-def test_assembly_that_needs_m0_is_given_it_or_hands_it_back():
+def test_assembly_that_writes_m0_says_so_or_hands_it_back():
     csrc = os.path.join(os.path.dirname(built_package().binding.LIB_PATH), "csrc")
     statements = [a for path in sorted(glob.glob(os.path.join(csrc, "*"))) for a in re.findall(r"asm volatile\((.*?)\);", open(path).read(), re.S)]
-    needing = [a for a in statements if re.search(r"buffer_load_\w+ .* lds", a)]
-    assert len(needing) >= 2
-    for a in needing:          # the compiler does not honour "m0" in a list of clobbers
-        if '"{m0}"' in a:
-            assert " m0," not in a, a
-        else:
-            assert re.search(r'"s_mov_b32 (%\d), m0\\n.*s_mov_b32 m0, \1"', a, re.S), a
+    writing = [a for a in statements if "s_mov_b32 m0," in a]
+    assert len(writing) >= 2
+    for a in writing:          # as an output: the compiler does not honour "m0" in a list of clobbers
+        assert '"={m0}"' in a or re.search(r'"s_mov_b32 (%\d), m0\\n.*s_mov_b32 m0, \1"', a, re.S), a
