@@ -1,0 +1,122 @@
+"""The fp32 readout on sums of two halves: the sizes where its tiles, blocks and dispatch can go wrong, and the values that two halves do not
+stand for, against float64 on the GPU."""
+import pytest
+import torch
+
+import paper_2605_16579_amd as A
+
+pytestmark = pytest.mark.gpu
+
+# Relative 2-norm error: rounding the operands to 23 bits and the fp32 sums give 1e-7 to 2.5e-7 for logits of a few units.
+TOL = 6e-7
+
+
+def draw(seed, *shape):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.randn(shape, generator=g, device="cuda")
+
+
+def exact(q, k, v, S=None, g=None, q_lin=None):
+    """[B, L, H, D] tensors; g broadcasts against the output."""
+    q, k, v = (x.double().transpose(1, 2) for x in (q, k, v))
+    o = torch.softmax((q @ k.transpose(-1, -2).contiguous()) * q.shape[-1] ** -0.5, -1) @ v
+    if S is not None:
+        x = q if q_lin is None else q_lin.double().transpose(1, 2)
+        inter = (x / torch.sqrt((x * x).sum(-1, keepdim=True) + 1e-6)) @ S.double()
+        o = o + (inter if g is None else inter * g.double().transpose(1, 2))
+    return o.transpose(1, 2)
+
+
+def error(got, ref):
+    assert torch.isfinite(got).all()
+    return float((got.double() - ref).norm() / ref.norm())
+
+
+@pytest.mark.parametrize("B,H,Lq,Lkv,D", [
+    (1, 130, 33, 1, 128), (1, 70, 64, 31, 64), (1, 140, 40, 33, 64), (1, 66, 100, 129, 128),     # one block, key groups without one
+    (1, 50, 70, 520, 128), (2, 3, 40, 700, 128), (1, 2, 40, 2050, 64), (1, 60, 257, 384, 64),    # last rows and keys of a tile
+    (3, 8, 1000, 128, 128), (1, 12, 1560, 97, 128), (2, 136, 64, 64, 64)])                         # whole tiles, halved last ones
+def test_softmax(B, H, Lq, Lkv, D):
+    q, k, v = draw(1, B, Lq, H, D), draw(2, B, Lkv, H, D), draw(3, B, Lkv, H, D)
+    out = torch.full_like(q, float("nan"))
+    A.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    e = error(out, exact(q, k, v))
+    assert e <= TOL, f"{e:.2e}"
+
+
+@pytest.mark.parametrize("B,H,L,D,gate,own", [
+    (1, 130, 40, 128, "head", False), (2, 40, 100, 64, "token", True), (1, 66, 130, 128, "element", True), (1, 12, 700, 64, "element", False),
+    (1, 3, 700, 128, None, True)])
+def test_state_gates_and_own_query(B, H, L, D, gate, own):
+    q, k, v, x = (draw(i, B, L, H, D) for i in range(4))
+    S = draw(5, B, H, D, D) * torch.logspace(-3, 3, D, device="cuda")            # columns of every size
+    shape = {"head": (B, L, H), "token": (B, L), "element": (B, L, H, D)}.get(gate)
+    g = None if gate is None else torch.rand(shape, device="cuda")
+    out = torch.full_like(q, float("nan"))
+    if own:
+        A.arl2_hybrid_attn_fwd_ex(q, k, v, x, S, g, out)
+    else:
+        A.arl2_hybrid_attn_fwd(q, k, v, S, g, out)
+    wide = None if g is None else {"head": lambda: g[..., None], "token": lambda: g[..., None, None], "element": lambda: g}[gate]()
+    ref = exact(q, k, v, S, wide, x if own else None)
+    for c in range(0, D, 16):                                                     # (a norm over all columns would only see the largest)
+        e = error(out[..., c:c + 16], ref[..., c:c + 16])
+        assert e <= TOL, f"columns {c}: {e:.2e}"
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("kind", ["small", "large", "outlier first", "outlier later", "large logits", "zero values", "zero then small"])
+def test_values_of_every_size(kind, D):
+    B, H, L = 1, 40, 400
+    q, k, v = (draw(i, B, L, H, D) for i in range(3))
+    if kind == "small":
+        q, k, v = q * 1e-18, k * 1e18, v * 1e-30
+    elif kind == "large":
+        q, k, v = q * 1e15, k * 1e-15, v * 1e30
+    elif kind == "outlier first":
+        v[:, 3] *= 1e6
+        k[:, 3, :, 0] = -1e4                     # almost nobody looks at it
+        q[..., 0] = q[..., 0].abs() + 0.1
+    elif kind == "outlier later":
+        v[:, 300] *= 1e7
+        k[:, 300, :, 1] += 3e3
+    elif kind == "large logits":
+        q = q * 20
+    elif kind == "zero values":
+        v = torch.zeros_like(v)
+    else:
+        k[:, :200] = 0
+        v[:, :200] = 0
+        v *= 1e-5
+    out = torch.full_like(q, float("nan"))
+    A.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    ref = exact(q, k, v)
+    if kind == "zero values":
+        assert (out == 0).all()
+        return
+    rows = (out.double() - ref).norm(dim=-1) / ref.norm(dim=-1)                   # every row by itself
+    big = (q.double().norm(dim=-1) * k.double().norm(dim=-1).amax() * D ** -0.5).clamp(min=1)
+    assert float((rows / big).max()) <= 5e-6, f"{float((rows / big).max()):.2e}"  # fp32 logits: 2^-24 of the largest, and some
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_infinities_and_nan(D):
+    B, H, L = 1, 40, 300
+    q, k, v = (draw(i, B, L, H, D) for i in range(3))
+    q[..., 0] = 1.0
+    k[:, 10:50, :, 0] = -float("inf")            # masked keys
+    out = torch.full_like(q, float("nan"))
+    A.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    keep = [j for j in range(L) if not 10 <= j < 50]
+    e = error(out, exact(q, k[:, keep], v[:, keep]))
+    assert e <= TOL, f"{e:.2e}"
+    k[:, 10:50, :, 0] = 0.0
+    v[0, 7, 3, 5], v[0, 9, 3, 6], v[0, 200, 4, 8], S = float("inf"), float("nan"), -float("inf"), draw(9, B, H, D, D)
+    S[0, 6, 2, 9], S[0, 6, 3, 10] = float("inf"), float("nan")
+    A.arl2_hybrid_attn_fwd(q, k, v, S, None, out)
+    ref = exact(q, k, v, S)
+    assert torch.equal(torch.isnan(out), torch.isnan(ref))
+    assert torch.equal(torch.isinf(out), torch.isinf(ref)) and torch.equal(out[torch.isinf(out)].double(), ref[torch.isinf(ref)])
+    ok = torch.isfinite(ref)
+    assert float((out.double()[ok] - ref[ok]).norm() / ref[ok].norm()) <= TOL
