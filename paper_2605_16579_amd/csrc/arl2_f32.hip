@@ -966,14 +966,19 @@ __global__ __launch_bounds__(512, 2) void fwd_f32_halves_kernel(FwdArgs a, int n
         if (q0 >= a.Lq) return;
         done = fwd_f32_half_tile<D, 16>(a, x2, bh, q0, smem);
     }
-    if (!done) {                                                    // four wavefronts for 32 rows
+    // Four wavefronts for half of the rows each.  All tiles done again, 1560 tokens: 12 heads x 128 192 us (157 on fp32 products alone; 244 with
+    // 32-row tiles left to four of the eight wavefronts), 2 x 16 x 64 240 us (185; 269).
+    if (!done) {
         const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
         constexpr int ML = F32Cfg<D, 32>::NW * 2 * 32 * 4, PART = F32Cfg<D, 32>::SMEM + ML;
-        static_assert(2 * PART <= F32HalfCfg<D, 32>::SMEM, "room for two tiles");
+        static_assert(2 * PART <= F32HalfCfg<D, 32>::SMEM && F32Cfg<D, 16>::SMEM <= F32Cfg<D, 32>::SMEM, "room for two tiles");
         int tid = threadIdx.x & 255;
         asm volatile("" : "+v"(tid));                               // (nothing of the other tile is kept for this one)
         unsigned char *mine = smem + part * PART;
-        fwd_f32_tile<D, 32, true>(a, x2, bh, q0 + 32 * part, end < a.Lq ? end : a.Lq, tid, mine, (float (*)[2][32])(mine + F32Cfg<D, 32>::SMEM));
+        float (*ml)[2][32] = (float (*)[2][32])(mine + F32Cfg<D, 32>::SMEM);
+        if (end > a.Lq) end = a.Lq;
+        if (half < 0) fwd_f32_tile<D, 32, true>(a, x2, bh, q0 + 32 * part, end, tid, mine, ml);
+        else fwd_f32_tile<D, 16, true>(a, x2, bh, q0 + 16 * part, end, tid, mine, ml);
     }
 }
 
