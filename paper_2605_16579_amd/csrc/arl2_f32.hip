@@ -482,11 +482,11 @@ __device__ __forceinline__ Parts split8(F &&x, float s)
     }
     return r;
 }
-// The power of two that takes `most` (>= 0) to 2^e .. 2^(e + 1), and its inverse; 1 is assumed of zero.
+// The power of two that takes `most` (>= 0) to 2^e .. 2^(e + 1), or 2^126 where that is less, and its inverse.  2^126 for zero: what the
+// scale is for is zero throughout, or ends in a sum that is not finite.
 __device__ __forceinline__ f32x2 scale_to(float most, int e)
 {
     int x = (int)(__float_as_uint(most) >> 23);                      // biased exponent
-    if (most == 0.f) x = 127;
     x = x < 127 + e - 126 ? 127 + e - 126 : x > 250 ? 250 : x;       // both powers are normal numbers
     return f32x2{__uint_as_float((uint32_t)(254 + e - x) << 23), __uint_as_float((uint32_t)(x - e) << 23)};
 }
@@ -656,7 +656,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
             lds_barrier();
             return false;
         }
-        sc = x2[0] * q_inv * ks[1];
+        sc = fmaxf(x2[0] * (q_inv * ks[1]), FLT_MIN);               // (not zero: keys past the end have a logit of -inf)
     }
     static_for<0, NLD>([&](auto i_) { static_for<0, 3>([&](auto third_) { put_k(third_, i_, k0[decltype(i_)::value]); }); });
     {

@@ -101,6 +101,20 @@ def test_values_of_every_size(kind, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("size", [1.0, 1e6, 1e9, 1e11])
+@pytest.mark.parametrize("later", [True, False])
+def test_first_keys_zero(size, later, D):
+    """The first 128 keys, from which the scale is taken, say nothing about the others: logits are ordinary whatever the sizes of q and k."""
+    B, H, Lq, Lkv = 1, 40, 400, 401
+    q, k, v = draw(0, B, Lq, H, D) * size, draw(1, B, Lkv, H, D) / size, draw(2, B, Lkv, H, D)
+    k[:, :128 if later else Lkv] = 0
+    out = torch.full_like(q, float("nan"))
+    A.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    e = error(out, exact(q, k, v))
+    assert e <= TOL, f"{e:.2e}"
+
+
+@pytest.mark.parametrize("D", [64, 128])
 def test_infinities_and_nan(D):
     B, H, L = 1, 40, 300
     q, k, v = (draw(i, B, L, H, D) for i in range(3))
