@@ -331,11 +331,13 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // instructions multiply exactly and round an fp32 sum once per 8 or 16 products, the fp32 ones once per product, so the results are
 // closer to 64 bits than with fp32 products (relative 2-norm error at usual logits, with a state 1.57e-7 -> 1.23e-7 at D = 128 and 1.21e-7 ->
 // 1.13e-7 at D = 64, softmax alone over 777 keys 3.0e-7 -> 2.2e-7 and 2.0e-7).  The scales keep lo parts normal numbers: query rows
-// have one each, keys and values one per tile from the largest value of its first 128 keys, with room for values 64 times as
-// large, probabilities 2^12.  What has no such parts is found out and done again on the fp32 instructions, by the same
-// workgroup: infinities, NaN and values beyond the room (they end in a sum that is not finite), values so small beside the
-// largest that what lo lacks would show in the output (`fits`), and logits that may exceed 32 in powers of two, where the missing bit
-// would weigh more than the roundings saved (logits of +-20: 6.7e-7 against 5.2e-7).
+// have one each, the keys of a tile one from the largest of its first 128, with room for 64 times as large ones, each feature of the
+// values, which is an output of its own, one from its largest among those keys, with room for 32 times as large ones, probabilities 2^15.
+// What has no such parts is found out and done again on the fp32 instructions, by the same workgroup: infinities, NaN and values beyond the
+// room (they end in a sum that is not finite); rows whose output is so small beside the scales that what lo lacks would show (`fits`);
+// features whose values fall far below their scale for a few blocks (`look_for_lost`); and logits that may exceed 32 in powers of two, where the missing bit
+// would weigh more than the roundings saved (logits of +-20: 6.7e-7 against 5.2e-7).  Single values of a feature among others are
+// exact to 2^-36 of its largest among the first 128 keys.
 //
 // A workgroup owns 64 (or 32) query rows: two row groups of QW rows x four key groups, one wavefront each.  In an iteration a
 // key group takes a block of 32 keys; its two wavefronts bring half of the block each from memory into registers and, as halves,
@@ -446,7 +448,7 @@ __device__ __forceinline__ f32x4 mfma_f16(u32x4 a, u32x4 b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
-constexpr float kPScale = 4096.f;             // probabilities are split times this, so that their lo parts are normal numbers
+constexpr float kPScale = 32768.f;            // probabilities are split times this, the most that halves have room for
 struct Parts {
     u32x4 hi, lo;             // eight halves each
 };
@@ -528,22 +530,23 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     auto k_chunk = [](int r) { return D == 128 ? r & 15 : (r >> 1) & 7; };
     auto v_chunk = [](int r) { return (D == 128 ? 4 * (r & 3) : 4 * ((r >> 1) & 1)) ^ (2 * ((r >> 2) & 1)); };
     // Offsets of the lane's piece of load 0; that of load i lies i RPI rows further, its chunk exchanged by the constants below.
-    float k_scale = 1.f, v_scale = 1.f;
+    float k_scale = 1.f;
+    f32x4 v_scale;
     uint32_t k_put = kg * 2 * C::PART + row0 * (2 * D) + 16 * ((col >> 1) ^ k_chunk(row0)) + 8 * (col & 1);
     uint32_t v_put = C::V_OFF + kg * 2 * C::PART + row0 * (2 * D) + 16 * ((col >> 1) ^ v_chunk(row0)) + 8 * (col & 1);
     uint32_t hi[2];
     float rest[4];
     // Thirds of four values' way from registers to LDS; their lo parts `part` bytes behind the hi ones.
-    auto put = [&](auto third_, const f32x4 &x, float s, uint32_t off, auto part_) {
+    auto put = [&](auto third_, const f32x4 &x, f32x4 s, uint32_t off, auto part_) {
         constexpr int third = decltype(third_)::value, PART = decltype(part_)::value;
         if constexpr (third == 0) {
-            hi[0] = pack_f16(x[0] * s, x[1] * s);
-            hi[1] = pack_f16(x[2] * s, x[3] * s);
+            hi[0] = pack_f16(x[0] * s[0], x[1] * s[1]);
+            hi[1] = pack_f16(x[2] * s[2], x[3] * s[3]);
         } else if constexpr (third == 1) {
-            rest[0] = rest_lo(x[0], s, hi[0]);
-            rest[1] = rest_hi(x[1], s, hi[0]);
-            rest[2] = rest_lo(x[2], s, hi[1]);
-            rest[3] = rest_hi(x[3], s, hi[1]);
+            rest[0] = rest_lo(x[0], s[0], hi[0]);
+            rest[1] = rest_hi(x[1], s[1], hi[0]);
+            rest[2] = rest_lo(x[2], s[2], hi[1]);
+            rest[3] = rest_hi(x[3], s[3], hi[1]);
         } else {
             unsigned char *p = smem + off;
             *(u32x2 *)p = u32x2{hi[0], hi[1]};
@@ -553,35 +556,50 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     const std::integral_constant<int, C::PART> kv_part{};
     auto put_k = [&](auto third_, auto i_, const f32x4 &x) {
         constexpr int i = decltype(i_)::value;
-        put(third_, x, k_scale, (k_put ^ (16 * 2 * i)) + C::RPI * i * (2 * D), kv_part);
+        put(third_, x, f32x4(k_scale), (k_put ^ (16 * 2 * i)) + C::RPI * i * (2 * D), kv_part);
     };
+    uint32_t any[2] = {0, 0}, lost = 0;                             // see `look_for_lost`
     auto put_v = [&](auto third_, auto i_, const f32x4 &x) {
-        constexpr int i = decltype(i_)::value;
+        constexpr int i = decltype(i_)::value, third = decltype(third_)::value;
+        if constexpr (third == 1) {
+            any[0] |= hi[0];
+            any[1] |= hi[1];
+        }
         put(third_, x, v_scale, (v_put ^ (16 * (D == 128 ? 8 * (i & 1) ^ (i & 2) : 2 * (i & 1)))) + C::RPI * i * (2 * D), kv_part);
+    };
+    // Whether all that a lane has seen of a feature, in two or three blocks, is below 2 (2^-9 of what the scale was taken from) and not all of it
+    // is zero: no half has the bit that stands for 2 and more.
+    auto look_for_lost = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            lost |= ((any[i] & 0x3fff3fffu) + 0x3fff3fffu) & ~any[i];
+            any[i] = 0;
+        }
     };
     // B operand of S^T: lane (row c, gr) takes features 8 (NG t + gr) + 0..7 of its row, scaled by a power of two of its own, as
     // halves from LDS rows like those of the keys.  Every wavefront moves an eighth of the rows.
     constexpr int QRW = C::BM / C::NW, NQL = QRW / C::RPI;          // rows and loads per wavefront
     f32x4 qraw[NQL];
-    auto fetch_q = [&](const float *src) {
+    auto fetch_q = [&](const float *src, int ln) {
 #pragma unroll
         for (int i = 0; i < NQL; ++i) {
-            const int r = q0 + QRW * wave + C::RPI * i + lane / C::CPR;
-            qraw[i] = *(const f32x4 *)(src + (((size_t)b * Lq + (r < Lq ? r : Lq - 1)) * H + h) * D + 4 * col);
+            const int r = q0 + QRW * wave + C::RPI * i + ln / C::CPR;
+            qraw[i] = *(const f32x4 *)(src + (((size_t)b * Lq + (r < Lq ? r : Lq - 1)) * H + h) * D + 4 * (ln % C::CPR));
         }
     };
     // info: [row][1 / scale, sum of squares]
-    auto put_q = [&](float *info) {
+    auto put_q = [&](float *info, int ln) {
+        const int cq = ln % C::CPR;
 #pragma unroll
         for (int i = 0; i < NQL; ++i) {
             const f32x4 x = qraw[i];
-            const int r = QRW * wave + C::RPI * i + lane / C::CPR, rr = r % QW;
+            const int r = QRW * wave + C::RPI * i + ln / C::CPR, rr = r % QW;
             const float ss = row_sum<C::CPR>(fmaf(x[0], x[0], x[1] * x[1]) + fmaf(x[2], x[2], x[3] * x[3]));
             const f32x2 s = scale_to(row_max<C::CPR>(fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3])))), 12);
             static_for<0, 3>([&](auto third_) {
-                put(third_, x, s[0], C::Q_OFF + (r / QW) * 2 * C::QPART + rr * (2 * D) + 16 * ((col >> 1) ^ k_chunk(rr)) + 8 * (col & 1), std::integral_constant<int, C::QPART>{});
+                put(third_, x, f32x4(s[0]), C::Q_OFF + (r / QW) * 2 * C::QPART + rr * (2 * D) + 16 * ((cq >> 1) ^ k_chunk(rr)) + 8 * (cq & 1), std::integral_constant<int, C::QPART>{});
             });
-            if (col == 0) *(f32x2 *)(info + 2 * r) = f32x2{s[1], ss};
+            if (cq == 0) *(f32x2 *)(info + 2 * r) = f32x2{s[1], ss};
         }
     };
     // Offsets of the lane's fragments of step 0.
@@ -604,50 +622,38 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         return Parts{__builtin_bit_cast(u32x4, lds_read_tr_pair(p, FPT * 2 * D)), __builtin_bit_cast(u32x4, lds_read_tr_pair(p + C::PART, FPT * 2 * D))};
     };
 
-    // ---- the first blocks, and with them the scales of keys and values
+    // ---- the first blocks, and with them the scale of the keys
     f32x4 raw[NLD], k0[NLD];
     {
         const __amdgpu_buffer_rsrc_t r = rsrc_of(kgl, 0);
 #pragma unroll
         for (int i = 0; i < NLD; ++i) k0[i] = load(r, i);
     }
-    fetch_q((const float *)a.q);
+    fetch_q((const float *)a.q, lane);
     {
         const __amdgpu_buffer_rsrc_t r = rsrc_of(vgl, 0);
 #pragma unroll
         for (int i = 0; i < NLD; ++i) raw[i] = load(r, i);
     }
-    float *ml = (float *)(smem + C::V_OFF), *info = ml + 2 * C::NW;
-    put_q(info);
+    float *ml = (float *)(smem + C::V_OFF), *info = ml + C::NW;
+    put_q(info, lane);
     {
-        float km = 0.f, vm = 0.f;
+        float km = 0.f;
 #pragma unroll
         for (int i = 0; i < NLD; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                km = fmaxf(km, fabsf(k0[i][e]));
-                vm = fmaxf(vm, fabsf(raw[i][e]));
-            }
+            for (int e = 0; e < 4; ++e) km = fmaxf(km, fabsf(k0[i][e]));
         km = swap_max<2>(row_max<32>(km));
-        vm = swap_max<2>(row_max<32>(vm));
-        if (lane == 0) {
-            ml[wave] = km;
-            ml[C::NW + wave] = vm;
-        }
+        if (lane == 0) ml[wave] = km;
     }
     lds_barrier();
-    float sc, o_inv, q_inv = info[2 * (QW * rg + c)], qss = info[2 * (QW * rg + c) + 1];
+    float sc, q_inv = info[2 * (QW * rg + c)], qss = info[2 * (QW * rg + c) + 1];
     {
-        float km = 0.f, vm = 0.f;
+        float km = 0.f;
 #pragma unroll
-        for (int w = 0; w < C::NW; ++w) {
-            km = fmaxf(km, ml[w]);
-            vm = fmaxf(vm, ml[C::NW + w]);
-        }
-        const f32x2 ks = scale_to(km, 9), vs = scale_to(vm, 9);
-        k_scale = ks[0];
-        v_scale = vs[0];
-        o_inv = vs[1] * (1.f / kPScale);
+        for (int w = 0; w < C::NW; ++w) km = fmaxf(km, ml[w]);
+        const f32x2 ks = scale_to(km, 9);
+        k_scale = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(ks[0])));
         float qmost = 0.f;
 #pragma unroll
         for (int r = 0; r < C::BM; r += 32) qmost = fmaxf(qmost, info[2 * (r + (lane & 31)) + 1]);
@@ -780,7 +786,29 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     products(yes, no, rsrc_of(kgl, 0));
     logits(kg);
     m = new_max();
-    lds_barrier();                                                  // the first keys have been read
+    // the scales of the values' features
+    uint64_t zeros;                           // bit i: features 4 i .. 4 i + 3 are zero
+    {
+        float *most = (float *)(smem + C::V_OFF);                   // [wavefront][feature]
+        f32x4 vm = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < NLD; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) vm[e] = fmaxf(vm[e], fabsf(raw[i][e]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vm[e] = swap_max<C::RPI>(vm[e]);
+        if (lane < C::CPR) *(f32x4 *)(most + D * wave + 4 * col) = vm;
+        lds_barrier();                                              // the first keys have been read
+#pragma unroll
+        for (int w = 0; w < C::NW; ++w) {
+            const f32x4 x = *(const f32x4 *)(most + D * w + 4 * col);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) vm[e] = fmaxf(vm[e], x[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v_scale[e] = scale_to(vm[e], 10)[0];
+        zeros = __ballot(vm[0] == 0.f && vm[1] == 0.f && vm[2] == 0.f && vm[3] == 0.f);
+    }
     static_for<0, NLD>([&](auto i_) { static_for<0, 3>([&](auto third_) { put_k(third_, i_, k0[decltype(i_)::value]); }); });
     lds_barrier();
 #pragma unroll 1
@@ -788,6 +816,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         // (one offset of each and not all that they lead to kept over the loop)
         asm volatile("" : "+v"(src0), "+v"(k_off), "+v"(q_off), "+v"(v_off), "+v"(k_put), "+v"(v_put));
         products(yes, yes, rsrc_of(kgl, it + 2));
+        if ((it & 1) != 0 && it != nit - 2) look_for_lost();
         lds_barrier();                                              // the keys have been read, the values are there
         values(yes, NKG * it + kg, rsrc_of(vgl, it + 1));
         if (__any(m_new > m)) {
@@ -800,6 +829,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         lds_barrier();                                              // the values have been read, the next keys are there
     }
     products(no, yes, rsrc_of(kgl, nit));
+    if (nit > 1 || 32 * kg + 32 <= Lkv) look_for_lost();            // (a few keys alone may be small by chance)
     lds_barrier();
     values(no, 0, rsrc_of(kgl, nit));
     lds_barrier();
@@ -819,13 +849,19 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     const size_t gi = a.g_per_token ? gtok : gtok * H + h;
     // ---- merge the four shares: everything relative to the largest maximum
     l = swap_sum<NG>(l);
-    float osq = 0.f;
+    // A lane looks at 16 features of its row at a time.
+    bool fits = (l < INFINITY) & ((lost & 0x40004000u) == 0);
+    constexpr int BPG = 16 / C::RPB;          // blocks with them
+    const uint32_t zero = (uint32_t)zeros >> gr_e;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < DB; db += BPG) {
+        float osq = 0.f;
 #pragma unroll
-        for (int r = 0; r < C::RPB; ++r) osq = fmaf(o[db][r], o[db][r], osq);
-    osq = swap_sum<NG>(osq);
-    const bool fits = osq >= l * (D * 2048.f * kPScale) && osq < INFINITY && l < INFINITY;
+        for (int i = 0; i < 16; ++i) osq = fmaf(o[db + i / C::RPB][i % C::RPB], o[db + i / C::RPB][i % C::RPB], osq);
+        constexpr uint32_t quads = QW == 32 ? 0x55 : 0x1111;
+        const float least = (~zero >> (QW / 4 * db) & quads) == 0 ? 0.f : 8.f * kPScale * kPScale;
+        fits &= (osq >= l * least) & (osq < INFINITY);
+    }
     const bool all_fit = __all(fits);
     ml = (float *)smem;                                             // [wavefront][maximum, sum, fits][row]
     if (gr_e == 0) {
@@ -833,6 +869,10 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         ml[wave * 96 + 32 + c_e] = l;
     }
     if (late == 0) ml[wave * 96 + 64] = all_fit ? 0.f : 1.f;
+    if (wave == 0 && late < C::CPR) {                               // by which each feature of O is too large, to its inverse
+        const u32x4 s = __builtin_bit_cast(u32x4, v_scale);
+        *(u32x4 *)(ml + 96 * C::NW + 4 * (late % C::CPR)) = u32x4{0x7f000000u - s[0], 0x7f000000u - s[1], 0x7f000000u - s[2], 0x7f000000u - s[3]};
+    }
     __syncthreads();
     float misfits = 0.f;
 #pragma unroll
@@ -842,7 +882,10 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     for (int w = 0; w < NKG; ++w) m_all = fmaxf(m_all, ml[(NKG * rg + w) * 96 + c_e]);
 #pragma unroll
     for (int w = 0; w < NKG; ++w) l_all = fmaf(ml[(NKG * rg + w) * 96 + 32 + c_e], pow2_diff(ml[(NKG * rg + w) * 96 + c_e] - m_all, x2[1]), l_all);
-    const float f = pow2_diff(m - m_all, x2[1]) * o_inv;
+    const float f = pow2_diff(m - m_all, x2[1]);
+    f32x4 o_inv[NR / 4];
+#pragma unroll
+    for (int r = 0; r < NR; r += 4) o_inv[r / 4] = *(const f32x4 *)(ml + 96 * C::NW + feature(r));
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(__float_as_int(misfits)) != 0) return false;      // (the same in all wavefronts)
     float *mine = (float *)smem + wave * (DB * C::RPB * 64) + late;                                      // [wavefront][feature block][register][lane]
@@ -853,6 +896,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     __syncthreads();
     const float *shares = (const float *)smem + (NKG * rg * DB * C::RPB + NR * kg) * 64 + late;
     float out[NR];
+    l_all *= kPScale;
     const float inv_l = 1.0f / l_all;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
@@ -861,7 +905,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         for (int w = 0; w < NKG; ++w) sum += shares[(w * DB * C::RPB + r) * 64];
         // sum / l_all, the quotient corrected once
         const float q = sum * inv_l;
-        out[r] = fmaf(fmaf(-q, l_all, sum), inv_l, q);
+        out[r] = fmaf(fmaf(-q, l_all, sum), inv_l, q) * o_inv[r / 4][r & 3];
     }
     float sv[OB][KS][8], g_row = 1.0f;
     if (a.S != nullptr) {
@@ -875,12 +919,12 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
                 for (int i = 0; i < 8; ++i) sv[ob][t][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(Sg, off + 4 * (8 * NG * t + i) * D, 0, 0));
         }
         if (a.g != nullptr && !a.g_per_element) g_row = a.g_is_bf16 ? (float)((const bf16_t *)a.g)[gi] : ((const float *)a.g)[gi];
-        if (a.q_lin != nullptr) fetch_q((const float *)a.q_lin);    // the linear branch's own query (Eq. (3))
+        if (a.q_lin != nullptr) fetch_q((const float *)a.q_lin, late);    // the linear branch's own query (Eq. (3))
     }
     if (a.S != nullptr) {
         if (a.q_lin != nullptr) {
             __syncthreads();                                        // the shares have been read
-            put_q((float *)smem);
+            put_q((float *)smem, late);
             __syncthreads();
             q_inv = ((float *)smem)[2 * (QW * rg + c_e)];
             qss = ((float *)smem)[2 * (QW * rg + c_e) + 1];

@@ -101,6 +101,41 @@ def test_values_of_every_size(kind, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("L", [100, 400, 700])
+@pytest.mark.parametrize("kind", ["logspace", "every second", "constant and noise", "small later", "small then nothing", "zero", "near the smallest"])
+def test_value_features_of_every_size(kind, L, D):
+    """The features of V are outputs of their own: each by itself is as exact as where they are of one size."""
+    B, H = 1, 40
+    q, k, v = (draw(i, B, L, H, D) for i in range(3))
+    if kind == "logspace":
+        v = v * torch.logspace(-10, 3, D, device="cuda")
+    elif kind == "every second":
+        v[..., 1::2] *= 1e-8
+    elif kind == "constant and noise":
+        v *= 1e-8
+        v[..., 3] = 1.0
+    elif kind == "small later":                 # and nearly all that queries look at
+        v[:, 128:, :, 5] *= 1e-7
+        k[..., 0], q[..., 0] = 0.0, 2 * D ** 0.5
+        k[:, :128 if L > 128 else 0, :, 0] = -9.0
+    elif kind == "small then nothing":
+        v[..., 5] *= 1e-7
+        v[:, 40:, :, 5] = 0
+    elif kind == "zero":                         # narrower values in wider rows
+        v[..., D // 2:] = 0
+    else:
+        v *= 1e-37
+    out = torch.full_like(q, float("nan"))
+    A.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    ref = exact(q, k, v)
+    if kind == "zero":
+        assert (out[..., D // 2:] == 0).all()
+        out, ref = out[..., :D // 2], ref[..., :D // 2]
+    e = float(((out.double() - ref).norm(dim=1) / ref.norm(dim=1)).max())         # the worst feature of a head, over its rows
+    assert e <= 2 * TOL, f"{e:.2e}"
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("size", [1.0, 1e6, 1e9, 1e11])
 @pytest.mark.parametrize("later", [True, False])
 def test_first_keys_zero(size, later, D):
