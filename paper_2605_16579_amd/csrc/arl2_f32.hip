@@ -329,14 +329,16 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // x s = hi + lo, s a power of two, hi = half(x s), lo = half(x s - hi): 23 of the 24 bits of an fp32 value (all of every second one's).
 // A product a b is a.hi b.hi + a.hi b.lo + a.lo b.hi; a.lo b.lo, 2^-24 of it, is left out.  The half-precision matrix
 // instructions multiply exactly and round an fp32 sum once per 8 or 16 products, the fp32 ones once per product, so the results are
-// closer to 64 bits than with fp32 products (relative 2-norm error at usual logits, with a state 1.57e-7 -> 1.23e-7 at D = 128 and 1.21e-7 ->
-// 1.13e-7 at D = 64, softmax alone over 777 keys 3.0e-7 -> 2.2e-7 and 2.0e-7).  The scales keep lo parts normal numbers: query rows
+// closer to 64 bits than with fp32 products, from one key to thousands and whatever the size of the logits.  Relative 2-norm errors, fp32 products
+// and this: with a state 1.57e-7 and 1.23e-7 at D = 128, 1.21e-7 and 1.13e-7 at D = 64; softmax alone, D = 128: 33 keys 1.67e-7 and 1.57e-7, 777 keys
+// 3.0e-7 and 2.0e-7, logits four times as large 4.8e-7 and 4.0e-7, queries and keys along one direction with logits of 45 2.5e-6 and 2.4e-6 (with one
+// chain of products over all 128 features 1.75e-7, 2.2e-7, 5.2e-7 and 3.1e-6).  The scales keep lo parts normal numbers: query rows
 // have one each, the keys of a tile one from the largest of its first 128, with room for 64 times as large ones, each feature of the
 // values, which is an output of its own, one from its largest among those keys, with room for 32 times as large ones, probabilities 2^15.
 // What has no such parts is found out and done again on the fp32 instructions, by the same workgroup: infinities, NaN and values beyond the
 // room (they end in a sum that is not finite); rows whose output is so small beside the scales that what lo lacks would show (`fits`);
-// features whose values fall far below their scale for a few blocks (`look_for_lost`); and logits that may exceed 32 in powers of two, where the missing bit
-// would weigh more than the roundings saved (logits of +-20: 6.7e-7 against 5.2e-7).  Single values of a feature among others are
+// features whose values fall far below their scale for a few blocks (`look_for_lost`); and queries so large against the keys' scale that
+// what the smallest parts of keys lack, 2^-35 of the largest, would show in logits (`kLargest`).  Single values of a feature among others are
 // exact to 2^-36 of its largest among the first 128 keys.
 //
 // A workgroup owns 64 (or 32) query rows: two row groups of QW rows x four key groups, one wavefront each.  In an iteration a
@@ -449,6 +451,10 @@ __device__ __forceinline__ f32x4 mfma_f16(u32x4 a, u32x4 b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
 constexpr float kPScale = 32768.f;            // probabilities are split times this, the most that halves have room for
+// Largest key element times longest query, as a logit in powers of two, up to which tiles stay on halves: what lo parts of the keys lack adds 2^-35
+// of that to a logit, here 2^-27.  (It says nothing about the logits, which the keys behind the first 128 may take further: these
+// lack in proportion to their own size.)
+constexpr float kLargest = 256.f;
 struct Parts {
     u32x4 hi, lo;             // eight halves each
 };
@@ -658,7 +664,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
 #pragma unroll
         for (int r = 0; r < C::BM; r += 32) qmost = fmaxf(qmost, info[2 * (r + (lane & 31)) + 1]);
         qmost = row_max<32>(qmost);
-        if (__builtin_amdgcn_readfirstlane(!(km * sqrtf(qmost) * x2[0] < 32.f))) {
+        if (__builtin_amdgcn_readfirstlane(!(km * sqrtf(qmost) * x2[0] < kLargest))) {
             lds_barrier();
             return false;
         }
@@ -680,7 +686,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     float m = -FLT_MAX, l = 0.f;
 
     float s[NL];                              // logits of the block whose softmax is next
-    acc_t sm[NS], sa[NS];                     // those of the block after it: products with a lo part, products of hi parts
+    acc_t sm[NS], sa[2][NS];                  // those of the block after it: products with a lo part, products of hi parts over half of the features each
     Parts pp[NU];                             // its probabilities
     // S^T of a block (S), beside the softmax of the block before it and its values on their way to LDS (P).
     auto products = [&](auto s_, auto p_, __amdgpu_buffer_rsrc_t next) {
@@ -691,7 +697,10 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         Parts kf[2], qf[2];
         float ls[2] = {0.f, 0.f};
         if constexpr (S) {
-            static_for<0, NS>([&](auto kb_) { sm[decltype(kb_)::value] = sa[decltype(kb_)::value] = acc_t(0.f); });
+            static_for<0, NS>([&](auto kb_) {
+                constexpr int kb = decltype(kb_)::value;
+                sm[kb] = sa[0][kb] = sa[1][kb] = acc_t(0.f);
+            });
             kf[0] = k_frag(0, 0);
             qf[0] = q_frag(0);
         }
@@ -705,7 +714,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
                 if constexpr (S) {
                     if constexpr (third == 0) sm[kb] = mfma_f16(k.hi, q.lo, sm[kb]);
                     if constexpr (third == 1) sm[kb] = mfma_f16(k.lo, q.hi, sm[kb]);
-                    if constexpr (third == 2) sa[kb] = mfma_f16(k.hi, q.hi, sa[kb]);
+                    if constexpr (third == 2) sa[2 * t / KS][kb] = mfma_f16(k.hi, q.hi, sa[2 * t / KS][kb]);
                 }
                 if constexpr (P) {
                     static_for<n * NP / N, (n + 1) * NP / N>([&](auto pair_) {
@@ -737,7 +746,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     // The logits out of the accumulators; logit i of a lane is key FPT (i / 4) + 4 gr + i % 4 of the block.
     auto logits = [&](int blk) {
 #pragma unroll
-        for (int i = 0; i < NL; ++i) s[i] = sm[i / C::RPB][i % C::RPB] + sa[i / C::RPB][i % C::RPB];
+        for (int i = 0; i < NL; ++i) s[i] = sm[i / C::RPB][i % C::RPB] + sa[0][i / C::RPB][i % C::RPB] + sa[1][i / C::RPB][i % C::RPB];
         if (32 * blk + 32 > Lkv) {                                  // keys past the end
 #pragma unroll
             for (int i = 0; i < NL; ++i)

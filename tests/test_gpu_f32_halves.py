@@ -45,6 +45,32 @@ def test_softmax(B, H, Lq, Lkv, D):
     assert e <= TOL, f"{e:.2e}"
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Lkv", [33, 64, 128, 700])
+@pytest.mark.parametrize("kind", ["usual", "large logits", "very large logits", "one direction", "larger keys later"])
+def test_no_less_exact_than_fp32_products(kind, Lkv, D):
+    """Against the kernel on fp32 products, which serves launches of up to 32 rows."""
+    B, H, Lq = 1, 40, 256
+    q, k, v = draw(1, B, Lq, H, D), draw(2, B, Lkv, H, D), draw(3, B, Lkv, H, D)
+    if kind == "large logits":
+        q *= 4
+    elif kind == "very large logits":
+        q *= 24
+    elif kind == "one direction":                                                # logits of 23 and 45
+        q, k = 0.3 * q + 2, 0.3 * k + 2
+    elif kind == "larger keys later":
+        k[:, 100:] *= 40
+        q *= 40 ** -0.5
+    ref, out, one = exact(q, k, v), torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    A.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    for r in range(0, Lq, 32):
+        part = torch.empty_like(q[:, r:r + 32].contiguous())
+        A.arl2_hybrid_attn_fwd(q[:, r:r + 32].contiguous(), k, v, None, None, part)
+        one[:, r:r + 32] = part
+    assert not torch.equal(out, one)
+    assert error(out, ref) <= 1.03 * error(one, ref), f"{error(out, ref):.2e} {error(one, ref):.2e}"
+
+
 @pytest.mark.parametrize("B,H,L,D,gate,own", [
     (1, 130, 40, 128, "head", False), (2, 40, 100, 64, "token", True), (1, 66, 130, 128, "element", True), (1, 12, 700, 64, "element", False),
     (1, 3, 700, 128, None, True)])
