@@ -567,13 +567,13 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     uint32_t any[2] = {0, 0}, lost = 0;                             // see `look_for_lost`
     auto put_v = [&](auto third_, auto i_, const f32x4 &x) {
         constexpr int i = decltype(i_)::value, third = decltype(third_)::value;
-        if constexpr (third == 1) {
+        if constexpr (third == 1 && i % (NLD / 4) == 0) {
             any[0] |= hi[0];
             any[1] |= hi[1];
         }
         put(third_, x, v_scale, (v_put ^ (16 * (D == 128 ? 8 * (i & 1) ^ (i & 2) : 2 * (i & 1)))) + C::RPI * i * (2 * D), kv_part);
     };
-    // Whether all that a lane has seen of a feature, in two or three blocks, is below 2 (2^-9 of what the scale was taken from) and not all of it
+    // Whether all that a lane has seen of a feature, four rows each of two or three blocks, is below 2 (2^-9 of what the scale was taken from) and not all of it
     // is zero: no half has the bit that stands for 2 and more.
     auto look_for_lost = [&]() {
 #pragma unroll
@@ -940,7 +940,6 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         }
         const float rq = 1.0f / sqrtf(qss + a.l2_eps);
         float x[NR];
-        bool finite = true;
         static_for<0, OB>([&](auto ob_) {
             constexpr int ob = decltype(ob_)::value;
             float most = 0.f;
@@ -948,8 +947,10 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
             for (int t = 0; t < KS; ++t)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) most = fmaxf(most, fabsf(sv[ob][t][i]));
-            const f32x2 ss = scale_to(swap_max<NG>(most), 12);     // every feature has a scale of its own
-            acc_t small = acc_t(0.f), main = acc_t(0.f);
+            most = swap_max<NG>(most);
+            const f32x2 ss = scale_to(most, 12);     // every feature has a scale of its own
+            const uint32_t zero = most == 0.f ? 0x7bff7bffu : 0u;     // (a feature of zeros lacks nothing)
+            acc_t small = acc_t(0.f), main = acc_t(0.f), sizes = acc_t(0.f);
             static_for<0, KS>([&](auto t_) {
                 constexpr int t = decltype(t_)::value;
                 const Parts sp = split8([&](int i) { return sv[ob][t][i]; }, ss[0]);
@@ -957,27 +958,39 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
                 small = mfma_f16(sp.hi, q.lo, small);
                 small = mfma_f16(sp.lo, q.hi, small);
                 main = mfma_f16(sp.hi, q.hi, main);
+                if constexpr (t % (KS / 2) == 0) sizes = mfma_f16((sp.hi & 0x7fff7fffu) | zero, q.hi & 0x7fff7fffu, sizes);
             });
             main += small;
             constexpr int N = NR < C::RPB ? NR : C::RPB;            // registers of this block
+            auto mine = [&](const acc_t &y, int i) {
+                if constexpr (NR < C::RPB) return r0 == 0 ? y[i] : y[i + NR];
+                else return y[i];
+            };
+            // What the lo parts lack, 2^-26 per feature beside factors of up to 2^13, is less than 2^-25 of products of size 2^16 and more
+            // (which some of the features, at D = 128 a quarter, have to reach).
+            float least = INFINITY, nan = 0.f;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                float y = main[i];
-                if constexpr (NR < C::RPB) y = r0 == 0 ? main[i] : main[i + NR];
                 const float inv = __shfl(ss[1], FPT * ((r0 + i) / 4) + 4 * gr_e + (i & 3), kWave);     // of the lane with that feature
-                x[ob * C::RPB + i] = y * (inv * q_inv);
-                finite &= fabsf(x[ob * C::RPB + i]) < INFINITY;
+                x[ob * C::RPB + i] = mine(main, i) * (inv * q_inv);
+                least = fminf(least, mine(sizes, i));
+                nan = fmaf(x[ob * C::RPB + i], 0.f, nan);          // of infinities too, which are no sums of halves either
+            }
+            if (__any(!(least >= 65536.f && nan == 0.f))) {
+                const float *src = (const float *)(a.q_lin != nullptr ? a.q_lin : a.q) + row_off + 8 * gr_e;
+                acc_t y = acc_t(0.f);
+#pragma unroll
+                for (int t = 0; t < KS; ++t)
+#pragma unroll
+                    for (int i = 0; i < 8; i += 4) {
+                        const f32x4 q4 = *(const f32x4 *)(src + 8 * NG * t + i);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) y = mfma_f32(sv[ob][t][i + j], q4[j], y);
+                    }
+#pragma unroll
+                for (int i = 0; i < N; ++i) x[ob * C::RPB + i] = mine(y, i);
             }
         });
-        if (__any(!finite)) {                    // infinities and NaN in the state are no sums of halves
-            const float *src = (const float *)(a.q_lin != nullptr ? a.q_lin : a.q) + row_off;
-#pragma unroll
-            for (int r = 0; r < NR; ++r) x[r] = 0.f;
-#pragma unroll 1
-            for (int d = 0; d < D; ++d)
-#pragma unroll
-                for (int r = 0; r < NR; ++r) x[r] = fmaf(src[d], a.S[(size_t)bh * D * D + d * D + feature(r)], x[r]);
-        }
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             float g = g_row;                     // headwise or per-token gate, or one gate per output feature

@@ -92,6 +92,38 @@ def test_state_gates_and_own_query(B, H, L, D, gate, own):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("own", [True, False])
+@pytest.mark.parametrize("kind", ["one feature", "large beside small", "zero state", "zero columns and rows", "zero queries"])
+def test_state_entries_of_every_size(kind, own, D):
+    """Every output by itself is as exact as the sizes of the products that it sums allow."""
+    B, H, L = 1, 40, 420
+    q, k, v, x, S = draw(0, B, L, H, D), draw(1, B, L, H, D), draw(2, B, L, H, D), draw(3, B, L, H, D), draw(4, B, H, D, D)
+    v[..., ::2] = 0                              # every second output is the state's alone
+    if kind == "one feature":                    # queries that only see entries far below the others of their columns
+        S[:, :, 1] *= torch.logspace(-20, 0, D, device="cuda")
+        x[..., :1], x[..., 2:] = 0, 0
+    elif kind == "large beside small":
+        x[..., 3] *= 1e7
+        S[:, :, 3] *= 1e-7
+    elif kind == "zero state":
+        S.zero_()
+    elif kind == "zero columns and rows":
+        S[..., D // 4:D // 2], S[:, :, 5:9] = 0, 0
+    else:
+        x[:, 7:100] = 0
+    out = torch.full_like(q, float("nan"))
+    if own:
+        A.arl2_hybrid_attn_fwd_ex(q, k, v, x, S, None, out)
+    else:
+        q = x * 1e-7 if kind == "large beside small" else x                       # (ordinary logits)
+        k[..., 3] *= 1e-3 if kind == "large beside small" else 1
+        A.arl2_hybrid_attn_fwd(q, k, v, S, None, out)
+        x = q
+    ref, size = exact(q, k, v, S, None, x), exact(q, k, v.abs(), S.abs(), None, x.abs())
+    assert ((out.double() - ref).abs() <= 2 ** -20 * size).all(), f"{((out.double() - ref).abs() / size.clamp(min=1e-300)).max():.2e}"
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("kind", ["small", "large", "outlier first", "outlier later", "large logits", "zero values", "zero then small"])
 def test_values_of_every_size(kind, D):
     B, H, L = 1, 40, 400
