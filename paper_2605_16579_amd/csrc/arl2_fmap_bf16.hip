@@ -9,7 +9,7 @@
 // so that a lane ends up with one token's outputs, four consecutive features per register quad: the
 // two members of every rotation pair sit in the same lane.
 //
-// One workgroup owns two (D = 128) or four consecutive heads and one or more tiles of 32 tokens (as many as it takes to run the
+// One workgroup owns two (D = 128) or four consecutive heads and one or more tiles of 32 tokens (often as many as it takes to run the
 // launch as one round of two workgroups per CU).  The rows of its heads are 512 contiguous bytes per token; the workgroups of the other
 // heads of the same tokens run at the same time.  The rotation table of a tile, which all heads share, is staged once per tile.
 // Each of its eight wavefronts keeps 32 rows of one head's W as MFMA A-operand fragments in registers for all its tiles,
@@ -30,10 +30,9 @@ namespace {
 
 constexpr int NT = 512;    // eight wavefronts with 32 output features of a head each
 constexpr int TT = 32;     // tokens per tile
-constexpr int MAX_NTILE = 64;  // most tiles per workgroup (W stays in registers across them)
 
 // PIPE: the x rows of the next tile are requested while the current one is computed (for workgroups that
-// walk several tiles; with a single tile the extra live registers only cost: 8 spill at D = 128).
+// walk several tiles; with a single tile there is none).
 template <int D, bool PIPE>
 __global__ __launch_bounds__(NT, 4) void feature_map_kernel(FmapArgs a, int n_ranges, int n_hg, int ntile)
 {
@@ -214,15 +213,18 @@ hipError_t launch_feature_map_bf16(const FmapArgs &a, hipStream_t stream)
     const int hg = NT / 64 / (a.D / 32);                 // heads per workgroup
     const int n_hg = (a.H + hg - 1) / hg;
     const int tiles = (a.L + TT - 1) / TT;
-    // Two workgroups fit a CU.  Up to that many workgroups run as one round, each walking as many tiles as that takes (8 x 12 heads
-    // x 128, 4680 tokens: 15 tiles and 480 workgroups 52 us, 14 tiles and 528 workgroups, sixteen of them in a second round, 64 us); beyond
-    // MAX_NTILE tiles per workgroup there are enough rounds for the last, partly filled one not to matter.
+    // Two workgroups fit a CU.  That many run as one round, each walking as many tiles as it takes, where that leaves few slots without work;
+    // other launches run in rounds of workgroups with MANY tiles each, enough for W to be read seldom and few enough for the last
+    // round to be short.  In us, D = 128, with rotation, one round and MANY tiles: 8 x 12 heads, 4680 tokens (15 tiles, 480 workgroups)
+    // 57.5 and 59.9, 12 x 12 heads, 4680 (21, 504) 77.4 and 83.2, 8 x 24 heads, 4680 (30, 480) 106 and 106; 12 x 24 heads, 1560 (17, 432) 61
+    // and 58, 16 x 24 heads, 1560 (25, 384) 86 and 73, 43 x 12 heads, 1560 (49, 258) 135 and 95.  Where no round holds all, 16 x 24 heads,
+    // 4680: 5, 16 and 64 tiles 201, 205 and 226, 12 x 24 heads, 6240: 197, 203 and 271.
     const long long slots = 2 * kNumCu;
     const long long groups = (long long)a.B * n_hg;
+    constexpr int MANY = 5, MOST = 24;
     long long ntile = (groups * tiles + slots - 1) / slots;
-    if (ntile < 1) ntile = 1;
-    while (ntile < MAX_NTILE && groups * ((tiles + ntile - 1) / ntile) > slots) ++ntile;
-    if (ntile > MAX_NTILE) ntile = MAX_NTILE;
+    while (ntile <= MOST && groups * ((tiles + ntile - 1) / ntile) > slots) ++ntile;
+    if (ntile > MANY && (ntile > MOST || 100 * groups * tiles < 85 * slots * ntile)) ntile = MANY;
     const int n_ranges = (tiles + (int)ntile - 1) / (int)ntile;
     const long long nwg = (long long)a.B * n_hg * n_ranges;
     if (nwg <= 0 || nwg > 0x7fffffffLL) return hipErrorInvalidValue;

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,H,L,D", [
     (1, 1, 1, 128), (1, 3, 33, 128), (2, 5, 31, 64),           # one tile per workgroup, last head group half empty
     (1, 12, 4680, 128), (1, 9, 6000, 64),                      # two tiles, the last range shorter
-    (8, 5, 3001, 128), (8, 12, 4680, 128), (8, 24, 3120, 128)])    # many; as many workgroups as slots, one round all the same
+    (8, 5, 3001, 128), (8, 12, 4680, 128), (8, 24, 3120, 128),     # many; as many workgroups as slots, one round all the same
+    (16, 24, 1560, 128), (43, 3, 777, 64), (264, 3, 70, 128)])     # rounds of short ranges; more workgroups than slots with one range each
 @pytest.mark.parametrize("rope", [True, False])
 def test_feature_map(B, H, L, D, rope):
     g = torch.Generator(device="cuda")
