@@ -334,12 +334,12 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // 3.0e-7 and 2.0e-7, logits four times as large 4.8e-7 and 4.0e-7, queries and keys along one direction with logits of 45 2.5e-6 and 2.4e-6 (with one
 // chain of products over all 128 features 1.75e-7, 2.2e-7, 5.2e-7 and 3.1e-6).  The scales keep lo parts normal numbers: query rows
 // have one each, the keys of a tile one from the largest of its first 128, with room for 64 times as large ones, each feature of the
-// values, which is an output of its own, one from its largest among those keys, with room for 32 times as large ones, probabilities 2^15.
+// values, which is an output of its own, one from its largest among those keys, with the same room, probabilities 2^15.
 // What has no such parts is found out and done again on the fp32 instructions, by the same workgroup: infinities, NaN and values beyond the
 // room (they end in a sum that is not finite); rows whose output is so small beside the scales that what lo lacks would show (`fits`);
 // features whose values fall far below their scale for a few blocks (`look_for_lost`); and queries so large against the keys' scale that
 // what the smallest parts of keys lack, 2^-35 of the largest, would show in logits (`kLargest`).  Single values of a feature among others are
-// exact to 2^-36 of its largest among the first 128 keys.
+// exact to 2^-35 of its largest among the first 128 keys.
 //
 // A workgroup owns 64 (or 32) query rows: two row groups of QW rows x four key groups, one wavefront each.  In an iteration a
 // key group takes a block of 32 keys; its two wavefronts bring half of the block each from memory into registers and, as halves,
@@ -564,22 +564,23 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         constexpr int i = decltype(i_)::value;
         put(third_, x, f32x4(k_scale), (k_put ^ (16 * 2 * i)) + C::RPI * i * (2 * D), kv_part);
     };
-    uint32_t any[2] = {0, 0}, lost = 0;                             // see `look_for_lost`
     auto put_v = [&](auto third_, auto i_, const f32x4 &x) {
-        constexpr int i = decltype(i_)::value, third = decltype(third_)::value;
-        if constexpr (third == 1 && i % (NLD / 4) == 0) {
-            any[0] |= hi[0];
-            any[1] |= hi[1];
-        }
+        constexpr int i = decltype(i_)::value;
         put(third_, x, v_scale, (v_put ^ (16 * (D == 128 ? 8 * (i & 1) ^ (i & 2) : 2 * (i & 1)))) + C::RPI * i * (2 * D), kv_part);
     };
-    // Whether all that a lane has seen of a feature, four rows each of two or three blocks, is below 2 (2^-9 of what the scale was taken from) and not all of it
-    // is zero: no half has the bit that stands for 2 and more.
+    // The largest value that a lane sees of each of its features in four rows of a block each (no NaN), and whether over two blocks and
+    // more all of it was below 1/2, 2^-10 of what the scale was taken from, and not zero.
+    float seen[4] = {0.f, 0.f, 0.f, 0.f};
+    uint64_t lost = 0;
+    auto look = [&](const f32x4 &x, const f32x4 &y) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(seen[e]) : "v"(x[e]), "v"(y[e]));
+    };
     auto look_for_lost = [&]() {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            lost |= ((any[i] & 0x3fff3fffu) + 0x3fff3fffu) & ~any[i];
-            any[i] = 0;
+        for (int e = 0; e < 4; ++e) {
+            lost |= __ballot(seen[e] > 0.f) & __ballot(seen[e] * v_scale[e] < 0.5f);
+            seen[e] = 0.f;
         }
     };
     // B operand of S^T: lane (row c, gr) takes features 8 (NG t + gr) + 0..7 of its row, scaled by a power of two of its own, as
@@ -736,6 +737,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
                         }
                     });
                     put_v(third_, n_, raw[n]);
+                    if constexpr (third == 1 && n % (NLD / 2) == 0) look(raw[n], raw[n + 1]);
                     if constexpr (third == 2) raw[n] = load(next, n);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -815,7 +817,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
             for (int e = 0; e < 4; ++e) vm[e] = fmaxf(vm[e], x[e]);
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v_scale[e] = scale_to(vm[e], 10)[0];
+        for (int e = 0; e < 4; ++e) v_scale[e] = scale_to(vm[e], 9)[0];
         zeros = __ballot(vm[0] == 0.f && vm[1] == 0.f && vm[2] == 0.f && vm[3] == 0.f);
     }
     static_for<0, NLD>([&](auto i_) { static_for<0, 3>([&](auto third_) { put_k(third_, i_, k0[decltype(i_)::value]); }); });
@@ -859,7 +861,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     // ---- merge the four shares: everything relative to the largest maximum
     l = swap_sum<NG>(l);
     // A lane looks at 16 features of its row at a time.
-    bool fits = (l < INFINITY) & ((lost & 0x40004000u) == 0);
+    bool fits = (l < INFINITY) & ((lost == 0));
     constexpr int BPG = 16 / C::RPB;          // blocks with them
     const uint32_t zero = (uint32_t)zeros >> gr_e;
 #pragma unroll
@@ -1032,8 +1034,10 @@ __global__ __launch_bounds__(512, 2) void fwd_f32_halves_kernel(FwdArgs a, int n
         if (q0 >= a.Lq) return;
         done = fwd_f32_half_tile<D, 16>(a, x2, bh, q0, smem);
     }
-    // Four wavefronts for half of the rows each.  All tiles done again, 1560 tokens: 12 heads x 128 192 us (157 on fp32 products alone; 244 with
-    // 32-row tiles left to four of the eight wavefronts), 2 x 16 x 64 240 us (185; 269).
+    // Four wavefronts for half of the rows each.  All tiles done again, 1560 tokens with a state, found before the key loop (infinite or
+    // outsized first keys) and after it (everything else): 12 heads x 128 192 and 274 us (157 on fp32 products alone), 2 x 16 x 64 239 and 344
+    // us (182).  (With 32-row tiles left to four of the eight wavefronts the first took 244 and 269 us.  A way out before the loop for values too
+    // costs other launches 1-3 %.)
     if (!done) {
         const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
         constexpr int ML = F32Cfg<D, 32>::NW * 2 * 32 * 4, PART = F32Cfg<D, 32>::SMEM + ML;

@@ -165,7 +165,7 @@ def test_values_of_every_size(kind, D):
 
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("L", [100, 400, 700])
-@pytest.mark.parametrize("kind", ["logspace", "every second", "constant and noise", "small later", "small then nothing", "zero", "near the smallest"])
+@pytest.mark.parametrize("kind", ["logspace", "every second", "constant and noise", "small later", "small then nothing", "zero", "near the smallest", "one outlier"])
 def test_value_features_of_every_size(kind, L, D):
     """The features of V are outputs of their own: each by itself is as exact as where they are of one size."""
     B, H = 1, 40
@@ -186,6 +186,8 @@ def test_value_features_of_every_size(kind, L, D):
         v[:, 40:, :, 5] = 0
     elif kind == "zero":                         # narrower values in wider rows
         v[..., D // 2:] = 0
+    elif kind == "one outlier":
+        v[:, 3, :, 5] = 300
     else:
         v *= 1e-37
     out = torch.full_like(q, float("nan"))
