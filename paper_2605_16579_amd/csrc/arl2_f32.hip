@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // x s = hi + lo, s a power of two, hi = half(x s), lo = half(x s - hi): 23 of the 24 bits of an fp32 value (all of every second one's).
 // A product a b is a.hi b.hi + a.hi b.lo + a.lo b.hi; a.lo b.lo, 2^-24 of it, is left out.  The half-precision matrix
 // instructions multiply exactly and round an fp32 sum once per 8 or 16 products, the fp32 ones once per product, so the results are
-// closer to 64 bits than with fp32 products, from one key to thousands and whatever the size of the logits.  Relative 2-norm errors, fp32 products
+// closer to 64 bits than with fp32 products, from 32 keys on (`halves_pay`) and whatever the size of the logits.  Relative 2-norm errors, fp32 products
 // and this: with a state 1.57e-7 and 1.23e-7 at D = 128, 1.21e-7 and 1.13e-7 at D = 64; softmax alone, D = 128: 33 keys 1.67e-7 and 1.57e-7, 777 keys
 // 3.0e-7 and 2.0e-7, logits four times as large 4.8e-7 and 4.0e-7, queries and keys along one direction with logits of 45 2.5e-6 and 2.4e-6 (with one
 // chain of products over all 128 features 1.75e-7, 2.2e-7, 5.2e-7 and 3.1e-6).  The scales keep lo parts normal numbers: query rows
@@ -1171,11 +1171,13 @@ __global__ __launch_bounds__(512, 2) void commit_f32_kernel(CommitArgs a)
 //   beyond: D = 128, 192 tiles 64 keys 10.2 and 8.7, 800 keys 39 and 23; 608 tiles 64 keys 21.6 and 19.5, 800 keys 80 and 54;
 //     D = 64, 192 tiles 64 keys 6.5 and 6.1, 800 keys 21.4 and 15.5; 608 tiles, where three workgroups of the fp32 kernel share a CU: 128
 //     keys 11.1 and 12.3, 200 keys 16.1 and 16.1, 512 keys 27.2 and 23.2;
+//   up to 31 keys: a sum of so few rounds less often than operands lose bits (relative error at D = 128, 1 key 0 and 4.5e-8, 8 keys 1.1e-7 and 1.2e-7,
+//     24 keys 1.5e-7 both), and fp32 products take 13.0 us where halves take 12.3 (60 heads, 250 rows; D = 64: 7.9 and 8.1);
 //   rows that leave a row group empty: up to 32 of them 300 heads x 128, 500 keys 36 and 41; 65 to 96 a third more work.
 bool halves_pay(const FwdArgs &a, long long tiles)
 {
     const int n_rb = (a.Lq + 31) / 32;
-    if (n_rb == 1) return false;
+    if (n_rb == 1 || a.Lkv < 32) return false;
     if (n_rb == 3 && a.Lkv < 512) return false;
     if (a.D == 128) return tiles > kNumCu / 2 || a.Lkv >= 640;
     return tiles > 2 * kNumCu ? a.Lkv >= 384 : tiles > kNumCu / 2 || a.Lkv >= 2048;

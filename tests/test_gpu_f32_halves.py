@@ -46,7 +46,15 @@ def test_softmax(B, H, Lq, Lkv, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("Lkv", [33, 64, 128, 700])
+def test_one_key_is_copied(D):
+    q, k, v = draw(1, 1, 256, 40, D), draw(2, 1, 1, 40, D), draw(3, 1, 1, 40, D)
+    out = torch.full_like(q, float("nan"))
+    A.arl2_hybrid_attn_fwd(q, k, v, None, None, out)
+    assert torch.equal(out, v.expand_as(out))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Lkv", [32, 33, 64, 128, 700])
 @pytest.mark.parametrize("kind", ["usual", "large logits", "very large logits", "one direction", "larger keys later"])
 def test_no_less_exact_than_fp32_products(kind, Lkv, D):
     """Against the kernel on fp32 products, which serves launches of up to 32 rows."""
