@@ -105,7 +105,12 @@ size_t arl2_workspace_bytes(const arl2_desc *desc);
  *   g         device [B][Lq][H]; NULL means a gate of one.
  *   out       device, io_dtype [B][Lq][H][D]; fully overwritten; must not alias an input.
  * bf16 I/O runs on bf16 MFMA with fp32 accumulation and fp32 softmax statistics;
- * fp32 I/O runs in fp32 throughout.
+ * fp32 I/O: sums, softmax statistics and the state are fp32.  Small launches multiply fp32 operands; launches
+ * that fill the chip take every operand as the sum of two scaled halves (23 of its 24 bits) and a product
+ * as three of halves, wherever that is no further from 64-bit arithmetic than fp32 products are; values
+ * that two halves do not stand for (infinities, NaN, sizes too far apart) are found and multiplied in fp32.
+ * What is not found: single values of a feature of v beside ones more than 2^10 times as large, which are
+ * exact to 2^-35 of the largest among the first 128 keys.
  */
 arl2_status arl2_hybrid_attn_fwd(const arl2_desc *desc,
                                  const void *q, const void *k, const void *v,

@@ -1,4 +1,4 @@
-// fp32-throughout variants of the two operations (for fp32 inputs) on gfx950:
+// The two operations for fp32 inputs, on gfx950:
 //   out = softmax(q k^T * sm_scale) v + g * L2Norm(q) S             paper Eq. (2), (3), (5), (6)
 //   S  <- gate * S + sum_i L2Norm(k_i)^T v_i                        paper Eq. (3), Eq. (4)
 // The readout has two kernels.  One is on the fp32 matrix instructions, v_mfma_f32_32x32x2_f32 and 16x16x4_f32, which multiply and

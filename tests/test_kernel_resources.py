@@ -23,9 +23,9 @@ def scratch():
 
 
 def test_readout_kernels_use_no_scratch(scratch):
-    readouts = {name: n for name, n in scratch.items() if "fwd_bf16_kernel" in name or "fwd_f32_kernel" in name}
-    # bf16: two head dimensions, three tile splits, with and without the fused map; fp32: two head dimensions
-    assert len(readouts) == 12 + 2, sorted(scratch)
+    readouts = {name: n for name, n in scratch.items() if any(k in name for k in ("fwd_bf16_kernel", "fwd_f32_kernel", "fwd_f32_halves_kernel"))}
+    # bf16: two head dimensions, three tile splits, with and without the fused map; fp32: two kernels, two head dimensions
+    assert len(readouts) == 12 + 2 + 2, sorted(scratch)
     assert not any(readouts.values()), {name: n for name, n in readouts.items() if n}
 
 
