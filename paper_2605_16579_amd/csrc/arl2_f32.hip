@@ -568,9 +568,9 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         constexpr int i = decltype(i_)::value;
         put(third_, x, v_scale, (v_put ^ (16 * (D == 128 ? 8 * (i & 1) ^ (i & 2) : 2 * (i & 1)))) + C::RPI * i * (2 * D), kv_part);
     };
-    // The largest value that a lane sees of each of its features in four rows of a block each (no NaN), and whether over two blocks and
-    // more all of it was below 1/2, 2^-10 of what the scale was taken from, and not zero.
-    float seen[4] = {0.f, 0.f, 0.f, 0.f};
+    // The largest value that a lane sees of each of its features in two rows of a block each (no NaN; of all the wavefront's rows in the first
+    // block), and whether over three blocks and more, or the first, all of it was below 1/2, 2^-10 of what the scale was taken from, and not zero.
+    float seen[4];
     uint64_t lost = 0;
     auto look = [&](const f32x4 &x, const f32x4 &y) {
 #pragma unroll
@@ -642,7 +642,8 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
 #pragma unroll
         for (int i = 0; i < NLD; ++i) raw[i] = load(r, i);
     }
-    float *ml = (float *)(smem + C::V_OFF), *info = ml + C::NW;
+    float *ml = (float *)(smem + C::V_OFF), *info = ml + C::NW, *most = info + 2 * C::BM;     // most: of every feature of the first values
+    if (tid < D) most[tid] = 0.f;
     put_q(info, lane);
     {
         float km = 0.f;
@@ -737,7 +738,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
                         }
                     });
                     put_v(third_, n_, raw[n]);
-                    if constexpr (third == 1 && n % (NLD / 2) == 0) look(raw[n], raw[n + 1]);
+                    if constexpr (third == 1 && n == 0) look(raw[0], raw[1]);
                     if constexpr (third == 2) raw[n] = load(next, n);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -800,7 +801,6 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     // the scales of the values' features
     uint64_t zeros;                           // bit i: features 4 i .. 4 i + 3 are zero
     {
-        float *most = (float *)(smem + C::V_OFF);                   // [wavefront][feature]
         f32x4 vm = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < NLD; ++i)
@@ -808,26 +808,29 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
             for (int e = 0; e < 4; ++e) vm[e] = fmaxf(vm[e], fabsf(raw[i][e]));
 #pragma unroll
         for (int e = 0; e < 4; ++e) vm[e] = swap_max<C::RPI>(vm[e]);
-        if (lane < C::CPR) *(f32x4 *)(most + D * wave + 4 * col) = vm;
+        if (lane < C::CPR)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) atomicMax((unsigned *)(most + 4 * col + e), __float_as_uint(vm[e]));     // (in the order of what is not negative)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) seen[e] = 32 * kg + 16 * rg + 16 <= Lkv ? vm[e] : INFINITY;         // (a few keys alone may be small by chance)
         lds_barrier();                                              // the first keys have been read
-#pragma unroll
-        for (int w = 0; w < C::NW; ++w) {
-            const f32x4 x = *(const f32x4 *)(most + D * w + 4 * col);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) vm[e] = fmaxf(vm[e], x[e]);
-        }
+        vm = *(const f32x4 *)(most + 4 * col);
 #pragma unroll
         for (int e = 0; e < 4; ++e) v_scale[e] = scale_to(vm[e], 9)[0];
         zeros = __ballot(vm[0] == 0.f && vm[1] == 0.f && vm[2] == 0.f && vm[3] == 0.f);
     }
     static_for<0, NLD>([&](auto i_) { static_for<0, 3>([&](auto third_) { put_k(third_, i_, k0[decltype(i_)::value]); }); });
     lds_barrier();
+    int look_at = nit >= 4 ? 0 : nit;
 #pragma unroll 1
     for (int it = 0; it + 1 < nit; ++it) {
         // (one offset of each and not all that they lead to kept over the loop)
         asm volatile("" : "+v"(src0), "+v"(k_off), "+v"(q_off), "+v"(v_off), "+v"(k_put), "+v"(v_put));
         products(yes, yes, rsrc_of(kgl, it + 2));
-        if ((it & 1) != 0 && it != nit - 2) look_for_lost();
+        if (it == look_at) {
+            look_for_lost();
+            look_at = it + 7 <= nit ? it + 3 : nit;
+        }
         lds_barrier();                                              // the keys have been read, the values are there
         values(yes, NKG * it + kg, rsrc_of(vgl, it + 1));
         if (__any(m_new > m)) {
@@ -840,7 +843,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         lds_barrier();                                              // the values have been read, the next keys are there
     }
     products(no, yes, rsrc_of(kgl, nit));
-    if (nit > 1 || 32 * kg + 32 <= Lkv) look_for_lost();            // (a few keys alone may be small by chance)
+    look_for_lost();
     lds_barrier();
     values(no, 0, rsrc_of(kgl, nit));
     lds_barrier();
@@ -861,7 +864,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     // ---- merge the four shares: everything relative to the largest maximum
     l = swap_sum<NG>(l);
     // A lane looks at 16 features of its row at a time.
-    bool fits = (l < INFINITY) & ((lost == 0));
+    bool fits = l < INFINITY && lost == 0;
     constexpr int BPG = 16 / C::RPB;          // blocks with them
     const uint32_t zero = (uint32_t)zeros >> gr_e;
 #pragma unroll
