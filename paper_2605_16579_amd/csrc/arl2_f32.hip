@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // x s = hi + lo, s a power of two, hi = half(x s), lo = half(x s - hi): 23 of the 24 bits of an fp32 value (all of every second one's).
 // A product a b is a.hi b.hi + a.hi b.lo + a.lo b.hi; a.lo b.lo, 2^-24 of it, is left out.  The half-precision matrix
 // instructions multiply exactly and round an fp32 sum once per 8 or 16 products, the fp32 ones once per product, so the results are
-// closer to 64 bits than with fp32 products, from 32 keys on (`halves_pay`) and whatever the size of the logits.  Relative 2-norm errors, fp32 products
+// closer to 64 bits than with fp32 products, from 33 keys on (`halves_pay`) and whatever the size of the logits.  Relative 2-norm errors, fp32 products
 // and this: with a state 1.57e-7 and 1.23e-7 at D = 128, 1.21e-7 and 1.13e-7 at D = 64; softmax alone, D = 128: 33 keys 1.67e-7 and 1.57e-7, 777 keys
 // 3.0e-7 and 2.0e-7, logits four times as large 4.8e-7 and 4.0e-7, queries and keys along one direction with logits of 45 2.5e-6 and 2.4e-6 (with one
 // chain of products over all 128 features 1.75e-7, 2.2e-7, 5.2e-7 and 3.1e-6).  The scales keep lo parts normal numbers: query rows
@@ -350,12 +350,13 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // values' way to LDS, then those of O^T beside the keys' way.  Each is 24 products per wavefront, in steps of three with one load's worth
 // of splitting.
 //
-// What bounds it: the vector work (about 480 instructions per wavefront and iteration, half of them the splitting) and the
-// fragments from LDS, which a SIMD does in turn, and the products, which run beside them only in part: 3000 + 3300 cycles per iteration
+// What bounds it: the vector work (about 520 instructions per wavefront and iteration, half of them the splitting) and the
+// fragments from LDS, which a SIMD does in turn, and the products, which run beside them only in part: 6400 cycles per iteration
 // for 2 x 1536 of products.  v_fma_mixlo / mixhi_f16 take 8 cycles on a SIMD, the conversion of a pair and v_fma_mix_f32 4
 // each, hence the separate steps of `put`.  Three bf16 parts (all 24 bits, six products, 32 cycles to split a pair against 20) were
-// 30 % slower.  Measured per pass, against fp32 products: 12 heads x 128, 1560 tokens 99 us, 165 us; 8 x 24 x 128, 777 tokens 361 and
-// 633 us; 2 x 16 x 64, 1560 tokens 126 and 181 us.
+// 30 % slower.  Measured per pass with a state, against fp32 products: 12 heads x 128, 1560 tokens 101 us, 165 us; 8 x 24 x 128, 777 tokens 370
+// and 664 us; 2 x 16 x 64, 1560 tokens 130 and 183 us.  Of these a scale per feature of the values with the search for lost bits takes 2 %
+// (64 heads x 128, 100 tokens 0.7 of 12.0 us) and the second chain of S^T 0.5 %.
 template <int D, int QW>
 struct F32HalfCfg {
     static constexpr int NKG = 4, NRG = 2, NW = NKG * NRG;   // key groups, row groups, wavefronts
@@ -1167,23 +1168,24 @@ __global__ __launch_bounds__(512, 2) void commit_f32_kernel(CommitArgs a)
 }
 
 // Whether tiles of 64 rows on sums of halves are faster than `tiles` ones of 32 rows on fp32 products.  Their start and end are longer
-// (scales, splitting, the state's product: 8.5 against 6.8 us for 64 keys at D = 128) and the key loop is shorter; and while 32-row
-// tiles find a CU for each of their halves these are 16-row ones.  In us, fp32 products and halves:
-//   up to 128 tiles, D = 128: 4 heads, 1000 rows, 320 keys 12.3 and 13.1, 512 keys 15.8 and 15.7, 800 keys 24.2 and 22.7; D = 64:
-//     800 keys 14.1 and 15.1, 1560 keys 24.7 and 25.1, 2000 keys 28.2 and 27.8;
-//   beyond: D = 128, 192 tiles 64 keys 10.2 and 8.7, 800 keys 39 and 23; 608 tiles 64 keys 21.6 and 19.5, 800 keys 80 and 54;
-//     D = 64, 192 tiles 64 keys 6.5 and 6.1, 800 keys 21.4 and 15.5; 608 tiles, where three workgroups of the fp32 kernel share a CU: 128
-//     keys 11.1 and 12.3, 200 keys 16.1 and 16.1, 512 keys 27.2 and 23.2;
-//   up to 31 keys: a sum of so few rounds less often than operands lose bits (relative error at D = 128, 1 key 0 and 4.5e-8, 8 keys 1.1e-7 and 1.2e-7,
-//     24 keys 1.5e-7 both), and fp32 products take 13.0 us where halves take 12.3 (60 heads, 250 rows; D = 64: 7.9 and 8.1);
-//   rows that leave a row group empty: up to 32 of them 300 heads x 128, 500 keys 36 and 41; 65 to 96 a third more work.
+// (scales, splitting, the search for lost bits) and the key loop is shorter; and while 32-row
+// tiles find a CU for each of their halves these are 16-row ones.  In us, softmax alone, fp32 products and halves:
+//   up to 128 tiles, D = 128: 4 heads, 1000 rows, 640 keys 19.0 and 19.0, 720 keys 21.9 and 21.4, 800 keys 24.4 and 23.9; D = 64: 2048 keys 29.3
+//     and 29.8, 4096 keys 53.9 and 54.3 (2 heads, 1560 rows 58.1 and 54.3), 8192 keys 106 and 103;
+//   beyond: D = 128, 200 tiles 64 keys 10.1 and 9.1; 600 tiles 32 keys 18.2 and 20.5, 48 keys 21.9 and 20.6, 128 keys 22.7 and 20.4;
+//     D = 64, 200 tiles 64 keys 6.46 and 6.46, 256 keys 8.9 and 8.0, 400 tiles 64 keys 9.8 and 8.1; 608 tiles, where three workgroups of the
+//     fp32 kernel share a CU: 384 keys 21.8 and 20.8, 512 keys 26.8 and 24.5;
+//   up to 32 keys: as above, and a sum of so few rounds less often than operands lose bits (relative error at D = 128, 1 key 0 and 4.5e-8, 8
+//     keys 1.1e-7 and 1.2e-7, 24 keys 1.5e-7 both);
+//   rows that leave a row group empty: up to 32 of them 300 heads x 128, 500 keys 36 and 41; 65 to 96 a third more work: 150 heads, 90 rows, 512
+//     keys 43.0 and 40.1.
 bool halves_pay(const FwdArgs &a, long long tiles)
 {
     const int n_rb = (a.Lq + 31) / 32;
-    if (n_rb == 1 || a.Lkv < 32) return false;
+    if (n_rb == 1 || a.Lkv <= 32) return false;
     if (n_rb == 3 && a.Lkv < 512) return false;
-    if (a.D == 128) return tiles > kNumCu / 2 || a.Lkv >= 640;
-    return tiles > 2 * kNumCu ? a.Lkv >= 384 : tiles > kNumCu / 2 || a.Lkv >= 2048;
+    if (a.D == 128) return tiles > kNumCu / 2 || a.Lkv >= 704;
+    return tiles > 2 * kNumCu ? a.Lkv >= 384 : tiles > kNumCu / 2 || a.Lkv >= 4096;
 }
 
 }  // namespace

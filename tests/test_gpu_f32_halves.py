@@ -35,7 +35,7 @@ def error(got, ref):
 
 @pytest.mark.parametrize("B,H,Lq,Lkv,D", [
     (1, 130, 33, 1, 128), (1, 70, 64, 31, 64), (1, 140, 40, 33, 64), (1, 66, 100, 129, 128),     # one block, key groups without one
-    (1, 50, 70, 520, 128), (2, 3, 40, 700, 128), (1, 2, 40, 2050, 64), (1, 60, 257, 384, 64),    # last rows and keys of a tile
+    (1, 50, 70, 520, 128), (2, 3, 40, 700, 128), (2, 3, 40, 740, 128), (1, 2, 40, 2050, 64), (1, 2, 40, 4100, 64), (1, 60, 257, 384, 64),    # last rows and keys of a tile
     (3, 8, 1000, 128, 128), (1, 12, 1560, 97, 128), (2, 136, 64, 64, 64)])                         # whole tiles, halved last ones
 def test_softmax(B, H, Lq, Lkv, D):
     q, k, v = draw(1, B, Lq, H, D), draw(2, B, Lkv, H, D), draw(3, B, Lkv, H, D)
@@ -54,7 +54,7 @@ def test_one_key_is_copied(D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("Lkv", [32, 33, 64, 128, 700])
+@pytest.mark.parametrize("Lkv", [33, 64, 128, 700])
 @pytest.mark.parametrize("kind", ["usual", "large logits", "very large logits", "one direction", "larger keys later"])
 def test_no_less_exact_than_fp32_products(kind, Lkv, D):
     """Against the kernel on fp32 products, which serves launches of up to 32 rows."""
