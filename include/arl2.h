@@ -110,7 +110,7 @@ size_t arl2_workspace_bytes(const arl2_desc *desc);
  * as three of halves, wherever that is no further from 64-bit arithmetic than fp32 products are; values
  * that two halves do not stand for (infinities, NaN, sizes too far apart) are found and multiplied in fp32.
  * What is not found: single values of a feature of v beside ones more than 2^10 times as large, which are
- * exact to 2^-35 of the largest among the first 128 keys.
+ * exact to 2^-34 of the largest among the first 128 keys.
  */
 arl2_status arl2_hybrid_attn_fwd(const arl2_desc *desc,
                                  const void *q, const void *k, const void *v,

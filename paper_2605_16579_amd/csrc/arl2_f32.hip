@@ -334,12 +334,12 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // 3.0e-7 and 2.0e-7, logits four times as large 4.8e-7 and 4.0e-7, queries and keys along one direction with logits of 45 2.5e-6 and 2.4e-6 (with one
 // chain of products over all 128 features 1.75e-7, 2.2e-7, 5.2e-7 and 3.1e-6).  The scales keep lo parts normal numbers: query rows
 // have one each, the keys of a tile one from the largest of its first 128, with room for 64 times as large ones, each feature of the
-// values, which is an output of its own, one from its largest among those keys, with the same room, probabilities 2^15.
+// values, which is an output of its own, one from its largest among those keys, with room for 128 times as large ones, probabilities 2^15.
 // What has no such parts is found out and done again on the fp32 instructions, by the same workgroup: infinities, NaN and values beyond the
 // room (they end in a sum that is not finite); rows whose output is so small beside the scales that what lo lacks would show (`fits`);
 // features whose values fall far below their scale for a few blocks (`look_for_lost`); and queries so large against the keys' scale that
 // what the smallest parts of keys lack, 2^-35 of the largest, would show in logits (`kLargest`).  Single values of a feature among others are
-// exact to 2^-35 of its largest among the first 128 keys.
+// exact to 2^-34 of its largest among the first 128 keys.
 //
 // A workgroup owns 64 (or 32) query rows: two row groups of QW rows x four key groups, one wavefront each.  In an iteration a
 // key group takes a block of 32 keys; its two wavefronts bring half of the block each from memory into registers and, as halves,
@@ -570,7 +570,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         put(third_, x, v_scale, (v_put ^ (16 * (D == 128 ? 8 * (i & 1) ^ (i & 2) : 2 * (i & 1)))) + C::RPI * i * (2 * D), kv_part);
     };
     // The largest value that a lane sees of each of its features in two rows of a block each (no NaN; of all the wavefront's rows in the first
-    // block), and whether over three blocks and more, or the first, all of it was below 1/2, 2^-10 of what the scale was taken from, and not zero.
+    // block), and whether over three blocks and more, or the first, all of it was below 1/4, 2^-10 of what the scale was taken from, and not zero.
     float seen[4];
     uint64_t lost = 0;
     auto look = [&](const f32x4 &x, const f32x4 &y) {
@@ -580,7 +580,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     auto look_for_lost = [&]() {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            lost |= __ballot(seen[e] > 0.f) & __ballot(seen[e] * v_scale[e] < 0.5f);
+            lost |= __ballot(seen[e] > 0.f) & __ballot(seen[e] * v_scale[e] < 0.25f);
             seen[e] = 0.f;
         }
     };
@@ -751,7 +751,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
     auto logits = [&](int blk) {
 #pragma unroll
         for (int i = 0; i < NL; ++i) s[i] = sm[i / C::RPB][i % C::RPB] + sa[0][i / C::RPB][i % C::RPB] + sa[1][i / C::RPB][i % C::RPB];
-        if (32 * blk + 32 > Lkv) {                                  // keys past the end
+        if (__builtin_expect(32 * blk + 32 > Lkv, 0)) {             // keys past the end
 #pragma unroll
             for (int i = 0; i < NL; ++i)
                 if (32 * blk + FPT * (i >> 2) + 4 * gr + (i & 3) >= Lkv) s[i] = -INFINITY;
@@ -817,7 +817,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
         lds_barrier();                                              // the first keys have been read
         vm = *(const f32x4 *)(most + 4 * col);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v_scale[e] = scale_to(vm[e], 9)[0];
+        for (int e = 0; e < 4; ++e) v_scale[e] = scale_to(vm[e], 8)[0];
         zeros = __ballot(vm[0] == 0.f && vm[1] == 0.f && vm[2] == 0.f && vm[3] == 0.f);
     }
     static_for<0, NLD>([&](auto i_) { static_for<0, 3>([&](auto third_) { put_k(third_, i_, k0[decltype(i_)::value]); }); });
@@ -982,7 +982,7 @@ __device__ __forceinline__ bool fwd_f32_half_tile(const FwdArgs &a, f32x2 x2, in
                 least = fminf(least, mine(sizes, i));
                 nan = fmaf(x[ob * C::RPB + i], 0.f, nan);          // of infinities too, which are no sums of halves either
             }
-            if (__any(!(least >= 65536.f && nan == 0.f))) {
+            if (__builtin_expect(__any(!(least >= 65536.f && nan == 0.f)), 0)) {
                 const float *src = (const float *)(a.q_lin != nullptr ? a.q_lin : a.q) + row_off + 8 * gr_e;
                 acc_t y = acc_t(0.f);
 #pragma unroll
