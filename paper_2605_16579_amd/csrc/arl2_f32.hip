@@ -354,8 +354,8 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(FwdArgs a, int n_rb, in
 // fragments from LDS, which a SIMD does in turn, and the products, which run beside them only in part: 6400 cycles per iteration
 // for 2 x 1536 of products.  v_fma_mixlo / mixhi_f16 take 8 cycles on a SIMD, the conversion of a pair and v_fma_mix_f32 4
 // each, hence the separate steps of `put`.  Three bf16 parts (all 24 bits, six products, 32 cycles to split a pair against 20) were
-// 30 % slower.  Measured per pass with a state, against fp32 products: 12 heads x 128, 1560 tokens 101 us, 165 us; 8 x 24 x 128, 777 tokens 370
-// and 664 us; 2 x 16 x 64, 1560 tokens 130 and 183 us.  Of these a scale per feature of the values with the search for lost bits takes 2 %
+// 30 % slower.  Measured per pass with a state, against fp32 products: 12 heads x 128, 1560 tokens 99 us, 162 us; 8 x 24 x 128, 777 tokens 359
+// and 631 us; 2 x 16 x 64, 1560 tokens 125 and 181 us.  Of these a scale per feature of the values with the search for lost bits takes 2 %
 // (64 heads x 128, 100 tokens 0.7 of 12.0 us) and the second chain of S^T 0.5 %.
 template <int D, int QW>
 struct F32HalfCfg {
@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(512, 2) void fwd_f32_halves_kernel(FwdArgs a, int n
         done = fwd_f32_half_tile<D, 16>(a, x2, bh, q0, smem);
     }
     // Four wavefronts for half of the rows each.  All tiles done again, 1560 tokens with a state, found before the key loop (infinite or
-    // outsized first keys) and after it (everything else): 12 heads x 128 192 and 274 us (157 on fp32 products alone), 2 x 16 x 64 239 and 344
+    // outsized first keys) and after it (everything else): 12 heads x 128 192 and 271 us (157 on fp32 products alone), 2 x 16 x 64 239 and 340
     // us (182).  (With 32-row tiles left to four of the eight wavefronts the first took 244 and 269 us.  A way out before the loop for values too
     // costs other launches 1-3 %.)
     if (!done) {
